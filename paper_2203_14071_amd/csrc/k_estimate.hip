@@ -32,7 +32,7 @@ __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, doub
   const double det = 1.0 - e1 * e1 - e2 * e2;
   const double g = 1.0 / (det * det);
   const double a11 = 1.0 + e1, a12 = e2, a22 = 1.0 - e1;
-  const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
+  const int64_t c0 = a.fold_offsets[s], c1 = a.fold_offsets[s + 1];
   const double *lw = a.logw + (int64_t)s * a.num_r;
   double mx = -INFINITY, acc = 0.0;
   for (int k0 = 0; k0 < a.num_r; k0 += 4) {

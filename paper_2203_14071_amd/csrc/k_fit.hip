@@ -5,6 +5,10 @@
 //   ln L(e, alpha_k) = D_k^2 / (2 M_k) - ln(M_k) / 2            (flux marginalised)
 //   ln L(e) = m + ln sum_k exp(ln w_k + ln L(e, alpha_k) - m)   (scale marginalised)
 //
+// f is even in (u, v): in the FP64 form a cell and its mirror image are one
+// record (W and W Re Vbar added, k_compact.hip), in the mixed form a record
+// is one cell.
+//
 // One thread per grid point, all knots of that point in registers (D_k, M_k),
 // a uniform loop over the source's cells: each cell record comes in through
 // one scalar load shared by the wave; it carries sqrt(W_c) in the profile's

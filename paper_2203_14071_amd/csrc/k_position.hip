@@ -22,15 +22,29 @@ __global__ __launch_bounds__(256) void k_pos_prep(PosPrepArgs a) {
   const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
   const int h = (a.n_side - 1) / 2;
   for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
-    const double uc = (double)a.ix[c] / theta, vc = (double)a.iy[c] / theta;   // as the compaction
-    const double W = a.wsum[c], vr = a.vre[c], vi = a.vim[c];
+    // cell centre (as the compaction) and sqrt(W) Vbar
+    double uc, vc, br, bi;
+    if (kMixed) {
+      const double rw = sqrt(a.wsum[c]);
+      uc = (double)a.ix[c] / theta;
+      vc = (double)a.iy[c] / theta;
+      br = rw;
+      bi = rw;
+    } else {
+      const FoldAux x = a.aux[c];
+      uc = (double)x.ix / theta;
+      vc = (double)x.iy / theta;
+      br = a.fit64[c].w;
+      bi = x.bi;
+    }
+    const double vr = kMixed ? a.vre[c] : 0.0, vi = kMixed ? a.vim[c] : 0.0;
     for (int p1 = 0; p1 < a.n_side; ++p1) {
       const double dl = (double)(p1 - h) * a.step;
       for (int p2 = 0; p2 < a.n_side; ++p2) {
         const double dm = (double)(p2 - h) * a.step;
         double sn, cs;
         sincospi(2.0 * fma(uc, dl, vc * dm), &sn, &cs);
-        const double g = sqrt(W) * fma(vr, cs, vi * sn);
+        const double g = kMixed ? br * fma(vr, cs, vi * sn) : fma(br, cs, bi * sn);
         const int64_t o = c * a.n_pos + p1 * a.n_side + p2;
         if (kMixed)
           a.g32[o] = (float)g;

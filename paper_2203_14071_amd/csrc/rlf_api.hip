@@ -352,7 +352,10 @@ void free_facets(rlf_facets *f) {
   dfree(f->cells.wsum);
   dfree(f->cells.vre);
   dfree(f->cells.vim);
+  dfree(f->cells.fold_offsets);
+  dfree(f->cells.n_fold);
   dfree(f->cells.fit64);
+  dfree(f->cells.fold_aux);
   dfree(f->cells.fit32);
   dfree(f->d_logw);
   dfree(f->d_lsurf);
@@ -736,6 +739,17 @@ std::vector<int32_t> lane_order(const std::vector<double> &theta) {
   return order;
 }
 
+// Likelihood records for `total` dense cells: the mixed form's, one per cell,
+// and the folded FP64 ones, at most (side^2 + 1) / 2 per source.
+int alloc_records(rlf_ctx *c, rlf_facets *f, int64_t total) {
+  const int64_t folded = (total + f->n_src) / 2;
+  if (f->mixed)
+    if (int e = dalloc(c, &f->cells.fit32, total)) return e;
+  if (int e = dalloc(c, &f->cells.fit64, folded)) return e;
+  if (f->mixed) return RLF_OK;
+  return dalloc(c, &f->cells.fold_aux, folded);
+}
+
 // A facet object for `cat`; with `share`, the uv-sorted layout of `share`
 // (made for the same observation) is borrowed instead of sorted again.
 int create_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const rlf_facets *share,
@@ -788,14 +802,15 @@ int create_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const 
     if ((rc = dalloc(c, &f->acc.cell, total))) break;
     if ((rc = dalloc(c, &f->cells.offsets, f->n_src + 1))) break;
     if ((rc = dalloc(c, &f->cells.n_nonempty, f->n_src))) break;
+    if ((rc = dalloc(c, &f->cells.fold_offsets, f->n_src + 1))) break;
+    if ((rc = dalloc(c, &f->cells.n_fold, f->n_src))) break;
     if ((rc = dalloc(c, &f->cells.ix, total))) break;
     if ((rc = dalloc(c, &f->cells.iy, total))) break;
     if ((rc = dalloc(c, &f->cells.count, total))) break;
     if ((rc = dalloc(c, &f->cells.wsum, total))) break;
     if ((rc = dalloc(c, &f->cells.vre, total))) break;
     if ((rc = dalloc(c, &f->cells.vim, total))) break;
-    if (f->mixed && (rc = dalloc(c, &f->cells.fit32, total))) break;
-    if ((rc = dalloc(c, &f->cells.fit64, total))) break;
+    if ((rc = alloc_records(c, f, total))) break;
     if ((rc = dalloc(c, &f->d_logw, f->n_src * c->p.num_r))) break;
     if ((rc = dalloc(c, &f->d_lsurf, f->n_src * (int64_t)c->n_valid))) break;
     if ((rc = dalloc(c, &f->d_redo, f->n_src))) break;
@@ -813,6 +828,7 @@ int create_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const 
   if (e == hipSuccess) e = hipMemcpy(f->d_logw, logw.data(), sizeof(double) * logw.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemset(f->acc.cell, 0, sizeof(double4) * (size_t)total);
   if (e == hipSuccess) e = hipMemset(f->cells.offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1));
+  if (e == hipSuccess) e = hipMemset(f->cells.fold_offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1));
   if (e == hipSuccess) e = hipMemset(f->d_redo, 0, sizeof(int32_t) * (size_t)f->n_src);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
@@ -867,6 +883,7 @@ int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
     dfree(f->cells.vre);
     dfree(f->cells.vim);
     dfree(f->cells.fit64);
+    dfree(f->cells.fold_aux);
     dfree(f->cells.fit32);
     if (f->d_pos_g) (void)hipFree(f->d_pos_g);
     f->d_pos_g = nullptr;
@@ -882,8 +899,7 @@ int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
       if ((rc = dalloc(c, &f->cells.wsum, total))) break;
       if ((rc = dalloc(c, &f->cells.vre, total))) break;
       if ((rc = dalloc(c, &f->cells.vim, total))) break;
-      if (f->mixed && (rc = dalloc(c, &f->cells.fit32, total))) break;
-      if ((rc = dalloc(c, &f->cells.fit64, total))) break;
+      if ((rc = alloc_records(c, f, total))) break;
     } while (0);
     if (rc != RLF_OK) return rc;                       // the object stays unusable until freed
     f->dense_cap = total;
@@ -896,6 +912,7 @@ int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
   if (int e = upload_async(c, f->d_logw, logw.data(), sizeof(double) * logw.size())) return e;
   HIPCHK(c, hipMemsetAsync(f->acc.cell, 0, sizeof(double4) * (size_t)total, c->stream));
   HIPCHK(c, hipMemsetAsync(f->cells.offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1), c->stream));
+  HIPCHK(c, hipMemsetAsync(f->cells.fold_offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1), c->stream));
   HIPCHK(c, hipMemsetAsync(f->d_redo, 0, sizeof(int32_t) * (size_t)f->n_src, c->stream));
   if (int e = upload_sources(c, cat, f->d_src, f->d_src32)) return e;
   f->model_key = cat_key(cat);
@@ -1216,7 +1233,7 @@ int fit_args(rlf_ctx *c, const rlf_facets *f, FitArgs &fa) {
   fa.valid_index = c->d_vidx;
   fa.sk = c->d_sk;
   fa.logw = f->d_logw;
-  fa.offsets = f->cells.offsets;
+  fa.offsets = f->mixed ? f->cells.offsets : f->cells.fold_offsets;
   fa.fit64 = f->cells.fit64;
   fa.fit32 = f->cells.fit32;
   fa.lsurf = f->d_lsurf;
@@ -1228,7 +1245,9 @@ int fit_args(rlf_ctx *c, const rlf_facets *f, FitArgs &fa) {
     pa.n_pos = f->pos_side * f->pos_side;
     pa.step = f->pos_step;
     pa.src = f->d_src;
-    pa.offsets = f->cells.offsets;
+    pa.offsets = fa.offsets;
+    pa.fit64 = f->cells.fit64;
+    pa.aux = f->cells.fold_aux;
     pa.ix = f->cells.ix;
     pa.iy = f->cells.iy;
     pa.wsum = f->cells.wsum;
@@ -1314,6 +1333,7 @@ int enqueue_fit(rlf_ctx *c, const rlf_facets *f, const rlf_fit_opts &o, const rl
   ea.surface = o.want_surface ? out.surface : nullptr;
   if (f->mixed && f->pos_side <= 1) {
     ea.fit64 = f->cells.fit64;
+    ea.fold_offsets = f->cells.fold_offsets;
     ea.sk = c->d_sk;
     ea.logw = f->d_logw;
     ea.num_r = c->p.num_r;

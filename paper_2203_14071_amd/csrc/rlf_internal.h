@@ -51,14 +51,28 @@ struct DenseAcc {
   double4 *cell;             // per dense cell: (W, Z re, Z im, count) -- one address per run flush
 };
 
+// Of a folded facet cell: its index, and sqrt(W) times the imaginary part of
+// its mean visibility, the mirror cell's conjugated (a real sky's visibility
+// at -(u, v) is the conjugate of that at (u, v)).
+struct FoldAux {
+  int32_t ix, iy;
+  double bi;
+};
+
 // Compacted facets (CSR by source, cells sorted by (iy, ix)).
 struct Cells {
   int64_t *offsets;          // [n_src+1]
   int64_t *n_nonempty;       // [n_src]
   int32_t *ix, *iy, *count;
   double *wsum, *vre, *vim;
-  double4 *fit64;            // (W^{-1/6} uc, W^{-1/6} vc, W^{-1/3}, sqrt(W) Re Vbar) for the FP64 fit
-  float4 *fit32;             // same in FP32 for the mixed fit
+  float4 *fit32;             // mixed fit: (W^{-1/6} uc, W^{-1/6} vc, W^{-1/3}, sqrt(W) Re Vbar) per cell, FP32
+  // folded cells, CSR by source: the profile is even in (u, v), so a cell and
+  // its mirror image (-ix, -iy) enter every sum over cells with the same
+  // profile value and are kept as one record, W and W Re Vbar added
+  int64_t *fold_offsets;     // [n_src+1]
+  int64_t *n_fold;           // [n_src]
+  double4 *fit64;            // (W^{-1/6} uc, W^{-1/6} vc, W^{-1/3}, sqrt(W) Re Vbar) of a folded cell
+  FoldAux *fold_aux;         // FP64 form: what the position marginalisation needs besides
 };
 
 struct ModelArgs {
@@ -157,7 +171,7 @@ struct FitArgs {
   const int32_t *epts;       // [n_valid] flat grid indices, increasing
   const double *sk;          // [num_r] 4 pi^2 alpha_k^2 (radians)
   const double *logw;        // [n_src*num_r] ln(spline weight * prior density)
-  const int64_t *offsets;
+  const int64_t *offsets;    // of the records in use: folded cells (FP64 form), cells (mixed form)
   const double4 *fit64;
   const float4 *fit32;
   const int32_t *window;     // [n_src*4] inclusive grid boxes, or null (full grid)
@@ -191,8 +205,10 @@ struct PosPrepArgs {
   int32_t n_pos;             // n_side^2
   double step;               // offset spacing in radians
   const SrcModel *src;       // theta per source
-  const int64_t *offsets;
-  const int32_t *ix, *iy;
+  const int64_t *offsets;    // folded cells (FP64 form), cells (mixed form)
+  const double4 *fit64;      // FP64 form: the folded records
+  const FoldAux *aux;
+  const int32_t *ix, *iy;    // mixed form: the cells
   const double *wsum, *vre, *vim;
   double *g64;               // FP64 form
   float *g32;                // mixed form
@@ -257,6 +273,7 @@ struct EstimateArgs {
   // FP64 cell records before the maximum and the set are taken; null fit64 =
   // no recheck (FP64 form).
   const double4 *fit64;
+  const int64_t *fold_offsets; // of fit64
   const double *sk;          // [num_r] 4 pi^2 alpha_k^2
   const double *logw;        // [n_src*num_r]
   int32_t num_r;
