@@ -26,6 +26,8 @@
 // FP sums are atomic and order-dependent in their last bits.  Runs are summed
 // in FP64 in both forms (the mixed form's FP32 terms are widened per term).
 #include <algorithm>
+#include <map>
+#include <mutex>
 
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
@@ -36,19 +38,45 @@ namespace rlf {
 namespace {
 
 constexpr int kXcd = 8;
-constexpr int kWaves = 4;          // waves per block (1024-entry table or none)
-// FP64 launches of at least kBigTableTiles source tiles take a 2048-entry
-// table (32 KB of LDS: sin's x^5 term drops, one FMA per pair) in blocks of
-// 8 waves, so that four blocks per CU keep eight waves per SIMD in 128 KB;
-// smaller launches, whose blocks hold idle waves, keep the 16 KB table and
-// four-wave blocks (eight blocks per CU)
-constexpr int kBigTableTiles = 8;
-template <bool kMixed, int T>
-constexpr int waves_per_block() { return (!kMixed && T == 2048) ? 8 : kWaves; }
+// Waves per block of k_extract: the FP64 form's 2048-entry table takes 32 KB
+// of LDS, so that four blocks of 8 waves per CU keep eight waves per SIMD.
+template <bool kMixed>
+constexpr int waves_per_block() { return kMixed ? 4 : 8; }
+constexpr int kTileTable = 2048;
 constexpr int kNsF64 = 1, kNsMixed = 1;        // sources per lane
 constexpr int kGroupF64 = 2, kGroupMixed = 4;  // visibilities whose scalar loads are issued together
 constexpr double kNoRun = 1099511627776.0;    // 2^40: "no open run" (run keys are below 2^31 in magnitude)
 constexpr int32_t kNoKey = INT32_MIN;          // the same for the previous run's integer key
+
+// Catalogues of at most kVpSources sources go through k_extract_vp, larger
+// ones through k_extract: its lanes are sources, and with few tiles a chunk's
+// scalar loads are shared by few waves (one tile alone takes 1.75 times what
+// it takes among 16).  Measured, FP64, 9,266,880 visibilities, k_extract /
+// k_extract_vp with the gather: 64 sources 1.72 / 1.48 ms, 128 sources 3.21 /
+// 2.6 ms; 1,158,361 visibilities: 64 sources 0.36 / 0.26 ms, 128 0.48 / 0.46,
+// 150 0.47 / 0.54; the mixed form crosses at the same place.
+constexpr int kVpSources = 128;
+// ... and so do launches that would leave the chip idle through k_extract:
+// fewer than kTileWaves waves of kMinChunk visibilities (11,400 visibilities,
+// 100 sources: 129 us against 34).
+constexpr int64_t kMinChunk = 256, kTileWaves = 4096;
+
+// Work item of a wave: blocks go to the eight XCDs round-robin by index; item
+// (chunk, part) with the parts of a chunk (source tiles or groups, which read
+// the same visibilities) side by side on one XCD, and consecutive chunks on
+// consecutive XCDs, so that every XCD gets its share of the dense and of the
+// sparse regions of the plane (a contiguous eighth of the order per XCD
+// measured 3 % slower on the 1000-source field).
+struct WorkItem {
+  int64_t chunk;
+  int part;
+};
+__device__ __forceinline__ WorkItem work_item(int waves, int parts) {
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t w = (blockIdx.x / kXcd) * waves + wid;           // wave within its XCD
+  const uint32_t c = w / (uint32_t)parts;
+  return WorkItem{(int64_t)c * kXcd + blockIdx.x % kXcd, (int)(w - c * (uint32_t)parts)};
+}
 
 // One source of a lane: facet geometry and two open runs, the current cell's
 // and the cell the lane was in before it.  Near a cell boundary the sorted
@@ -141,24 +169,21 @@ __device__ __forceinline__ void enter_cell(LaneSrc &L, double4 *__restrict__ acc
 // steers the scalar registers: a minimum of 7 waves gives 94 SGPRs with two
 // spilled to VGPR lanes and measured 4.5 % faster than 6 (97 SGPRs, none
 // spilled), while 8 spills 17 and is 15 % slower.
-// T: entries of the FP64 form's exp table (1024 or 2048; the mixed form has none).
-template <bool kMixed, int NS, int G, int T>
-__global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8) void k_extract(
+template <bool kMixed, int NS, int G>
+__global__ __launch_bounds__((64 * waves_per_block<kMixed>()), kMixed ? 7 : 8) void k_extract(
     ExtractArgs a, const double4 *__restrict__ sgeo, const void *__restrict__ squad, const void *__restrict__ sres,
     const uint64_t *__restrict__ swt, double4 *__restrict__ acc) {
-  constexpr int kW = waves_per_block<kMixed, T>();
-  __shared__ double2 tab[kMixed ? 1 : T];
+  constexpr int kW = waves_per_block<kMixed>();
+  __shared__ double2 tab[kMixed ? 1 : kTileTable];
   if (!kMixed) {
-    cis_table_init<T>(tab);
+    cis_table_load<kTileTable>(tab, a.cis);
     __syncthreads();
   }
   const int lane = threadIdx.x & 63;
-  const int wid = threadIdx.x >> 6;
-  const int bpc = (a.n_tiles + kW - 1) / kW;                     // blocks per chunk
-  const int64_t xcd = blockIdx.x % kXcd, local = blockIdx.x / kXcd;
-  const int64_t chunk = (local / bpc) * kXcd + xcd;
-  const int tile = (int)(local % bpc) * kW + wid;
-  if (chunk >= a.n_chunks || tile >= a.n_tiles) return;          // uniform per wave
+  const WorkItem it = work_item(kW, a.n_tiles);
+  const int64_t chunk = it.chunk;
+  const int tile = it.part;
+  if (chunk >= a.n_chunks) return;                               // uniform per wave
 
   LaneSrc L[NS];
   int src[NS];
@@ -226,7 +251,7 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
           const double ph = fma(u, p[i].l, fma(v, p[i].m, gg[t].z * p[i].n1));
-          const double2 cs = cis2pi_f64<T>(ph, tab);
+          const double2 cs = cis2pi_f64<kTileTable>(ph, tab);
           const double x = fma(p[i].q11, qg[t].x, fma(p[i].q12x2, qg[t].y, fma(p[i].q22, qg[t].z, c0[i])));
           const double own = pow_m32_f64(x);                        // own model / spec, real after the shift
           enter_cell(L[i], acc, a.err, nproc, rint(__dmul_rn(u, p[i].theta)), rint(__dmul_rn(v, p[i].theta)));
@@ -298,291 +323,372 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8
   }
 }
 
-// Visibility-parallel extraction for catalogues of at most kVpSources
-// sources (the chunks of a sequential refinement): a wave takes kVpSteps
-// steps of 64 consecutive sorted visibilities, one per lane (coalesced
-// loads), and evaluates each pair exactly as k_extract does (sources in a
-// uniform outer loop, records in SGPRs).  Lanes that fall in one facet cell
-// are contiguous runs of the sorted order, so a segmented scan over the
-// lanes sums each run; a run that reaches the last lane stays open (its
-// sums carried in registers) and continues into the next step, so a cell is
-// updated once per run of the sorted order (four FP64 atomics at one
-// address), as in k_extract.  A one-source call keeps every lane busy
-// instead of one lane in 128.
-constexpr int kVpSources = 8;
-constexpr int kVpSteps = 32;
-
-// Cross-lane moves by DPP (a VALU operand modifier: no LDS round trip).
-// Lanes whose source is outside the pattern, or whose row is masked out,
-// receive `old`.
-template <int kCtrl, int kRowMask = 0xf>
-__device__ __forceinline__ int dpp(int old, int v) {
-  return __builtin_amdgcn_update_dpp(old, v, kCtrl, kRowMask, 0xf, false);
+// Visibility-parallel extraction: small catalogues, small observations, the
+// chunks of a sequential refinement (kVpSources, kTileWaves).  A wave takes a.chunk steps of 64
+// consecutive sorted visibilities, one per lane (coalesced loads, the next
+// step's issued before this one's arithmetic), for NS sources at a time
+// (their records wave-uniform, so the loads serve both), and evaluates each
+// pair exactly as k_extract does.  Along the sorted order a source stays in
+// one facet cell for runs of ~200 visibilities and alternates between two
+// cells near a boundary, so the wave keeps two open cells per source whose
+// keys are wave-uniform and whose sums are per-lane partial sums: a step that
+// falls into one open cell (about three in four) costs three additions, a
+// step split between them a masked set of each, and only a third cell makes
+// the wave reduce the less recent one over its lanes and add it to memory
+// (four FP64 atomics); a segmented scan over the lanes at every step would
+// this replaces, cost about four times the pair arithmetic.
+__device__ __forceinline__ double from_lane(double x, int l) {   // l wave-uniform
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                          __builtin_amdgcn_readlane(__double2loint(x), l));
 }
-template <int kCtrl, int kRowMask = 0xf>
-__device__ __forceinline__ double dpp(double old, double v) {
-  return __hiloint2double(dpp<kCtrl, kRowMask>(__double2hiint(old), __double2hiint(v)),
-                          dpp<kCtrl, kRowMask>(__double2loint(old), __double2loint(v)));
-}
-constexpr int kRowShr = 0x110;      // + n: row_shr:n (within rows of 16 lanes)
-constexpr int kRowBcast15 = 0x142;  // lane 15 of a row to the whole next row
-constexpr int kRowBcast31 = 0x143;  // lane 31 to rows 2 and 3
-constexpr int kWaveShr1 = 0x138;    // lane i - 1 to lane i across the wave
-constexpr int kWaveShl1 = 0x130;    // lane i + 1 to lane i across the wave
 
-// One level of the segmented scan: add the value `kCtrl` brings in when it
-// comes from the same segment.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ void seg_level(double &a, double &b, double &c, double &d, int seg) {
-  const bool take = dpp<kCtrl, kRowMask>(-1, seg) == seg;        // segment ids are >= 1
-  const double oa = dpp<kCtrl, kRowMask>(0.0, a), ob = dpp<kCtrl, kRowMask>(0.0, b);
-  const double oc = dpp<kCtrl, kRowMask>(0.0, c), od = dpp<kCtrl, kRowMask>(0.0, d);
-  if (take) {
-    a += oa;
-    b += ob;
-    c += oc;
-    d += od;
+// Sum the values the wave's two halves (kHalf) or the rows of 16 lanes in
+// each half hold, for two quantities at once: the lower half (even rows) of
+// the result sums a, the upper half (odd rows) b.
+template <bool kHalf>
+__device__ __forceinline__ double fold_lanes(double a, double b) {
+  const auto lo = kHalf ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
+                        : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = kHalf ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
+                        : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// x + x of the lane kRor below in the row of 16 (cyclic), by DPP (a VALU
+// operand modifier: no LDS round trip).
+template <int kRor>
+__device__ __forceinline__ double add_ror(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + kRor, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kRor, 0xf, 0xf, false);
+  return x + __hiloint2double(hi, lo);
+}
+
+// An open cell of a wave: wave-uniform run key (kNoRun: none) and count, the
+// lanes' partial sums.
+struct OpenCell {
+  double key;
+  int32_t n;
+  double w, zr, zi;
+  __device__ __forceinline__ void open(double k) {
+    key = k;
+    n = 0;
+    w = zr = zi = 0.0;
   }
+  // Add on the lanes of m, all 64 lanes active: three additions under an
+  // execution mask (written as selects, the compiler spends six more
+  // instructions and copies of all sums where the branches join).
+  __device__ __forceinline__ void add(uint64_t m, double vw, double vr, double vi) {
+    asm volatile("s_mov_b64 exec, %6\n\tv_add_f64 %0, %0, %3\n\tv_add_f64 %1, %1, %4\n\tv_add_f64 %2, %2, %5\n\t"
+                 "s_mov_b64 exec, -1"
+                 : "+v"(w), "+v"(zr), "+v"(zi)
+                 : "v"(vw), "v"(vr), "v"(vi), "s"(m));
+    n += __popcll(m);
+  }
+  // Reduce over the lanes and add to the dense cell: row r of 16 lanes ends
+  // up with component r, and its first lane issues one FP64 atomic (four
+  // consecutive addresses).
+  __device__ __forceinline__ void close(double4 *__restrict__ acc, int64_t base, int lane) const {
+    if (key == kNoRun) return;                                   // uniform
+    const double cnt = lane == 0 ? (double)n : 0.0;
+    double x = fold_lanes<false>(fold_lanes<true>(w, zi), fold_lanes<true>(zr, cnt));
+    // rows 0, 1: w, zr; rows 2, 3: zi, count
+    x = add_ror<8>(x);
+    x = add_ror<4>(x);
+    x = add_ror<2>(x);
+    x = add_ror<1>(x);
+    if ((lane & 15) == 0) unsafeAtomicAdd(&acc[base + (int32_t)key].x + (lane >> 4), x);
+  }
+};
+
+__device__ __forceinline__ double uniform(double x) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 
-// Inclusive scans of a, b, c, d over the lanes of the same segment (segment
-// ids non-decreasing along the lanes, >= 1): shifts by 1, 2, 4 and 8 within
-// rows of 16 lanes, then row 0's last lane into row 1 and row 2's into row
-// 3, then lane 31 into rows 2 and 3.
-__device__ __forceinline__ void seg_scan4(double &a, double &b, double &c, double &d, int seg) {
-  seg_level<kRowShr + 1, 0xf>(a, b, c, d, seg);
-  seg_level<kRowShr + 2, 0xf>(a, b, c, d, seg);
-  seg_level<kRowShr + 4, 0xf>(a, b, c, d, seg);
-  seg_level<kRowShr + 8, 0xf>(a, b, c, d, seg);
-  seg_level<kRowBcast15, 0xa>(a, b, c, d, seg);
-  seg_level<kRowBcast31, 0xc>(a, b, c, d, seg);
-}
+constexpr int kVpTable = 1024;
+constexpr int kVpThreads = 256;
 
-// The value of lane L (wave-uniform).
-template <int L>
-__device__ __forceinline__ double read_lane(double x) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), L);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), L);
-  return __hiloint2double(hi, lo);
-}
-
-// kUpd: the residual kept in sorted order is first updated for changed
-// source models (UpdateArgs, as k_update_sorted does, with the same sums),
-// in the same pass: each lane updates its visibilities while the first
-// source is extracted and the extraction reads the updated values.
-template <bool kMixed, bool kUpd>
-__global__ __launch_bounds__(256) void k_extract_vp(ExtractArgs a, const double4 *__restrict__ sgeo,
-                                                    const void *__restrict__ squad, const void *sres,
-                                                    const uint64_t *__restrict__ swt, double4 *__restrict__ acc,
-                                                    UpdateArgs u) {
-  __shared__ double2 tab[kMixed ? 1 : kCisTable];
+// kUpd (NS = 1, one source in the launch): the residual kept in sorted order
+// is first updated for changed source models (UpdateArgs, as k_update_sorted
+// does, with the same sums), in the same pass: each lane updates its
+// visibilities and extracts from the updated values.
+template <bool kMixed, int NS, bool kUpd>
+__global__ __launch_bounds__(kVpThreads) void k_extract_vp(ExtractArgs a, const double4 *__restrict__ sgeo,
+                                                           const void *sres, const uint64_t *__restrict__ swt,
+                                                           double4 *__restrict__ acc, UpdateArgs u) {
+  static_assert(!kUpd || NS == 1, "the update is fused for one source");
+  __shared__ double2 tab[kMixed ? 1 : kVpTable];
   if (!kMixed) {
-    cis_table_init(tab);
+    cis_table_load<kVpTable>(tab, a.cis);
     __syncthreads();
   }
   const int lane = threadIdx.x & 63;
-  const int64_t jw = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * (64 * kVpSteps);
+  const int groups = (a.n_src + NS - 1) / NS;
+  const WorkItem it = work_item(kVpThreads / 64, groups);
+  const int64_t jw = it.chunk * a.chunk * 64;
   if (jw >= a.sv.n_vis) return;                                  // uniform per wave
-  for (int s = 0; s < a.n_src; ++s) {                              // uniform
-    const SrcGeom g = a.geom[s];
-    const int64_t base = g.base + (int64_t)g.half * (g.side + 1);
-    const double half = (double)g.half, side = (double)g.side;
-    // the open run carried between steps (wave-uniform)
-    double ckey = kNoRun, cw = 0.0, cr = 0.0, ci = 0.0, cn = 0.0;
-    for (int t = 0; t < kVpSteps; ++t) {
-      const int64_t jb = jw + (int64_t)t * 64;
-      if (jb >= a.sv.n_vis) break;                               // uniform
-      const int64_t j = jb + lane;                               // < n_vis + 64: inside the padded arrays
-      const uint64_t wb = swt[j];
-      const bool use = j < a.sv.n_vis && wb != 0u;               // flagged and padding entries add nothing
-      const double ww = use ? __longlong_as_double((long long)wb) : 0.0;
-      const double4 gg = sgeo[j];
-      double zr, zi;
-      double xf, yf;
+  const int first = it.part * NS;
+  const int steps = (int)min((int64_t)a.chunk, (a.sv.n_vis - jw + 63) >> 6);
+
+  SrcModel p[NS];
+  SrcMixed pm[NS];
+  int64_t base[NS];
+  double half[NS], side[NS];
+  OpenCell A[NS], B[NS];
+  bool last_b[NS];                                               // uniform: the last visibility went to B
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    // a group past the last source repeats it without adding anything
+    const int s = __builtin_amdgcn_readfirstlane(a.order[min(first + i, a.n_src - 1)]);
+    if (kMixed) pm[i] = a.src32[s];
+    else p[i] = a.src[s];
+    const SrcGeom gm = a.geom[s];
+    base[i] = gm.base + (int64_t)gm.half * (gm.side + 1);
+    half[i] = (double)gm.half;
+    side[i] = (double)gm.side;
+    A[i].open(kNoRun);
+    B[i].open(kNoRun);
+    last_b[i] = false;
+  }
+  const bool two = NS == 1 || first + 1 < a.n_src;               // uniform
+  double own_scale[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) own_scale[i] = kMixed ? 0.0 : uniform(kPowM32Scale * p[i].flux);
+
+  // one visibility's data; element o of the wave's span (32-bit byte offsets
+  // from wave-uniform pointers)
+  struct Vis {
+    double4 g;
+    uint64_t w;
+    double2 rd;
+    float2 rf;
+  };
+  const char *gp = reinterpret_cast<const char *>(sgeo + jw), *wp = reinterpret_cast<const char *>(swt + jw);
+  const char *rp = reinterpret_cast<const char *>(sres) + jw * (kMixed ? sizeof(float2) : sizeof(double2));
+  auto load = [&](uint32_t o) {
+    Vis x{};
+    x.g = *reinterpret_cast<const double4 *>(gp + o * 32u);
+    x.w = *reinterpret_cast<const uint64_t *>(wp + o * 8u);
+    if (kMixed) x.rf = *reinterpret_cast<const float2 *>(rp + o * 8u);
+    else if (!kUpd) x.rd = *reinterpret_cast<const double2 *>(rp + o * 16u);
+    return x;
+  };
+  auto step = [&](const Vis &cur, uint32_t o) {
+    const double4 gg = cur.g;
+    const uint64_t wb = cur.w;
+    double2 rd = cur.rd;
+    float2 rf = cur.rf;
+
+    const double ww = __longlong_as_double((long long)wb);
+    double uu = 0.0, uv = 0.0, vv = 0.0, ws = 0.0;
+    float uuf = 0.0f, uvf = 0.0f, vvf = 0.0f;
+    const float spf = (float)gg.w;
+    if (kMixed) {
+      const float uf = (float)gg.x, vf = (float)gg.y;
+      uuf = uf * uf;
+      uvf = uf * vf;
+      vvf = vf * vf;
+    } else {
+      uu = __dmul_rn(gg.x, gg.x);
+      uv = __dmul_rn(gg.x, gg.y);
+      vv = __dmul_rn(gg.y, gg.y);
+      ws = __dmul_rn(ww, gg.w);
+    }
+    if (kUpd && jw + o < a.sv.n_vis) {
+      const int64_t j = jw + o;
       if (!kMixed) {
-        const double4 qg = reinterpret_cast<const double4 *>(squad)[j];
-        double2 rg;
-        if (kUpd && s == 0) {                                    // uniform
-          rg = make_double2(0.0, 0.0);
-          if (j < a.sv.n_vis) {
-            const double2 ao = sum_f64(gg.x, gg.y, gg.z, u.old64, 0, u.n_old, tab);
-            const double2 an = sum_f64(gg.x, gg.y, gg.z, u.new64, 0, u.n_new, tab);
-            double2 r = u.rs[j];
-            r = make_double2(fma(gg.w, ao.x, r.x), fma(gg.w, ao.y, r.y));
-            r = make_double2(fma(-gg.w, an.x, r.x), fma(-gg.w, an.y, r.y));
-            u.rs[j] = r;
-            const double wpos = __longlong_as_double((long long)wb);
-            rg = make_double2(wpos * r.x, wpos * r.y);
-            reinterpret_cast<double2 *>(u.sv.res)[j] = rg;
-          }
-        } else {
-          rg = reinterpret_cast<const double2 *>(sres)[j];
-        }
-        const SrcModel p = a.src[s];
-        const double ph = fma(gg.x, p.l, fma(gg.y, p.m, gg.z * p.n1));
-        const double2 cs = cis2pi_f64(ph, tab);
-        const double x = fma(p.q11, qg.x, fma(p.q12x2, qg.y, fma(p.q22, qg.z, 1.0)));
-        const double own = (kPowM32Scale * p.flux) * pow_m32_f64(x);
-        // w z = (w R) exp(-2 pi i ph) + (w spec) own
-        zr = fma(rg.x, cs.x, fma(rg.y, cs.y, qg.w * own));
-        zi = fma(rg.y, cs.x, -rg.x * cs.y);
-        xf = rint(__dmul_rn(gg.x, p.theta));
-        yf = rint(__dmul_rn(gg.y, p.theta));
+        const double2 ao = sum_f64(gg.x, gg.y, gg.z, u.old64, 0, u.n_old, tab);
+        const double2 an = sum_f64(gg.x, gg.y, gg.z, u.new64, 0, u.n_new, tab);
+        double2 r = u.rs[j];
+        r = make_double2(fma(gg.w, ao.x, r.x), fma(gg.w, ao.y, r.y));
+        r = make_double2(fma(-gg.w, an.x, r.x), fma(-gg.w, an.y, r.y));
+        u.rs[j] = r;
+        rd = make_double2(ww * r.x, ww * r.y);
+        reinterpret_cast<double2 *>(u.sv.res)[j] = rd;
       } else {
-        const float4 qg = reinterpret_cast<const float4 *>(squad)[j];
-        float2 rg = reinterpret_cast<const float2 *>(sres)[j];
-        if (kUpd && s == 0 && j < a.sv.n_vis) {                  // uniform source test
-          const float2 ao = sum_mixed(gg.x, gg.y, gg.z, u.old32, 0, u.n_old);
-          const float2 an = sum_mixed(gg.x, gg.y, gg.z, u.new32, 0, u.n_new);
-          const float sp = (float)gg.w;
-          rg = make_float2(fmaf(sp, ao.x, rg.x), fmaf(sp, ao.y, rg.y));
-          rg = make_float2(fmaf(-sp, an.x, rg.x), fmaf(-sp, an.y, rg.y));
-          reinterpret_cast<float2 *>(u.sv.res)[j] = rg;
-        }
-        const SrcMixed p = a.src32[s];
-        const double ph = fma(gg.x, p.l, fma(gg.y, p.m, gg.z * p.n1));
+        const float2 ao = sum_mixed(gg.x, gg.y, gg.z, u.old32, 0, u.n_old);
+        const float2 an = sum_mixed(gg.x, gg.y, gg.z, u.new32, 0, u.n_new);
+        rf = make_float2(fmaf(spf, ao.x, rf.x), fmaf(spf, ao.y, rf.y));
+        rf = make_float2(fmaf(-spf, an.x, rf.x), fmaf(-spf, an.y, rf.y));
+        reinterpret_cast<float2 *>(u.sv.res)[j] = rf;
+      }
+    }
+    const uint64_t all = __ballot(wb != 0u);                     // flagged and padding entries take no part
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (i > 0 && !two) break;                                  // uniform
+      double zr, zi, xf, yf;
+      if (!kMixed) {
+        const double ph = fma(gg.x, p[i].l, fma(gg.y, p[i].m, gg.z * p[i].n1));
+        const double2 cs = cis2pi_f64<kVpTable>(ph, tab);
+        const double x = fma(p[i].q11, uu, fma(p[i].q12x2, uv, fma(p[i].q22, vv, 1.0)));
+        const double own = own_scale[i] * pow_m32_f64(x);
+        // w z = (w R) exp(-2 pi i ph) + (w spec) own
+        zr = fma(rd.x, cs.x, fma(rd.y, cs.y, ws * own));
+        zi = fma(rd.y, cs.x, -rd.x * cs.y);
+        xf = rint(__dmul_rn(gg.x, p[i].theta));
+        yf = rint(__dmul_rn(gg.y, p[i].theta));
+      } else {
+        const double ph = fma(gg.x, pm[i].l, fma(gg.y, pm[i].m, gg.z * pm[i].n1));
         const float tt = (float)__builtin_amdgcn_fract(ph);
         const float sn = __builtin_amdgcn_sinf(tt), cs = __builtin_amdgcn_cosf(tt);
-        float fr = fmaf(rg.x, cs, rg.y * sn);
-        const float fi = fmaf(rg.y, cs, -(rg.x * sn));
-        const float x = fmaf(p.q11, qg.x, fmaf(p.q12x2, qg.y, fmaf(p.q22, qg.z, 1.0f)));
+        float fr = fmaf(rf.x, cs, rf.y * sn);
+        const float fi = fmaf(rf.y, cs, -(rf.x * sn));
+        const float x = fmaf(pm[i].q11, uuf, fmaf(pm[i].q12x2, uvf, fmaf(pm[i].q22, vvf, 1.0f)));
         const float qr = __builtin_amdgcn_rsqf(x);
-        fr = fmaf(qg.w * p.flux, qr * qr * qr, fr);
+        fr = fmaf(spf * pm[i].flux, qr * qr * qr, fr);
         zr = ww * (double)fr;
         zi = ww * (double)fi;
-        xf = rint(__dmul_rn(gg.x, p.theta));
-        yf = rint(__dmul_rn(gg.y, p.theta));
+        xf = rint(__dmul_rn(gg.x, pm[i].theta));
+        yf = rint(__dmul_rn(gg.y, pm[i].theta));
       }
-      const bool inb = fabs(xf) <= half && fabs(yf) <= half;
-      if (use && !inb) atomicOr(a.err, 1u);
-      const bool on = use && inb;
-      const double key = on ? fma(yf, side, xf) : kNoRun;
-      double vw = on ? ww : 0.0, vr = on ? zr : 0.0, vi = on ? zi : 0.0, vn = on ? 1.0 : 0.0;
-      // the carried run continues into lane 0's cell, or is closed now
-      if (ckey != kNoRun) {                                      // uniform
-        if (read_lane<0>(key) == ckey) {
-          if (lane == 0) {
-            vw += cw;
-            vr += cr;
-            vi += ci;
-            vn += cn;
-          }
-        } else if (lane == 0) {
-          double *c = &acc[base + (int32_t)ckey].x;
-          unsafeAtomicAdd(c, cw);
-          unsafeAtomicAdd(c + 1, cr);
-          unsafeAtomicAdd(c + 2, ci);
-          unsafeAtomicAdd(c + 3, cn);
+      const double key = fma(yf, side[i], xf);
+      uint64_t pend = all;
+      for (;;) {                                                 // uniform; nearly always one round
+        const uint64_t ma = __ballot(key == A[i].key) & pend, mb = __ballot(key == B[i].key) & pend;
+        A[i].add(ma, ww, zr, zi);
+        B[i].add(mb, ww, zr, zi);
+        if (ma | mb) last_b[i] = (mb >> (63 - __clzll((long long)(ma | mb)))) & 1;
+        pend &= ~(ma | mb);
+        if (!pend) break;
+        // the first lane left opens its cell in place of the less recent one
+        const int l = __ffsll((unsigned long long)pend) - 1;
+        if (fabs(from_lane(xf, l)) > half[i] || fabs(from_lane(yf, l)) > half[i]) {
+          // out of the facet: cannot happen unless uvw changed
+          if (lane == 0) atomicOr(a.err, 1u);
+          pend &= ~(1ull << l);
+          if (!pend) break;
+          continue;
         }
+        const double nk = from_lane(key, l);
+        if (!last_b[i]) {
+          const OpenCell x = A[i];
+          A[i] = B[i];
+          B[i] = x;
+        }
+        A[i].close(acc, base[i], lane);
+        A[i].open(nk);
+        last_b[i] = false;
       }
-      // segments: runs of equal keys along the lanes
-      const double prev = dpp<kWaveShr1>(key, key);
-      const bool head = lane == 0 || prev != key;
-      const int seg = __popcll(__ballot(head) & (((uint64_t)2 << lane) - 1));
-      seg_scan4(vw, vr, vi, vn, seg);
-      const int next = dpp<kWaveShl1>(-1, seg);
-      if (lane < 63 && next != seg && on) {                      // a run that ends inside this step
-        double *c = &acc[base + (int32_t)key].x;
-        unsafeAtomicAdd(c, vw);
-        unsafeAtomicAdd(c + 1, vr);
-        unsafeAtomicAdd(c + 2, vi);
-        unsafeAtomicAdd(c + 3, vn);
-      }
-      // the run reaching lane 63 stays open
-      ckey = read_lane<63>(key);
-      cw = read_lane<63>(vw);
-      cr = read_lane<63>(vr);
-      ci = read_lane<63>(vi);
-      cn = read_lane<63>(vn);
     }
-    if (ckey != kNoRun && lane == 0) {
-      double *c = &acc[base + (int32_t)ckey].x;
-      unsafeAtomicAdd(c, cw);
-      unsafeAtomicAdd(c + 1, cr);
-      unsafeAtomicAdd(c + 2, ci);
-      unsafeAtomicAdd(c + 3, cn);
-    }
+  };
+  // two steps per iteration, the loads of a step issued one step ahead (the
+  // arrays are padded by two steps of zero weight, which take no part)
+  uint32_t o = lane;
+  Vis v0 = load(o);
+  for (int t = 0; t < steps; t += 2, o += 128) {
+    const Vis v1 = load(o + 64);
+    step(v0, o);
+    v0 = load(o + 128);
+    if (t + 1 < steps) step(v1, o + 64);
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    if (i > 0 && !two) break;
+    A[i].close(acc, base[i], lane);
+    B[i].close(acc, base[i], lane);
   }
 }
 
-// Resident blocks of an extraction kernel on the current device (cached).
+// Resident blocks of a kernel on the current device (kept per kernel and
+// device; the value is a property of both, so a race writes it twice).
 template <class K>
-int64_t resident_blocks(K kernel, int slot, int threads) {
-  static int64_t cache[3][16] = {};
+int64_t resident_blocks(K kernel, int threads) {
+  static std::mutex mu;
+  static std::map<std::pair<const void *, int>, int64_t> cache;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return 0;
-  if (!cache[slot][dev]) {
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  std::lock_guard<std::mutex> lock(mu);
+  int64_t &n = cache[{reinterpret_cast<const void *>(kernel), dev}];
+  if (!n) {
     int per_cu = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
       (void)hipGetLastError();
       return 0;
     }
-    cache[slot][dev] = (int64_t)per_cu * cus;
+    n = (int64_t)per_cu * cus;
   }
-  return cache[slot][dev];
+  return n;
 }
 
-// Visibilities per wave: near a nominal 2048, sized so the grid is a whole
-// number of rounds of resident blocks (a last round nearly empty would leave
-// the chip idle for a whole block's duration).
-int64_t chunk_size(int64_t n_vis, int64_t bpc, int64_t capacity) {
-  constexpr int64_t kNominal = 2048, kMin = 256;
-  auto blocks = [&](int64_t chunk) { return ((n_vis + chunk - 1) / chunk + kXcd - 1) / kXcd * kXcd * bpc; };
-  if (capacity <= 0 || n_vis <= 0) return kNominal;
-  const int64_t b0 = blocks(kNominal);
-  const int64_t rounds = std::max<int64_t>(1, (b0 + capacity / 2) / capacity);
-  const int64_t max_chunks = std::max<int64_t>(kXcd, (rounds * capacity / bpc) / kXcd * kXcd);
-  return std::max(kMin, (n_vis + max_chunks - 1) / max_chunks);
+// Visibilities per wave of k_extract, sized so that the waves are a whole
+// number of rounds of the resident ones (a last round nearly empty would leave
+// the chip idle for a whole wave's duration): near 2048 where that makes at
+// least four rounds, near 450 otherwise.  A chunk of the dense core of the
+// plane takes longer than one of its outskirts, and fewer rounds leave that
+// unevened: 2,316,728 visibilities, 600 sources, mixed form: one round of
+// 2829 1.94 ms, six of 471 1.57 ms; 1,158,361 and 1000, FP64: one of 2263
+// 1.95 ms, four of 565 1.68 ms.
+int64_t chunk_size(int64_t n_vis, int64_t n_tiles, int64_t capacity) {
+  constexpr int64_t kLarge = 2048, kSmall = 450;
+  if (capacity <= 0 || n_vis <= 0) return kLarge;
+  const int64_t nominal = n_vis * n_tiles >= 4 * kLarge * capacity ? kLarge : kSmall;
+  const int64_t w0 = (n_vis + nominal - 1) / nominal * n_tiles;
+  const int64_t rounds = std::max<int64_t>(1, (w0 + capacity / 2) / capacity);
+  const int64_t max_chunks = std::max<int64_t>(1, rounds * capacity / n_tiles);
+  return std::max(kMinChunk, (n_vis + max_chunks - 1) / max_chunks);
+}
+
+// Steps of 64 visibilities per wave of k_extract_vp: enough waves to fill the
+// chip once, between 2 and 64 steps (a wave ends with two reductions and
+// eight atomics per source).
+int64_t vp_steps(int64_t n_vis, int64_t groups, int64_t capacity) {
+  const int64_t total = (n_vis + 63) / 64 * groups;
+  return std::min<int64_t>(64, std::max<int64_t>(2, (total + capacity - 1) / std::max<int64_t>(1, capacity)));
+}
+
+// Blocks whose waves cover every (chunk, part): per XCD, the parts of every
+// eighth chunk (work_item).
+unsigned grid_blocks(int64_t chunks, int64_t parts, int64_t waves) {
+  return (unsigned)(kXcd * (((chunks + kXcd - 1) / kXcd * parts + waves - 1) / waves));
+}
+
+template <bool kMixed, int NS, bool kUpd>
+hipError_t run_vp(ExtractArgs a, const UpdateArgs &u, hipStream_t st) {
+  const Sorted &v = a.sv;
+  auto kern = k_extract_vp<kMixed, NS, kUpd>;
+  constexpr int kW = kVpThreads / 64;
+  const int64_t groups = (a.n_src + NS - 1) / NS;
+  const int64_t capacity = resident_blocks(kern, kVpThreads) * kW;
+  a.chunk = (int32_t)vp_steps(v.n_vis, groups, capacity > 0 ? capacity : 4096);
+  const int64_t chunks = (v.n_vis + 64 * (int64_t)a.chunk - 1) / (64 * (int64_t)a.chunk);
+  hipLaunchKernelGGL(kern, dim3(grid_blocks(chunks, groups, kW)), dim3(kVpThreads), 0, st, a, v.geo, v.res,
+                     reinterpret_cast<const uint64_t *>(v.wt), a.acc.cell, u);
+  return hipGetLastError();
+}
+
+template <bool kMixed, int NS, int G>
+hipError_t run_tiles(ExtractArgs a, hipStream_t st) {
+  const Sorted &v = a.sv;
+  auto kern = k_extract<kMixed, NS, G>;
+  constexpr int kW = waves_per_block<kMixed>();
+  a.n_tiles = (a.n_src + 64 * NS - 1) / (64 * NS);
+  a.chunk = (int32_t)chunk_size(v.n_vis, a.n_tiles, resident_blocks(kern, 64 * kW) * kW);
+  a.n_chunks = (v.n_vis + a.chunk - 1) / a.chunk;
+  hipLaunchKernelGGL(kern, dim3(grid_blocks(a.n_chunks, a.n_tiles, kW)), dim3(64 * kW), 0, st, a, v.geo, v.quad, v.res,
+                     reinterpret_cast<const uint64_t *>(v.wt), a.acc.cell);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_extract(const ExtractArgs &a0, int mixed, hipStream_t st, const UpdateArgs *upd) {
-  const int ns = mixed ? kNsMixed : kNsF64;
-  ExtractArgs a = a0;
-  const Sorted &v = a.sv;
-  const uint64_t *wt = reinterpret_cast<const uint64_t *>(v.wt);
-  // the update is fused only for one changed source (a serial refinement):
-  // more sources' sums in the first source's pass lengthen the extraction's
-  // latency-bound steps by more than the separate pass costs
-  const bool fuse = upd && a.n_src <= kVpSources && upd->n_old <= 1 && upd->n_new <= 1;
-  if (upd && !fuse) {
+hipError_t launch_extract(const ExtractArgs &a, int mixed, hipStream_t st, const UpdateArgs *upd) {
+  // the update is fused into the extraction of a single source (a serial
+  // refinement): with more, other waves would read the residual meanwhile
+  const bool fuse = upd && a.n_src == 1;
+  if (fuse) return mixed ? run_vp<true, 1, true>(a, *upd, st) : run_vp<false, 1, true>(a, *upd, st);
+  if (upd) {
     hipError_t e = launch_update_sorted(*upd, mixed, st);
     if (e != hipSuccess) return e;
   }
-  if (a.n_src <= kVpSources) {
-    const int64_t waves = (v.n_vis + 64 * kVpSteps - 1) / (64 * kVpSteps);
-    const dim3 grid((unsigned)((waves + 3) / 4));
-    UpdateArgs u = fuse ? *upd : UpdateArgs{};
-    if (fuse) {
-      if (mixed)
-        hipLaunchKernelGGL((k_extract_vp<true, true>), grid, dim3(256), 0, st, a, v.geo, v.quad, v.res, wt, a.acc.cell, u);
-      else
-        hipLaunchKernelGGL((k_extract_vp<false, true>), grid, dim3(256), 0, st, a, v.geo, v.quad, v.res, wt, a.acc.cell, u);
-    } else {
-      if (mixed)
-        hipLaunchKernelGGL((k_extract_vp<true, false>), grid, dim3(256), 0, st, a, v.geo, v.quad, v.res, wt, a.acc.cell, u);
-      else
-        hipLaunchKernelGGL((k_extract_vp<false, false>), grid, dim3(256), 0, st, a, v.geo, v.quad, v.res, wt, a.acc.cell, u);
-    }
-    return hipGetLastError();
+  const int64_t tile_waves = (a.sv.n_vis + kMinChunk - 1) / kMinChunk * ((a.n_src + 63) / 64);
+  if (a.n_src <= kVpSources || tile_waves < kTileWaves) {
+    const UpdateArgs none{};
+    if (a.n_src == 1) return mixed ? run_vp<true, 1, false>(a, none, st) : run_vp<false, 1, false>(a, none, st);
+    return mixed ? run_vp<true, 2, false>(a, none, st) : run_vp<false, 2, false>(a, none, st);
   }
-  a.n_tiles = (a.n_src + 64 * ns - 1) / (64 * ns);
-  const bool big = !mixed && a.n_tiles >= kBigTableTiles;
-  const int waves = big ? waves_per_block<false, 2048>() : kWaves;
-  const int64_t bpc = (a.n_tiles + waves - 1) / waves;
-  auto kmixed = k_extract<true, kNsMixed, kGroupMixed, 1024>;   // (T unused: no table)
-  auto kf64 = k_extract<false, kNsF64, kGroupF64, 1024>;
-  auto kf64big = k_extract<false, kNsF64, kGroupF64, 2048>;
-  const int64_t capacity = mixed ? resident_blocks(kmixed, 1, 64 * kWaves)
-                                 : (big ? resident_blocks(kf64big, 2, 64 * waves) : resident_blocks(kf64, 0, 64 * kWaves));
-  a.chunk = (int32_t)chunk_size(v.n_vis, bpc, capacity);
-  a.n_chunks = (v.n_vis + a.chunk - 1) / a.chunk;
-  const int64_t blocks = ((a.n_chunks + kXcd - 1) / kXcd) * kXcd * bpc;
-  auto kern = mixed ? kmixed : (big ? kf64big : kf64);
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * waves), 0, st, a, v.geo, v.quad, v.res, wt, a.acc.cell);
-  return hipGetLastError();
+  return mixed ? run_tiles<true, kNsMixed, kGroupMixed>(a, st) : run_tiles<false, kNsF64, kGroupF64>(a, st);
 }
 
 }  // namespace rlf

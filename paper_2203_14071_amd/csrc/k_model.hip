@@ -34,7 +34,7 @@ template <bool kMixed>
 __global__ __launch_bounds__(model_threads<kMixed>()) void k_model(ModelArgs a) {
   __shared__ double2 tab[kMixed ? 1 : kModelTable];
   if (!kMixed) {
-    cis_table_init<kModelTable>(tab);
+    cis_table_load<kModelTable>(tab, a.cis);
     __syncthreads();
   }
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -89,7 +89,7 @@ template <bool kMixed>
 __global__ __launch_bounds__(model_threads<kMixed>(), kMixed ? 1 : 8) void k_residual_sorted(ResidualArgs a) {
   __shared__ double2 tab[kMixed ? 1 : kModelTable];
   if (!kMixed && a.subtract) {
-    cis_table_init<kModelTable>(tab);
+    cis_table_load<kModelTable>(tab, a.cis);
     __syncthreads();
   }
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -133,7 +133,7 @@ template <bool kMixed>
 __global__ __launch_bounds__(256) void k_update_sorted(UpdateArgs a) {
   __shared__ double2 tab[kMixed ? 1 : kCisTable];
   if (!kMixed) {
-    cis_table_init(tab);
+    cis_table_load<kCisTable>(tab, a.cis);
     __syncthreads();
   }
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

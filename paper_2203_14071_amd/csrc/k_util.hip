@@ -1,6 +1,7 @@
 // Small utility kernels: max |x| over an array (facet sizing) and fills.
 // Fills are kernels rather than hipMemsetAsync so that a captured graph
 // holds only kernel nodes.
+#include "rlf_devmath.h"
 #include "rlf_internal.h"
 
 namespace rlf {
@@ -26,6 +27,8 @@ __global__ __launch_bounds__(256) void k_absmax(const double *x, int64_t n, doub
 __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
+
+__global__ __launch_bounds__(256) void k_fill_cis(double2 *master) { cis_table_init<kCisMaster>(master); }
 
 // dst[idx[i]] = src[i] (| bits for the 32-bit form), i < n; idx in range by
 // construction of the caller.
@@ -62,6 +65,11 @@ hipError_t launch_scatter_u32(const uint32_t *src, const int32_t *idx, int64_t n
                               hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_scatter_u32, dim3(grid_for(n)), dim3(256), 0, st, src, idx, n, bits, dst);
+  return hipGetLastError();
+}
+
+hipError_t launch_fill_cis(double2 *master, hipStream_t st) {
+  hipLaunchKernelGGL(k_fill_cis, dim3(1), dim3(256), 0, st, master);
   return hipGetLastError();
 }
 

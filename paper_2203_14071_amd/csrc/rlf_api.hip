@@ -13,6 +13,7 @@
 #include <mutex>
 #include <vector>
 
+#include "rlf_devmath.h"
 #include "rlf_objects.h"
 
 using namespace rlf;
@@ -23,7 +24,7 @@ constexpr double kArcsec = M_PI / 648000.0;     // radians per arcsecond
 constexpr double kC = 299792458.0;              // m/s
 constexpr int kVersion = 100;                   // 0.1.0
 constexpr int kMaxFacetHalf = 16383;            // side*side stays below 2^31
-constexpr int kSortedPad = 64;                  // zero-weight tail of the sorted arrays
+constexpr int kSortedPad = 256;                 // zero-weight tail of the sorted arrays (loads run ahead)
 constexpr int kMaxRefineLevel = 12;             // finest refinement step e_step / 4096
 // Bound on the mixed form's ln L error, delta = kRecheckRel (|ln Lmax| +
 // kRecheckAbs), used to pick the points its estimator re-evaluates in FP64.
@@ -514,6 +515,11 @@ int rlf_create(rlf_ctx **out, int device, void *hip_stream, const rlf_params *p)
     }
     if ((rc = dalloc(c, &c->d_err, 1))) break;
     if ((rc = dalloc(c, &c->d_absmax, 2))) break;
+    if ((rc = dalloc(c, &c->d_cis, kCisMaster))) break;
+    if (launch_fill_cis(c->d_cis, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+      rc = RLF_EDEVICE;
+      break;
+    }
     if (hipMemset(c->d_err, 0, sizeof(uint32_t)) != hipSuccess) {
       rc = RLF_EDEVICE;
       break;
@@ -547,6 +553,7 @@ int rlf_destroy(rlf_ctx *c) {
   dfree(c->d_chan);
   dfree(c->d_err);
   dfree(c->d_absmax);
+  dfree(c->d_cis);
   dfree(c->d_part);
   if (c->pinned) (void)hipHostFree(c->pinned);
   c->pinned = nullptr;
@@ -613,6 +620,7 @@ int rlf_model_vis(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, int64_
   a.s_end = (int32_t)src_end;
   a.vis_in = obs->vis;
   a.out = out;
+  a.cis = c->d_cis;
   hipError_t e = launch_model(a, c->p.precision == RLF_MIXED, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "model kernel launch");
   return RLF_OK;
@@ -674,6 +682,7 @@ int rlf_model_vis_noalloc(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat
   a.s_end = (int32_t)n;
   a.vis_in = obs->vis;
   a.out = out;
+  a.cis = c->d_cis;
   hipError_t e = launch_model(a, c->p.precision == RLF_MIXED, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "model kernel launch");
   return RLF_OK;
@@ -956,6 +965,7 @@ int extract_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const
     ra.vis = vis;
     ra.weight = obs->weight;
     ra.subtract = subtract;
+    ra.cis = c->d_cis;
     e = launch_residual_sorted(ra, f->mixed, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "residual kernel launch");
   }
@@ -963,8 +973,7 @@ int extract_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const
   a.sv = f->sv;
   a.n_chan = obs->n_chan;
   a.n_src = (int32_t)f->n_src;
-  a.n_tiles = (int32_t)((f->n_src + 63) / 64);
-  // chunk and n_chunks: chosen by the launcher from the device's occupancy
+  // n_tiles, chunk and n_chunks: chosen by the launcher from the device's occupancy
   a.chan = c->d_chan;
   a.src = f->d_src;
   a.src32 = f->d_src32;
@@ -972,6 +981,7 @@ int extract_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const
   a.order = f->d_order;
   a.acc = f->acc;
   a.err = c->d_err;
+  a.cis = c->d_cis;
   e = launch_extract(a, f->mixed, c->stream, upd);
   if (e != hipSuccess) return hip_fail(c, e, "extract kernel launch");
   CompactArgs ca{};
@@ -1008,6 +1018,7 @@ int sorted_residual(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *sky, cons
   ra.vis = obs->vis;
   ra.weight = obs->weight;
   ra.subtract = 1;
+  ra.cis = c->d_cis;
   ra.rs = f->mixed ? nullptr : rs;
   hipError_t e = launch_residual_sorted(ra, f->mixed, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "residual kernel launch");
@@ -1034,6 +1045,7 @@ int prepare_update(rlf_ctx *c, const rlf_catalog *old_m, const rlf_catalog *new_
   u.n_old = (int32_t)old_m->n_src;
   u.n_new = (int32_t)new_m->n_src;
   u.rs = f->mixed ? nullptr : rs;
+  u.cis = c->d_cis;
   return RLF_OK;
 }
 

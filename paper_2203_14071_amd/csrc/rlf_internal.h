@@ -86,6 +86,7 @@ struct ModelArgs {
   int32_t s_begin, s_end;
   const void *vis_in;        // RESIDUAL mode only
   void *out;
+  const double2 *cis;        // exp table in memory (kCisMaster entries)
 };
 
 // Per-visibility arrays of a facet object in uv-sorted order (sorted once at
@@ -115,7 +116,7 @@ struct ExtractArgs {
   int32_t n_chan;
   int32_t n_src;
   int32_t n_tiles;           // ceil(n_src / 64)
-  int32_t chunk;             // sorted visibilities per wave (set by launch_extract)
+  int32_t chunk;             // sorted visibilities (k_extract_vp: steps of 64) per wave (set by launch_extract)
   int64_t n_chunks;
   const ChanTable *chan;
   const SrcModel *src;
@@ -124,6 +125,7 @@ struct ExtractArgs {
   const int32_t *order;      // [n_src] source of each lane slot: sources by increasing theta
   DenseAcc acc;
   uint32_t *err;             // bit 0: a cell index fell outside its facet (visibility skipped)
+  const double2 *cis;        // exp table in memory (kCisMaster entries)
 };
 
 // Residual in sorted order: res[j] = vis[order[j]] - sum over sources of Eq. 1
@@ -139,6 +141,7 @@ struct ResidualArgs {
   const void *weight;        // caller order
   int32_t subtract;          // 1: vis - sky; 0: gather only
   double2 *rs;               // optional, FP64 form: the unweighted residual R in sorted order
+  const double2 *cis;        // exp table in memory (kCisMaster entries)
 };
 
 // In-place update of a residual kept in sorted order when some sources'
@@ -152,6 +155,7 @@ struct UpdateArgs {
   const SrcModel *old64, *new64;
   const SrcMixed *old32, *new32;
   double2 *rs;
+  const double2 *cis;        // exp table in memory (kCisMaster entries)
 };
 
 struct CompactArgs {
@@ -346,6 +350,7 @@ hipError_t launch_refine_estimate(const RefineArgs &r, hipStream_t st);
 hipError_t launch_scatter_f64(const double *src, const int32_t *idx, int64_t n, double *dst, hipStream_t st);
 hipError_t launch_scatter_u32(const uint32_t *src, const int32_t *idx, int64_t n, uint32_t bits, uint32_t *dst,
                               hipStream_t st);
+hipError_t launch_fill_cis(double2 *master, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &g, int split_k, hipStream_t st);
 hipError_t launch_bias_act(const float *c, const float *b, int64_t rows, int cols, float *z, __bf16 *h, int act,
