@@ -19,7 +19,11 @@ namespace rlf {
 
 namespace {
 
-constexpr int kThreads = 256;
+// Threads per block (one block per source): a pass over the 6,333 grid values
+// is a few loads per thread; the mixed form's recheck needs twice the
+// registers.
+template <bool kRecheck>
+constexpr int est_threads() { return kRecheck ? 512 : 1024; }
 constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
 
 // ln L(e) of source s at (e1, e2) in FP64, evaluated by one whole wave (all
@@ -76,13 +80,16 @@ __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, doub
   return mx + log(acc);
 }
 
+template <int kWavesEst>
 __device__ __forceinline__ double block_sum(double x, double *sh) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
   if (lane == 0) sh[wid] = x;
   __syncthreads();
-  const double t = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  double t = 0.0;
+#pragma unroll
+  for (int w = 0; w < kWavesEst; ++w) t += sh[w];
   __syncthreads();
   return t;
 }
@@ -99,10 +106,12 @@ __device__ __forceinline__ bool in_box(const int32_t *win, int s, int i1, int i2
   return i1 >= b.x && i1 <= b.y && i2 >= b.z && i2 <= b.w;
 }
 
-__global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
-  __shared__ double shd[4];
-  __shared__ double shv[4];
-  __shared__ int shi[4];
+template <bool kRecheck>
+__global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateArgs a) {
+  constexpr int kThreads = est_threads<kRecheck>(), kWavesEst = kThreads / 64;
+  __shared__ double shd[kWavesEst];
+  __shared__ double shv[kWavesEst];
+  __shared__ int shi[kWavesEst];
   __shared__ int touch;
   const int s = blockIdx.x;
   if (a.redo && !a.redo[s]) return;
@@ -148,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
     __syncthreads();
     best = shv[0];
     bi = shi[0];
-    for (int q = 1; q < 4; ++q)
+    for (int q = 1; q < kWavesEst; ++q)
       if (shv[q] > best || (shv[q] == best && shi[q] < bi)) {
         best = shv[q];
         bi = shi[q];
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
   // FP64 recheck (mixed form): the points that can decide the maximum or sit
   // at the threshold, each evaluated by a whole wave; the waves own disjoint
   // points, and every read of a point's FP32-summed value precedes its write
-  if (a.fit64 && best > -INFINITY) {
+  if (kRecheck && best > -INFINITY) {
     const double delta = a.recheck_rel * (fabs(best) + a.recheck_abs);
     const double lo = best - 2.0 * delta, thr0 = best + a.log_frac;
     const bool lat_out = a.redo_out && a.check_stride > 0;
@@ -257,10 +266,10 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
       cnt += 1.0;
     }
   }
-  sw = block_sum(sw, shd);
-  s1 = block_sum(s1, shd);
-  s2 = block_sum(s2, shd);
-  cnt = block_sum(cnt, shd);
+  sw = block_sum<kWavesEst>(sw, shd);
+  s1 = block_sum<kWavesEst>(s1, shd);
+  s2 = block_sum<kWavesEst>(s2, shd);
+  cnt = block_sum<kWavesEst>(cnt, shd);
   const double m1 = s1 / sw, m2 = s2 / sw;
 
   // pass 3: central second moments
@@ -278,9 +287,9 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
       c12 += w * d1 * d2;
     }
   }
-  c11 = block_sum(c11, shd) / sw;
-  c22 = block_sum(c22, shd) / sw;
-  c12 = block_sum(c12, shd) / sw;
+  c11 = block_sum<kWavesEst>(c11, shd) / sw;
+  c22 = block_sum<kWavesEst>(c22, shd) / sw;
+  c12 = block_sum<kWavesEst>(c12, shd) / sw;
 
   if (threadIdx.x == 0) {
     const double sd1 = sqrt(c11), sd2 = sqrt(c22);
@@ -317,7 +326,10 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
 }  // namespace
 
 hipError_t launch_estimate(const EstimateArgs &a, hipStream_t st) {
-  hipLaunchKernelGGL(k_estimate, dim3(a.n_src), dim3(kThreads), 0, st, a);
+  if (a.fit64)
+    hipLaunchKernelGGL(k_estimate<true>, dim3(a.n_src), dim3(est_threads<true>()), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_estimate<false>, dim3(a.n_src), dim3(est_threads<false>()), 0, st, a);
   return hipGetLastError();
 }
 

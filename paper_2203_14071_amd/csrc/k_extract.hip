@@ -26,11 +26,11 @@
 // FP sums are atomic and order-dependent in their last bits.  Runs are summed
 // in FP64 in both forms (the mixed form's FP32 terms are widened per term).
 #include <algorithm>
-#include <map>
-#include <mutex>
 
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
+#include "rlf_lanes.h"
+#include "rlf_launch.h"
 #include "rlf_sky.h"
 
 namespace rlf {
@@ -342,18 +342,6 @@ __device__ __forceinline__ double from_lane(double x, int l) {   // l wave-unifo
                           __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
-// Sum the values the wave's two halves (kHalf) or the rows of 16 lanes in
-// each half hold, for two quantities at once: the lower half (even rows) of
-// the result sums a, the upper half (odd rows) b.
-template <bool kHalf>
-__device__ __forceinline__ double fold_lanes(double a, double b) {
-  const auto lo = kHalf ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
-                        : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-  const auto hi = kHalf ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
-                        : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-
 // x + x of the lane kRor below in the row of 16 (cyclic), by DPP (a VALU
 // operand modifier: no LDS round trip).
 template <int kRor>
@@ -588,28 +576,6 @@ __global__ __launch_bounds__(kVpThreads) void k_extract_vp(ExtractArgs a, const 
     A[i].close(acc, base[i], lane);
     B[i].close(acc, base[i], lane);
   }
-}
-
-// Resident blocks of a kernel on the current device (kept per kernel and
-// device; the value is a property of both, so a race writes it twice).
-template <class K>
-int64_t resident_blocks(K kernel, int threads) {
-  static std::mutex mu;
-  static std::map<std::pair<const void *, int>, int64_t> cache;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  std::lock_guard<std::mutex> lock(mu);
-  int64_t &n = cache[{reinterpret_cast<const void *>(kernel), dev}];
-  if (!n) {
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-      (void)hipGetLastError();
-      return 0;
-    }
-    n = (int64_t)per_cu * cus;
-  }
-  return n;
 }
 
 // Visibilities per wave of k_extract, sized so that the waves are a whole

@@ -34,9 +34,13 @@
 // term h is sqrt(W_c) f_c), so a (cell, point, knot) costs the profile (6
 // ops), M (1) and one FMA per offset, plus the quadratic form once per knot
 // block.
+#include <algorithm>
+
 #include "rlf_cellsums.h"
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
+#include "rlf_lanes.h"
+#include "rlf_launch.h"
 
 namespace rlf {
 
@@ -277,74 +281,139 @@ __global__ __launch_bounds__(256) void k_fit(FitArgs a, int num_r) {
   eval_point<R, kExact, kMixed, NP>(a, num_r, s, j);
 }
 
-// Few sources (FP64 form, position fixed, R knots in one pass): the grid of
-// one source is only ~100 waves, each walking all of the source's cells, so
-// the cells are cut into a.parts ranges (blockIdx.z), each thread writes its
-// range's D_k and M_k, and k_fit_join adds the ranges in order and forms
-// ln L(e) as loglike_e does.
-template <int R>
-__global__ __launch_bounds__(256) void k_fit_part(FitArgs a) {
-  const int s = blockIdx.y, part = blockIdx.z;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= a.n_valid) return;
-  if (a.redo && !a.redo[s]) return;
-  const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
-  const int64_t len = (c1 - c0 + a.parts - 1) / a.parts;
-  const int64_t cb = min(c1, c0 + part * len), ce = min(c1, cb + len);
-  const int idx = a.epts[j];
-  const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
-  const int ctr = (a.n_e - 1) / 2;
-  const double e1 = (double)(i1 - ctr) * a.e_step, e2 = (double)(i2 - ctr) * a.e_step;
-  const double det = 1.0 - e1 * e1 - e2 * e2;
-  const double g = 1.0 / (det * det);
-  double D[R], M[R], sk[R];
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    D[k] = M[k] = 0.0;
-    sk[k] = a.sk[k] * g;
-  }
-  cell_sums_f64<R>(a.fit64, cb, ce, 1.0 + e1, e2, 1.0 - e1, sk, R, D, M);
-  double *out = a.part_sums + ((int64_t)s * a.parts + part) * (2 * R) * a.n_valid + j;
-#pragma unroll
-  for (int k = 0; k < R; ++k) {
-    out[(int64_t)k * a.n_valid] = D[k];
-    out[(int64_t)(R + k) * a.n_valid] = M[k];
-  }
-}
+// Split likelihood grid (FP64 form, position fixed, R knots in one pass), for
+// launches of few sources: the full grid of a small catalogue, and the full
+// refit of the sources a narrowed fit was not trusted for.  k_fit's waves walk
+// all cells of a source for 64 points: one source is ~100 waves, and a launch
+// of a few sources ends with its largest facet's walk.  Here a block of four
+// waves takes 32 points of a source, the halves of its waves each every
+// eighth cell (so the cell records are two vector loads per wave, a few cycles
+// against ~800 of arithmetic), and the partial sums are added in the block:
+// the two halves of a wave by lane swaps (D and M of a knot in one exchange),
+// the waves through LDS in order; then a thread per (knot, point) forms
+// ln(w_k L) and two lanes per point their log-sum-exp.  The items
+// (source, points) are taken in a fixed stride by a grid of resident blocks,
+// largest facets first; with a.redo, only the flagged sources are counted.
+// Catalogues of at most kSplitSources take it: grid and estimate, k_fit /
+// split, 197-antenna array: 1 source 62 / 32 us, 10 sources 126 / 94, 24
+// sources 203 / 195, 32 sources 248 / 238 (20-antenna array 194 / 205), 64
+// sources 346 / 417 (the sums in the block cost it a quarter more per source).
+constexpr int kSplitPoints = 32;
+constexpr int kSplitThreads = 256;
+constexpr int kSplitSources = 24;
 
 template <int R>
-__global__ __launch_bounds__(256) void k_fit_join(FitArgs a) {
-  const int s = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= a.n_valid) return;
-  if (a.redo && !a.redo[s]) return;
-  double *dst = a.lsurf + (int64_t)s * a.n_valid + j;
-  if (a.offsets[s + 1] == a.offsets[s]) {
-    *dst = NAN;
-    return;
-  }
-  double D[R], M[R];
-#pragma unroll
-  for (int k = 0; k < R; ++k) D[k] = M[k] = 0.0;
-  for (int part = 0; part < a.parts; ++part) {
-    const double *in = a.part_sums + ((int64_t)s * a.parts + part) * (2 * R) * a.n_valid + j;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      D[k] += in[(int64_t)k * a.n_valid];
-      M[k] += in[(int64_t)(R + k) * a.n_valid];
+__global__ __launch_bounds__(kSplitThreads, 3) void k_fit_split(FitArgs a) {
+  static_assert(kSplitPoints == 32 && R % 2 == 0, "two halves of a wave");
+  __shared__ double sums[4 * R * 64];
+  __shared__ double ll[R * kSplitPoints];
+  __shared__ int wcount[4];
+  __shared__ int found;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int p = lane & 31, half = lane >> 5;
+  const int nb = (a.n_valid + kSplitPoints - 1) / kSplitPoints;
+  const int ctr = (a.n_e - 1) / 2;
+  auto source = [&](int i) { return a.size_order ? a.size_order[a.n_src - 1 - i] : i; };
+  int rank = -1, s = -1;                       // the flagged source in hand
+  int scanned = 0, seen = 0;                   // flags of the first `scanned` sources hold `seen` ones
+  for (int64_t item = blockIdx.x;; item += gridDim.x) {
+    const int64_t want64 = item / nb;
+    if (want64 >= a.n_src) return;             // uniform
+    const int want = (int)want64;
+    if (want != rank) {
+      rank = want;
+      if (!a.redo) {
+        s = source(want);
+      } else {
+        // the flagged source number `want`: flags 256 at a time
+        for (;;) {
+          if (scanned >= a.n_src) return;      // uniform: no more flagged sources
+          const int i = scanned + threadIdx.x;
+          const int mine = i < a.n_src ? source(i) : 0;
+          const bool f = i < a.n_src && a.redo[mine] != 0;
+          const uint64_t m = __ballot(f);
+          if (lane == 0) wcount[wid] = __popcll(m);
+          __syncthreads();
+          int before = seen + __popcll(m & ((1ull << lane) - 1ull)), total = 0;
+          for (int w = 0; w < 4; ++w) {
+            before += w < wid ? wcount[w] : 0;
+            total += wcount[w];
+          }
+          if (f && before == want) found = mine;
+          __syncthreads();
+          if (want < seen + total) break;
+          seen += total;
+          scanned += kSplitThreads;
+        }
+        s = found;
+        __syncthreads();
+      }
     }
-  }
-  const double *lw = a.logw + (int64_t)s * a.num_r;
-  double bm = -INFINITY;
+    const int j0 = (int)(item - (int64_t)rank * nb) * kSplitPoints;
+    const int j = j0 + p;
+    const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
+    double *dst = a.lsurf + (int64_t)s * a.n_valid;
+    if (c0 == c1) {                            // uniform
+      if (threadIdx.x < kSplitPoints && j < a.n_valid) dst[j] = NAN;
+      continue;
+    }
+    const int idx = a.epts[min(j, a.n_valid - 1)];
+    const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
+    const double e1 = (double)(i1 - ctr) * a.e_step, e2 = (double)(i2 - ctr) * a.e_step;
+    const double id = 1.0 / (1.0 - e1 * e1 - e2 * e2);
+    const double a11 = (1.0 + e1) * id, a12 = e2 * id, a22 = (1.0 - e1) * id;
+    const double4 *__restrict__ cells = a.fit64;
+    {
+      double X[2 * R];                         // D_k, M_k of knot k in X[2 k], X[2 k + 1]
 #pragma unroll
-  for (int k = 0; k < R; ++k) {
-    D[k] = lw[k] + (D[k] * D[k] / (2.0 * M[k]) - 0.5 * log(M[k]) - kLnPowM32Scale);
-    bm = fmax(bm, D[k]);
-  }
-  double bs = 0.0;
+      for (int k = 0; k < 2 * R; ++k) X[k] = 0.0;
+      for (int64_t c = c0 + wid * 2 + half; c < c1; c += 8) {
+        const double4 cl = cells[c];
+        const double ku = fma(a11, cl.x, a12 * cl.y);
+        const double kv = fma(a12, cl.x, a22 * cl.y);
+        const double q = fma(ku, ku, kv * kv);
 #pragma unroll
-  for (int k = 0; k < R; ++k) bs += exp(D[k] - bm);
-  *dst = bm + log(bs);
+        for (int k = 0; k < R; ++k) {
+          const double h = pow_m32_f64(fma(a.sk[k], q, cl.z));          // (2/3) sqrt(W) f_c
+          X[2 * k] = fma(cl.w, h, X[2 * k]);
+          X[2 * k + 1] = fma(h, h, X[2 * k + 1]);
+        }
+      }
+      // the lower half ends up with D_k, the upper with M_k over the wave's cells
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+        sums[(wid * R + k) * 64 + lane] = fold_lanes<true>(X[2 * k], X[2 * k + 1]);
+    }
+    __syncthreads();
+    const double *lw = a.logw + (int64_t)s * a.num_r;
+    for (int t = threadIdx.x; t < R * kSplitPoints; t += kSplitThreads) {
+      double D = 0.0, M = 0.0;
+      const int k = t / kSplitPoints, o = k * 64 + t % kSplitPoints;
+      for (int w = 0; w < 4; ++w) {
+        D += sums[w * R * 64 + o];
+        M += sums[w * R * 64 + o + 32];
+      }
+      ll[t] = lw[k] + (D * D / (2.0 * M) - 0.5 * log(M) - kLnPowM32Scale);
+    }
+    __syncthreads();
+    if (wid == 0) {
+      double v[R / 2], m = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < R / 2; ++k) {
+        v[k] = ll[(half * (R / 2) + k) * kSplitPoints + p];
+        m = fmax(m, v[k]);
+      }
+      m = fmax(m, __shfl_xor(m, 32));
+      double e = 0.0;
+#pragma unroll 2
+      for (int k = 0; k < R / 2; ++k) e += exp(v[k] - m);
+      e += __shfl_xor(e, 32);
+      if (half == 0 && j < a.n_valid) dst[j] = m + log(e);
+    }
+    // (the next item's writes to sums and ll come after its first barrier
+    // and every read of them here before that: sums are read before the
+    // second barrier above, ll by wave 0 alone before it reaches the next)
+  }
 }
 
 // Windowed launch: blockIdx.y = source, one thread per position of the
@@ -514,10 +583,11 @@ hipError_t launch(const FitArgs &a, hipStream_t st) {
     const int lattice = (a.check_stride > 0 && a.lattice_pass != 2) ? (2 * h + 1) * (2 * h + 1) : 0;
     const int positions = (a.lattice_pass == 1 ? 0 : a.n_e * a.n_e) + lattice;
     RLF_FIT_DISPATCH(k_fit_window, dim3((positions + 255) / 256, a.n_src), a);
-  } else if (!kMixed && a.parts > 1 && a.num_r == 20) {
-    const unsigned bx = (unsigned)((a.n_valid + 255) / 256);
-    hipLaunchKernelGGL(k_fit_part<20>, dim3(bx, a.n_src, a.parts), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_fit_join<20>, dim3(bx, a.n_src), dim3(256), 0, st, a);
+  } else if (!kMixed && a.num_r == 20 && (a.redo || a.n_src <= kSplitSources)) {
+    auto kern = k_fit_split<20>;
+    const int64_t items = (int64_t)a.n_src * ((a.n_valid + kSplitPoints - 1) / kSplitPoints);
+    const int64_t blocks = std::min(items, resident_blocks(kern, kSplitThreads));
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, blocks)), dim3(kSplitThreads), 0, st, a);
   } else {
     RLF_FIT_DISPATCH(k_fit, dim3((a.n_valid + 255) / 256, a.n_src), a);
   }

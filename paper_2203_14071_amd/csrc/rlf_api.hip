@@ -204,12 +204,17 @@ static_assert(kNoAllocSrcOff % 256 == 0 && kNoAllocSrc32Off % 256 == 0, "table o
 
 __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
+// exp(2 pi i k / kCisMaster), the source of the kernels' LDS tables: constants,
+// filled once per device by the first context on it.
+__device__ double2 cis_table[kCisMaster];
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
+double2 *g_cis_ptr[kMaxDevices] = {};
 
-// The device address of `scratch` on the current device `device`, resolved
-// on the first call for that device.
+// The device addresses of `scratch` and `cis_table` on the current device
+// `device`, resolved (and the table filled) on the first call for that device.
 int resolve_scratch(rlf_ctx *c, int device) {
   if (device < 0 || device >= kMaxDevices) return fail(c, RLF_EUNSUPPORTED, "device index above 63");
   std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -217,8 +222,20 @@ int resolve_scratch(rlf_ctx *c, int device) {
   void *ptr = nullptr;
   hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
   if (e != hipSuccess || !ptr) return hip_fail(c, e != hipSuccess ? e : hipErrorInvalidSymbol, "hipGetSymbolAddress(scratch)");
+  void *cis = nullptr;
+  e = hipGetSymbolAddress(&cis, HIP_SYMBOL(cis_table));
+  if (e != hipSuccess || !cis) return hip_fail(c, e != hipSuccess ? e : hipErrorInvalidSymbol, "hipGetSymbolAddress(cis_table)");
+  HIPCHK(c, launch_fill_cis(static_cast<double2 *>(cis), nullptr));
+  HIPCHK(c, hipStreamSynchronize(nullptr));
+  g_cis_ptr[device] = static_cast<double2 *>(cis);
   g_scratch_ptr[device] = ptr;
   return RLF_OK;
+}
+
+const double2 *cis_master(int device) {
+  if (device < 0 || device >= kMaxDevices) return nullptr;
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  return g_cis_ptr[device];
 }
 
 void *scratch_ptr(int device) {
@@ -515,11 +532,6 @@ int rlf_create(rlf_ctx **out, int device, void *hip_stream, const rlf_params *p)
     }
     if ((rc = dalloc(c, &c->d_err, 1))) break;
     if ((rc = dalloc(c, &c->d_absmax, 2))) break;
-    if ((rc = dalloc(c, &c->d_cis, kCisMaster))) break;
-    if (launch_fill_cis(c->d_cis, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
-      rc = RLF_EDEVICE;
-      break;
-    }
     if (hipMemset(c->d_err, 0, sizeof(uint32_t)) != hipSuccess) {
       rc = RLF_EDEVICE;
       break;
@@ -527,6 +539,7 @@ int rlf_create(rlf_ctx **out, int device, void *hip_stream, const rlf_params *p)
     // rlf_model_vis_noalloc: the device's scratch address and a host staging
     // buffer of the same size, made here so that the entry point allocates nothing
     if ((rc = resolve_scratch(c, device))) break;
+    c->d_cis = cis_master(device);
     try {
       c->noalloc_stage.resize(kNoAllocBytes);
     } catch (...) {
@@ -553,8 +566,6 @@ int rlf_destroy(rlf_ctx *c) {
   dfree(c->d_chan);
   dfree(c->d_err);
   dfree(c->d_absmax);
-  dfree(c->d_cis);
-  dfree(c->d_part);
   if (c->pinned) (void)hipHostFree(c->pinned);
   c->pinned = nullptr;
   for (auto &sl : c->slot) {
@@ -1271,27 +1282,6 @@ int fit_args(rlf_ctx *c, const rlf_facets *f, FitArgs &fa) {
     fa.n_pos = pa.n_pos;
     fa.pos_g64 = pa.g64;
     fa.pos_g32 = pa.g32;
-  }
-  // few sources: split each source's cells over several waves per grid point
-  // (a source alone is ~100 waves; split until ~2048 waves run), unless the
-  // stream is being captured (the partial-sum buffer may have to grow)
-  if (!f->mixed && f->pos_side <= 1 && c->p.num_r == 20) {
-    const int64_t waves = f->n_src * (int64_t)((c->n_valid + 63) / 64);
-    const int64_t parts = std::min<int64_t>(16, 2048 / std::max<int64_t>(1, waves));
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    HIPCHK(c, hipStreamIsCapturing(c->stream, &cs));
-    if (parts >= 2 && cs == hipStreamCaptureStatusNone) {
-      const int64_t need = f->n_src * parts * 2 * c->p.num_r * (int64_t)c->n_valid;
-      if (need > c->part_cap) {
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        dfree(c->d_part);
-        c->part_cap = 0;
-        if (int e = dalloc(c, &c->d_part, need)) return e;
-        c->part_cap = need;
-      }
-      fa.parts = (int32_t)parts;
-      fa.part_sums = c->d_part;
-    }
   }
   return RLF_OK;
 }

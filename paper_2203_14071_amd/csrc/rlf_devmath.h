@@ -40,8 +40,8 @@ __device__ __forceinline__ void cis_table_init(double2 *tab) {
   }
 }
 
-// The same values copied from a table of kCisMaster entries in memory (built
-// once per context by cis_table_init's rule): a launch of short blocks would
+// The same values copied from a table of kCisMaster entries in memory (filled
+// once per device by cis_table_init): a launch of short blocks would
 // otherwise spend as long on the table's sincospi as on its work.
 constexpr int kCisMaster = 2048;
 template <int T>

@@ -38,10 +38,7 @@ struct rlf_ctx {
   uint64_t tick = 0;
   uint32_t *d_err = nullptr;
   double *d_absmax = nullptr;
-  double2 *d_cis = nullptr;                  // exp(2 pi i k / kCisMaster), the kernels' LDS tables' source
-  // partial likelihood sums of split fits (few sources), grown on demand
-  double *d_part = nullptr;
-  int64_t part_cap = 0;
+  const double2 *d_cis = nullptr;            // the device's exp table, the kernels' LDS tables' source
   // pinned staging ring of the asynchronous table uploads
   char *pinned = nullptr;
   size_t pinned_off = 0;
