@@ -34,13 +34,9 @@
 // term h is sqrt(W_c) f_c), so a (cell, point, knot) costs the profile (6
 // ops), M (1) and one FMA per offset, plus the quadratic form once per knot
 // block.
-#include <algorithm>
-
 #include "rlf_cellsums.h"
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
-#include "rlf_lanes.h"
-#include "rlf_launch.h"
 
 namespace rlf {
 
@@ -48,6 +44,11 @@ namespace {
 
 constexpr int kBlock = kCellBlock;
 constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
+// Full grids of at most this many sources share their knots between waves
+// (k_fit_knots); grid and estimate in FP64, k_fit / k_fit_knots: 1 source 62 /
+// 38 us, 10 sources 126 / 92, 32 sources 246 / 212, 48 sources 288 / 283, 64
+// sources 347 / 359; in the mixed form 160 / 98 us and 230 / 183 us for 1 and 10.
+constexpr int kKnotSources = 48;
 
 // Knots per pass over the cells: the mixed form with 20 knots takes them in
 // two passes of 10 (the quadratic form is formed twice per cell, but half
@@ -56,77 +57,97 @@ constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
 template <int R, bool kMixed>
 constexpr int knots_per_pass() { return (kMixed && R == 20) ? 10 : R; }
 
+// A log-sum-exp in the making: ln of the terms so far = mx + ln(acc).
+struct Lse {
+  double mx = -INFINITY, acc = 0.0;
+  // Add the n terms exp(v[k]).
+  template <int N>
+  __device__ __forceinline__ void add(const double (&v)[N], int n) {
+    double bm = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (k < n) bm = fmax(bm, v[k]);
+    const double nm = fmax(mx, bm);
+    double bs = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (k < n) bs += exp(v[k] - nm);
+    acc = (mx > -INFINITY ? acc * exp(mx - nm) : 0.0) + bs;
+    mx = nm;
+  }
+};
+
+// The terms ln(w_k L(e, alpha_k)) of source s (not empty) at (e1, e2),
+// |e| < 1, for the n <= KP knots from k0 on: one pass over the source's
+// records.
+template <int KP, bool kMixed>
+__device__ __forceinline__ void knot_terms(const FitArgs &a, int s, double e1, double e2, int k0, int n,
+                                           double (&D)[KP]) {
+  const double det = 1.0 - e1 * e1 - e2 * e2;
+  const double g = 1.0 / (det * det);
+  const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
+  const double *lw = a.logw + (int64_t)s * a.num_r;
+  double M[KP];
+#pragma unroll
+  for (int k = 0; k < KP; ++k) D[k] = M[k] = 0.0;
+  if (!kMixed) {
+    // A^{-T} with its 1/det folded in, so that the knot scales s_k stay
+    // wave-uniform (SGPR operands: 40 VGPRs fewer than per-lane s_k g)
+    const double id = 1.0 / det;
+    const double a11 = (1.0 + e1) * id, a12 = e2 * id, a22 = (1.0 - e1) * id;
+    double sk[KP];
+#pragma unroll
+    for (int k = 0; k < KP; ++k) sk[k] = k < n ? a.sk[k0 + k] : 0.0;
+    cell_sums_f64<KP>(a.fit64, c0, c1, a11, a12, a22, sk, n, D, M);
+  } else {
+    const float a11 = (float)(1.0 + e1), a12 = (float)e2, a22 = (float)(1.0 - e1);
+    float sk[KP];
+#pragma unroll
+    for (int k = 0; k < KP; ++k) sk[k] = k < n ? (float)(a.sk[k0 + k] * g) : 0.0f;
+    cell_sums_f32<KP>(a.fit32, c0, c1, a11, a12, a22, sk, n, D, M);
+  }
+  // ln(w_k L(e, alpha_k)) in place of D; FP64 form: D and M carry (2/3)
+  // and (4/9) of their values, so the ratio term is unchanged and ln M is
+  // off by ln(4/9) = -2 ln(3/2)
+#pragma unroll
+  for (int k = 0; k < KP; ++k)
+    if (k < n) D[k] = lw[k0 + k] + (D[k] * D[k] / (2.0 * M[k]) - 0.5 * log(M[k]) - (kMixed ? 0.0 : kLnPowM32Scale));
+}
+
 // ln L(e) of source s at (e1, e2), |e| < 1; NaN for an empty facet.
 template <int R, bool kExact, bool kMixed>
 __device__ __forceinline__ double loglike_e(const FitArgs &a, int num_r_arg, int s, double e1, double e2) {
   constexpr int KP = knots_per_pass<R, kMixed>();
+  if (a.offsets[s + 1] == a.offsets[s]) return NAN;
   const int num_r = kExact ? R : num_r_arg;
-  const double det = 1.0 - e1 * e1 - e2 * e2;
-  const double g = 1.0 / (det * det);
-  const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
-  if (c1 == c0) return NAN;
-  const double *lw = a.logw + (int64_t)s * a.num_r;
-  double mx = -INFINITY, acc = 0.0;
+  Lse t;
 #pragma unroll 1
   for (int k0 = 0; k0 < R; k0 += KP) {
     if (k0 >= num_r) break;
-    double D[KP], M[KP];
-#pragma unroll
-    for (int k = 0; k < KP; ++k) D[k] = M[k] = 0.0;
-    if (!kMixed) {
-      // A^{-T} with its 1/det folded in, so that the knot scales s_k stay
-      // wave-uniform (SGPR operands: 40 VGPRs fewer than per-lane s_k g)
-      const double id = 1.0 / det;
-      const double a11 = (1.0 + e1) * id, a12 = e2 * id, a22 = (1.0 - e1) * id;
-      double sk[KP];
-#pragma unroll
-      for (int k = 0; k < KP; ++k) sk[k] = k0 + k < num_r ? a.sk[k0 + k] : 0.0;
-      cell_sums_f64<KP>(a.fit64, c0, c1, a11, a12, a22, sk, num_r - k0, D, M);
-    } else {
-      const float a11 = (float)(1.0 + e1), a12 = (float)e2, a22 = (float)(1.0 - e1);
-      float sk[KP];
-#pragma unroll
-      for (int k = 0; k < KP; ++k) sk[k] = k0 + k < num_r ? (float)(a.sk[k0 + k] * g) : 0.0f;
-      cell_sums_f32<KP>(a.fit32, c0, c1, a11, a12, a22, sk, num_r - k0, D, M);
-    }
-    // ln(w_k L(e, alpha_k)) in place of D; FP64 form: D and M carry (2/3)
-    // and (4/9) of their values, so the ratio term is unchanged and ln M is
-    // off by ln(4/9) = -2 ln(3/2)
-    double bm = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < KP; ++k) {
-      if (k0 + k < num_r) {
-        D[k] = lw[k0 + k] + (D[k] * D[k] / (2.0 * M[k]) - 0.5 * log(M[k]) - (kMixed ? 0.0 : kLnPowM32Scale));
-        bm = fmax(bm, D[k]);
-      }
-    }
-    const double nm = fmax(mx, bm);
-    double bs = 0.0;
-#pragma unroll
-    for (int k = 0; k < KP; ++k)
-      if (k0 + k < num_r) bs += exp(D[k] - nm);
-    acc = (mx > -INFINITY ? acc * exp(mx - nm) : 0.0) + bs;
-    mx = nm;
+    double v[KP];
+    knot_terms<KP, kMixed>(a, s, e1, e2, k0, num_r - k0, v);
+    t.add(v, num_r - k0);
   }
-  return mx + log(acc);
+  return t.mx + log(t.acc);
 }
 
 // Knots per block of the position-marginalised sum: KB * NP partial sums
 // in registers (FP64, plus as many FP32 ones in the mixed form).
 constexpr int pos_knot_block(int np) { return np <= 9 ? 4 : (np <= 25 ? 2 : 1); }
 
-// Position-marginalised ln L(e) of source s at (e1, e2), |e| < 1; NaN for an
-// empty facet.
+// The position-marginalised terms, sum over the offsets included, of the
+// blocks of KB = pos_knot_block(NP) knots from kfirst on in steps of kstep.
 template <int NP, bool kMixed>
-__device__ __forceinline__ double loglike_pos(const FitArgs &a, int num_r, int s, double e1, double e2) {
+__device__ __forceinline__ void add_knots_pos(const FitArgs &a, int num_r, int s, double e1, double e2, int kfirst,
+                                              int kstep, Lse &acc_out) {
   constexpr int KB = pos_knot_block(NP);
   const double det = 1.0 - e1 * e1 - e2 * e2;
   const double g = 1.0 / (det * det);
   const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
-  if (c1 == c0) return NAN;
   const double *lw = a.logw + (int64_t)s * a.num_r;
-  double mx = -INFINITY, acc = 0.0;
-  for (int k0 = 0; k0 < num_r; k0 += KB) {
+  double mx = acc_out.mx, acc = acc_out.acc;
+#pragma unroll 1
+  for (int k0 = kfirst; k0 < num_r; k0 += kstep) {
     double D[KB][NP], M[KB];
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
@@ -141,19 +162,65 @@ __device__ __forceinline__ double loglike_pos(const FitArgs &a, int num_r, int s
       for (int b = 0; b < KB; ++b) sk[b] = k0 + b < num_r ? a.sk[k0 + b] * g : 0.0;
       const double4 *__restrict__ cells = a.fit64;
       const double *__restrict__ G = a.pos_g64;
-      for (int64_t c = c0; c < c1; ++c) {
-        const double4 cl = cells[c];
+      // A cell's row of G arrives in chunks of at most 13 values through two
+      // buffers of scalar registers: once a chunk is there, the next one (of
+      // this cell or the next) is issued, and the chunk's FMAs cover its way.
+      // Scalar loads return in any order, so a wait is for all of them: left
+      // to itself the compiler waited for a whole row, or for every eight
+      // values, with nothing in flight behind them.
+      // (A row of 9 is one chunk, behind four knots' arithmetic.)
+      constexpr int kChunks = NP <= 13 ? 1 : (NP <= 26 ? 2 : 4), CH = (NP + kChunks - 1) / kChunks;
+      double buf[2][CH];
+      double4 nx;
+      auto load = [&](int64_t c, int ch, double(&b)[CH]) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+          if (ch * CH + i < NP) b[i] = G[c * NP + ch * CH + i];
+      };
+      auto cell = [&](int64_t c) {
+        const double4 cl = nx;
         const double ku = fma(a11, cl.x, a12 * cl.y);
         const double kv = fma(a12, cl.x, a22 * cl.y);
         const double q = fma(ku, ku, kv * kv);
-        const double *gc = G + c * NP;
+        double f[KB];
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
-          const double f = pow_m32_f64(fma(sk[b], q, cl.z));        // (2/3) sqrt(W) f_c
-          M[b] = fma(f, f, M[b]);
-#pragma unroll
-          for (int p = 0; p < NP; ++p) D[b][p] = fma(f, gc[p], D[b][p]);
+          f[b] = pow_m32_f64(fma(sk[b], q, cl.z));                  // (2/3) sqrt(W) f_c
+          M[b] = fma(f[b], f[b], M[b]);
         }
+#pragma unroll
+        for (int ch = 0; ch < kChunks; ++ch) {
+          double(&have)[CH] = buf[ch & 1];
+          double(&next)[CH] = buf[(ch + 1) & 1];
+#pragma unroll
+          for (int i = 0; i < CH; ++i)
+            if (kChunks > 1 && ch * CH + i < NP) asm("" : "+s"(have[i]));             // arrived
+          __builtin_amdgcn_sched_barrier(0);
+          if (ch + 1 < kChunks) {
+            load(c, ch + 1, next);
+          } else if (kChunks > 1) {
+            const int64_t cn = min(c + 1, c1 - 1);
+            nx = cells[cn];
+            load(cn, 0, next);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+              if (ch * CH + i < NP) D[b][ch * CH + i] = fma(f[b], have[i], D[b][ch * CH + i]);
+        }
+      };
+      if constexpr (kChunks > 1) {
+        nx = cells[c0];
+        load(c0, 0, buf[0]);
+      }
+      for (int64_t c = c0; c < c1; ++c) {
+        if constexpr (kChunks == 1) {
+          nx = cells[c];
+          load(c, 0, buf[0]);
+        }
+        cell(c);
       }
     } else {
       const float a11 = (float)(1.0 + e1), a12 = (float)e2, a22 = (float)(1.0 - e1);
@@ -223,197 +290,165 @@ __device__ __forceinline__ double loglike_pos(const FitArgs &a, int num_r, int s
     acc = (mx > -INFINITY ? acc * exp(mx - nm) : 0.0) + bs;
     mx = nm;
   }
-  return mx + log(acc / (double)NP);
-}
-
-// ln L(e): position fixed (NP = 0) or marginalised over NP offsets.
-template <int R, bool kExact, bool kMixed, int NP>
-__device__ __forceinline__ double loglike(const FitArgs &a, int num_r, int s, double e1, double e2) {
-  if constexpr (NP == 0)
-    return loglike_e<R, kExact, kMixed>(a, num_r, s, e1, e2);
-  else
-    return loglike_pos<NP, kMixed>(a, num_r, s, e1, e2);
+  acc_out.mx = mx;
+  acc_out.acc = acc;
 }
 
 // ln L(e) at valid grid point j (index into the valid-point list) of source s.
-template <int R, bool kExact, bool kMixed, int NP = 0>
+template <int R, bool kExact, bool kMixed>
 __device__ __forceinline__ void eval_point(const FitArgs &a, int num_r, int s, int j) {
   const int idx = a.epts[j];
   const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
   const int ctr = (a.n_e - 1) / 2;
   a.lsurf[(int64_t)s * a.n_valid + j] =
-      loglike<R, kExact, kMixed, NP>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step);
+      loglike_e<R, kExact, kMixed>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step);
 }
 
-// Refinement level: one thread per point of the source's window at
-// resolution e_step / 2^level, e = k * that step, |e| < 1 tested on the
-// integers; -inf outside the domain.
-template <int R, bool kExact, bool kMixed, int NP = 0>
-__global__ __launch_bounds__(256) void k_refine_eval(FitArgs a, RefineArgs r, int num_r) {
+// Knots shared by waves: all waves of a block work on the same 64 points of
+// one source, each on every fourth block of knots.  Position fixed, the terms
+// meet in LDS and are summed in loglike_e's order (ln L is the same to the
+// bit); marginalised, wave 0 joins the waves' log-sum-exps in their order.  A source's 6,333
+// points are ~100 such blocks, and a wave's walk over the cells is NW times
+// shorter than with all knots in one thread, so that a launch of few sources,
+// or its largest facet, does not leave the chip idle; the records' scalar
+// loads are shared.  It costs the quadratic form once per block of knots
+// (6 operations to 11 per knot), nothing for the position-marginalised sum,
+// whose knots come in blocks anyway.  Four waves: a fifth shares its SIMD with
+// another (5 x 5 offsets, 100 sources: 3.9 ms with five waves, 2.2 with four).
+// The refinement, whose windows of a few hundred points used to be one or two
+// blocks per source, gains most: 100 sources, three levels, 0.63 -> 0.41 ms
+// position-fixed, 3.0 -> 1.65 ms over 5 x 5 offsets, 4.3 -> 2.3 ms over 7 x 7.
+template <bool kMixed, int NP>
+struct KnotSplit {
+  static constexpr int kKnots = NP ? pos_knot_block(NP) : 5;
+  static constexpr int kWaves = 4;
+  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kWavesPerSimd = NP == 0 ? 5 : (kMixed ? 2 : 3);
+};
+
+// Doubles of LDS loglike_block needs.
+template <bool kMixed, int NP>
+constexpr int block_doubles() { return NP ? 2 * 64 * KnotSplit<kMixed, NP>::kWaves : kMaxKnots * 64; }
+
+// ln L(e) of source s (not empty) at one point per lane, the same points in
+// every wave of the block; the result is wave 0's.
+template <bool kMixed, int NP>
+__device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int s, double e1, double e2, double *sh) {
+  using S = KnotSplit<kMixed, NP>;
+  constexpr int KP = S::kKnots;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (NP != 0) {
+    Lse t;
+    add_knots_pos<NP, kMixed>(a, num_r, s, e1, e2, wid * KP, S::kWaves * KP, t);
+    sh[wid * 64 + lane] = t.mx;
+    sh[(S::kWaves + wid) * 64 + lane] = t.acc;
+    __syncthreads();
+    double nm = t.mx, acc = 0.0;
+#pragma unroll
+    for (int w = 0; w < S::kWaves; ++w) nm = fmax(nm, sh[w * 64 + lane]);
+#pragma unroll
+    for (int w = 0; w < S::kWaves; ++w) {
+      const double m = sh[w * 64 + lane];
+      acc += m > -INFINITY ? sh[(S::kWaves + w) * 64 + lane] * exp(m - nm) : 0.0;   // (a wave without knots)
+    }
+    return nm + log(acc / (double)NP);
+  } else {
+#pragma unroll 1
+    for (int k0 = wid * KP; k0 < num_r; k0 += S::kWaves * KP) {
+      double v[KP];
+      if (k0 + KP <= num_r)
+        knot_terms<KP, kMixed>(a, s, e1, e2, k0, KP, v);
+      else
+        knot_terms<KP, kMixed>(a, s, e1, e2, k0, num_r - k0, v);
+#pragma unroll
+      for (int k = 0; k < KP; ++k)
+        if (k0 + k < num_r) sh[(k0 + k) * 64 + lane] = v[k];
+    }
+    __syncthreads();
+    // loglike_e adds its terms pass by pass (the mixed form takes 20 knots in
+    // two): the maximum of the passes so far, then the pass's exponentials,
+    // here each by the wave that has the knot
+    const int per = kMixed && num_r == 20 ? 10 : num_r;
+    double mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll 4
+    for (int k = 0; k < num_r; ++k) mx[k >= per] = fmax(mx[k >= per], sh[k * 64 + lane]);
+    mx[1] = fmax(mx[0], mx[1]);
+    __syncthreads();
+#pragma unroll 1
+    for (int k0 = wid * KP; k0 < num_r; k0 += S::kWaves * KP)
+#pragma unroll
+      for (int k = 0; k < KP; ++k)
+        if (k0 + k < num_r) sh[(k0 + k) * 64 + lane] = exp(sh[(k0 + k) * 64 + lane] - (k0 + k < per ? mx[0] : mx[1]));
+    __syncthreads();
+    double L = 0.0;
+    if (wid == 0) {
+      double acc = 0.0, bs = 0.0;
+      for (int k = 0; k < per; ++k) acc += sh[k * 64 + lane];
+      if (per < num_r) {
+        for (int k = per; k < num_r; ++k) bs += sh[k * 64 + lane];
+        acc = acc * exp(mx[0] - mx[1]) + bs;
+      }
+      L = mx[1] + log(acc);
+    }
+    return L;
+  }
+}
+
+// Refinement level: the points of the source's window at resolution
+// e_step / 2^level, 64 per block, e = k * that step, |e| < 1 tested on the
+// integers; -inf outside the domain.  blockIdx.y = source, the grid sized for
+// the largest window (blocks past a source's window leave at once).
+template <bool kMixed, int NP>
+__global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixed, NP>::kWavesPerSimd)) void k_refine_eval(FitArgs a, RefineArgs r, int num_r) {
+  __shared__ double sh[block_doubles<kMixed, NP>()];
   const int s = blockIdx.y;
   const int32_t *w = r.win + (int64_t)s * 5;
-  if (!w[0]) return;
-  const int n1 = w[3], n2 = w[4];
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n1 * n2) return;
-  const int64_t k1 = w[1] + t / n2, k2 = w[2] + t % n2;
+  if (!w[0]) return;                           // (empty facets are never active)
+  const int n1 = w[3], n2 = w[4], np = n1 * n2;
   const int64_t lim = (int64_t)r.unit << r.level;
-  double *out = r.lloc + (int64_t)s * r.max_side * r.max_side + t;
-  if (k1 * k1 + k2 * k2 >= lim * lim) {
-    *out = -INFINITY;
-    return;
-  }
   const double res = a.e_step / (double)(1 << r.level);
-  *out = loglike<R, kExact, kMixed, NP>(a, num_r, s, (double)k1 * res, (double)k2 * res);
+  const int t = blockIdx.x * 64 + (int)(threadIdx.x & 63);
+  if ((int)blockIdx.x * 64 >= np) return;      // uniform
+  const int64_t k1 = w[1] + min(t, np - 1) / n2, k2 = w[2] + min(t, np - 1) % n2;
+  const bool in = k1 * k1 + k2 * k2 < lim * lim;
+  // a point outside the domain is evaluated at the centre and dropped
+  const double L = loglike_block<kMixed, NP>(a, num_r, s, in ? (double)k1 * res : 0.0, in ? (double)k2 * res : 0.0, sh);
+  if (threadIdx.x < 64 && t < np) r.lloc[(int64_t)s * r.max_side * r.max_side + t] = in ? L : -INFINITY;
 }
-
 
 // Grid launch: blockIdx.y = source (largest facets first when a.size_order
 // is set: blocks are dispatched in index order, and the long blocks of the
 // largest facets then do not trail the launch), one thread per valid grid
 // point.
-template <int R, bool kExact, bool kMixed, int NP = 0>
+template <int R, bool kExact, bool kMixed>
 __global__ __launch_bounds__(256) void k_fit(FitArgs a, int num_r) {
   const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= a.n_valid) return;
   if (a.redo && !a.redo[s]) return;
-  eval_point<R, kExact, kMixed, NP>(a, num_r, s, j);
+  eval_point<R, kExact, kMixed>(a, num_r, s, j);
 }
 
-// Split likelihood grid (FP64 form, position fixed, R knots in one pass), for
-// launches of few sources: the full grid of a small catalogue, and the full
-// refit of the sources a narrowed fit was not trusted for.  k_fit's waves walk
-// all cells of a source for 64 points: one source is ~100 waves, and a launch
-// of a few sources ends with its largest facet's walk.  Here a block of four
-// waves takes 32 points of a source, the halves of its waves each every
-// eighth cell (so the cell records are two vector loads per wave, a few cycles
-// against ~800 of arithmetic), and the partial sums are added in the block:
-// the two halves of a wave by lane swaps (D and M of a knot in one exchange),
-// the waves through LDS in order; then a thread per (knot, point) forms
-// ln(w_k L) and two lanes per point their log-sum-exp.  The items
-// (source, points) are taken in a fixed stride by a grid of resident blocks,
-// largest facets first; with a.redo, only the flagged sources are counted.
-// Catalogues of at most kSplitSources take it: grid and estimate, k_fit /
-// split, 197-antenna array: 1 source 62 / 32 us, 10 sources 126 / 94, 24
-// sources 203 / 195, 32 sources 248 / 238 (20-antenna array 194 / 205), 64
-// sources 346 / 417 (the sums in the block cost it a quarter more per source).
-constexpr int kSplitPoints = 32;
-constexpr int kSplitThreads = 256;
-constexpr int kSplitSources = 24;
-
-template <int R>
-__global__ __launch_bounds__(kSplitThreads, 3) void k_fit_split(FitArgs a) {
-  static_assert(kSplitPoints == 32 && R % 2 == 0, "two halves of a wave");
-  __shared__ double sums[4 * R * 64];
-  __shared__ double ll[R * kSplitPoints];
-  __shared__ int wcount[4];
-  __shared__ int found;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int p = lane & 31, half = lane >> 5;
-  const int nb = (a.n_valid + kSplitPoints - 1) / kSplitPoints;
+// The grid with the knots shared by waves, for launches of few sources: the
+// full grid of a small catalogue, the full refit of the sources a narrowed
+// fit was not trusted for (blocks of the others leave at once), and every
+// position-marginalised grid.  blockIdx.y = source, largest facets first; one
+// group of 64 points per block (in a loop over groups the stores of one would
+// keep the next one's record loads from being scalar).
+template <bool kMixed, int NP>
+__global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixed, NP>::kWavesPerSimd)) void k_fit_knots(
+    FitArgs a, int num_r) {
+  __shared__ double sh[block_doubles<kMixed, NP>()];
+  const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
+  if (a.redo && !a.redo[s]) return;            // uniform
+  const int j = blockIdx.x * 64 + (int)(threadIdx.x & 63);
+  const int idx = a.epts[min(j, a.n_valid - 1)];
+  const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
   const int ctr = (a.n_e - 1) / 2;
-  auto source = [&](int i) { return a.size_order ? a.size_order[a.n_src - 1 - i] : i; };
-  int rank = -1, s = -1;                       // the flagged source in hand
-  int scanned = 0, seen = 0;                   // flags of the first `scanned` sources hold `seen` ones
-  for (int64_t item = blockIdx.x;; item += gridDim.x) {
-    const int64_t want64 = item / nb;
-    if (want64 >= a.n_src) return;             // uniform
-    const int want = (int)want64;
-    if (want != rank) {
-      rank = want;
-      if (!a.redo) {
-        s = source(want);
-      } else {
-        // the flagged source number `want`: flags 256 at a time
-        for (;;) {
-          if (scanned >= a.n_src) return;      // uniform: no more flagged sources
-          const int i = scanned + threadIdx.x;
-          const int mine = i < a.n_src ? source(i) : 0;
-          const bool f = i < a.n_src && a.redo[mine] != 0;
-          const uint64_t m = __ballot(f);
-          if (lane == 0) wcount[wid] = __popcll(m);
-          __syncthreads();
-          int before = seen + __popcll(m & ((1ull << lane) - 1ull)), total = 0;
-          for (int w = 0; w < 4; ++w) {
-            before += w < wid ? wcount[w] : 0;
-            total += wcount[w];
-          }
-          if (f && before == want) found = mine;
-          __syncthreads();
-          if (want < seen + total) break;
-          seen += total;
-          scanned += kSplitThreads;
-        }
-        s = found;
-        __syncthreads();
-      }
-    }
-    const int j0 = (int)(item - (int64_t)rank * nb) * kSplitPoints;
-    const int j = j0 + p;
-    const int64_t c0 = a.offsets[s], c1 = a.offsets[s + 1];
-    double *dst = a.lsurf + (int64_t)s * a.n_valid;
-    if (c0 == c1) {                            // uniform
-      if (threadIdx.x < kSplitPoints && j < a.n_valid) dst[j] = NAN;
-      continue;
-    }
-    const int idx = a.epts[min(j, a.n_valid - 1)];
-    const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
-    const double e1 = (double)(i1 - ctr) * a.e_step, e2 = (double)(i2 - ctr) * a.e_step;
-    const double id = 1.0 / (1.0 - e1 * e1 - e2 * e2);
-    const double a11 = (1.0 + e1) * id, a12 = e2 * id, a22 = (1.0 - e1) * id;
-    const double4 *__restrict__ cells = a.fit64;
-    {
-      double X[2 * R];                         // D_k, M_k of knot k in X[2 k], X[2 k + 1]
-#pragma unroll
-      for (int k = 0; k < 2 * R; ++k) X[k] = 0.0;
-      for (int64_t c = c0 + wid * 2 + half; c < c1; c += 8) {
-        const double4 cl = cells[c];
-        const double ku = fma(a11, cl.x, a12 * cl.y);
-        const double kv = fma(a12, cl.x, a22 * cl.y);
-        const double q = fma(ku, ku, kv * kv);
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-          const double h = pow_m32_f64(fma(a.sk[k], q, cl.z));          // (2/3) sqrt(W) f_c
-          X[2 * k] = fma(cl.w, h, X[2 * k]);
-          X[2 * k + 1] = fma(h, h, X[2 * k + 1]);
-        }
-      }
-      // the lower half ends up with D_k, the upper with M_k over the wave's cells
-#pragma unroll
-      for (int k = 0; k < R; ++k)
-        sums[(wid * R + k) * 64 + lane] = fold_lanes<true>(X[2 * k], X[2 * k + 1]);
-    }
-    __syncthreads();
-    const double *lw = a.logw + (int64_t)s * a.num_r;
-    for (int t = threadIdx.x; t < R * kSplitPoints; t += kSplitThreads) {
-      double D = 0.0, M = 0.0;
-      const int k = t / kSplitPoints, o = k * 64 + t % kSplitPoints;
-      for (int w = 0; w < 4; ++w) {
-        D += sums[w * R * 64 + o];
-        M += sums[w * R * 64 + o + 32];
-      }
-      ll[t] = lw[k] + (D * D / (2.0 * M) - 0.5 * log(M) - kLnPowM32Scale);
-    }
-    __syncthreads();
-    if (wid == 0) {
-      double v[R / 2], m = -INFINITY;
-#pragma unroll
-      for (int k = 0; k < R / 2; ++k) {
-        v[k] = ll[(half * (R / 2) + k) * kSplitPoints + p];
-        m = fmax(m, v[k]);
-      }
-      m = fmax(m, __shfl_xor(m, 32));
-      double e = 0.0;
-#pragma unroll 2
-      for (int k = 0; k < R / 2; ++k) e += exp(v[k] - m);
-      e += __shfl_xor(e, 32);
-      if (half == 0 && j < a.n_valid) dst[j] = m + log(e);
-    }
-    // (the next item's writes to sums and ll come after its first barrier
-    // and every read of them here before that: sums are read before the
-    // second barrier above, ll by wave 0 alone before it reaches the next)
-  }
+  double L = NAN;
+  if (a.offsets[s + 1] != a.offsets[s])        // uniform
+    L = loglike_block<kMixed, NP>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step, sh);
+  if (threadIdx.x < 64 && j < a.n_valid) a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
 
 // Windowed launch: blockIdx.y = source, one thread per position of the
@@ -559,35 +594,29 @@ __global__ void k_reset_counter(uint32_t *c) {
                          a.num_r);                                                                  \
   } while (0)
 
-// Position-marginalised launches: the offset count selects the kernel (the
-// knot count is a run-time bound there).
-#define RLF_POS_DISPATCH(KERNEL, GRID, ...)                                                             \
-  do {                                                                                                  \
-    if (a.n_pos == 9)                                                                                   \
-      hipLaunchKernelGGL((KERNEL<1, false, kMixed, 9>), GRID, dim3(256), 0, st, __VA_ARGS__, a.num_r);  \
-    else if (a.n_pos == 25)                                                                             \
-      hipLaunchKernelGGL((KERNEL<1, false, kMixed, 25>), GRID, dim3(256), 0, st, __VA_ARGS__, a.num_r); \
-    else if (a.n_pos == 49)                                                                             \
-      hipLaunchKernelGGL((KERNEL<1, false, kMixed, 49>), GRID, dim3(256), 0, st, __VA_ARGS__, a.num_r); \
-    else                                                                                                \
-      return hipErrorInvalidValue;                                                                      \
-  } while (0)
+template <bool kMixed, int NP>
+hipError_t launch_knots(const FitArgs &a, hipStream_t st) {
+  constexpr int threads = KnotSplit<kMixed, NP>::kThreads;
+  hipLaunchKernelGGL((k_fit_knots<kMixed, NP>), dim3((a.n_valid + 63) / 64, a.n_src), dim3(threads), 0, st, a, a.num_r);
+  return hipGetLastError();
+}
 
 template <bool kMixed>
 hipError_t launch(const FitArgs &a, hipStream_t st) {
   if (a.n_pos) {
     if (a.window || a.lattice_pass) return hipErrorInvalidValue;   // full grid only
-    RLF_POS_DISPATCH(k_fit, dim3((a.n_valid + 255) / 256, a.n_src), a);
-  } else if (a.window || a.lattice_pass == 1) {
+    if (a.n_pos == 9) return launch_knots<kMixed, 9>(a, st);
+    if (a.n_pos == 25) return launch_knots<kMixed, 25>(a, st);
+    if (a.n_pos == 49) return launch_knots<kMixed, 49>(a, st);
+    return hipErrorInvalidValue;
+  }
+  if (a.window || a.lattice_pass == 1) {
     const int h = a.check_stride > 0 ? ((a.n_e - 1) / 2) / a.check_stride : 0;
     const int lattice = (a.check_stride > 0 && a.lattice_pass != 2) ? (2 * h + 1) * (2 * h + 1) : 0;
     const int positions = (a.lattice_pass == 1 ? 0 : a.n_e * a.n_e) + lattice;
     RLF_FIT_DISPATCH(k_fit_window, dim3((positions + 255) / 256, a.n_src), a);
-  } else if (!kMixed && a.num_r == 20 && (a.redo || a.n_src <= kSplitSources)) {
-    auto kern = k_fit_split<20>;
-    const int64_t items = (int64_t)a.n_src * ((a.n_valid + kSplitPoints - 1) / kSplitPoints);
-    const int64_t blocks = std::min(items, resident_blocks(kern, kSplitThreads));
-    hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, blocks)), dim3(kSplitThreads), 0, st, a);
+  } else if (a.redo || a.n_src <= kKnotSources) {
+    return launch_knots<kMixed, 0>(a, st);
   } else {
     RLF_FIT_DISPATCH(k_fit, dim3((a.n_valid + 255) / 256, a.n_src), a);
   }
@@ -617,22 +646,30 @@ int queue_blocks_per_cu(int num_r) {
 hipError_t launch_fit_f64(const FitArgs &a, hipStream_t st) { return launch<false>(a, st); }
 hipError_t launch_fit_mixed(const FitArgs &a, hipStream_t st) { return launch<true>(a, st); }
 
-hipError_t launch_refine_eval(const FitArgs &a, const RefineArgs &r, int mixed, hipStream_t st) {
-  const dim3 grid((r.max_side * r.max_side + 255) / 256, a.n_src);
-  if (mixed) {
-    constexpr bool kMixed = true;
-    if (a.n_pos)
-      RLF_POS_DISPATCH(k_refine_eval, grid, a, r);
-    else
-      RLF_FIT_DISPATCH(k_refine_eval, grid, a, r);
-  } else {
-    constexpr bool kMixed = false;
-    if (a.n_pos)
-      RLF_POS_DISPATCH(k_refine_eval, grid, a, r);
-    else
-      RLF_FIT_DISPATCH(k_refine_eval, grid, a, r);
-  }
+namespace {
+
+template <bool kMixed, int NP>
+hipError_t refine_eval(const FitArgs &a, const RefineArgs &r, hipStream_t st) {
+  hipLaunchKernelGGL((k_refine_eval<kMixed, NP>), dim3((r.max_side * r.max_side + 63) / 64, a.n_src), dim3(KnotSplit<kMixed, NP>::kThreads), 0, st, a, r,
+                     a.num_r);
   return hipGetLastError();
+}
+
+template <bool kMixed>
+hipError_t refine_eval(const FitArgs &a, const RefineArgs &r, hipStream_t st) {
+  switch (a.n_pos) {
+    case 0: return refine_eval<kMixed, 0>(a, r, st);
+    case 9: return refine_eval<kMixed, 9>(a, r, st);
+    case 25: return refine_eval<kMixed, 25>(a, r, st);
+    case 49: return refine_eval<kMixed, 49>(a, r, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_refine_eval(const FitArgs &a, const RefineArgs &r, int mixed, hipStream_t st) {
+  return mixed ? refine_eval<true>(a, r, st) : refine_eval<false>(a, r, st);
 }
 
 hipError_t launch_lattice_windows(const FitArgs &a, double log_frac, int32_t *win, hipStream_t st) {

@@ -1,9 +1,9 @@
-"""The split likelihood grid of small catalogues, and the full refit of
-flagged sources it also serves, against the oracle and against the grid of
+"""The likelihood grid with the knots shared by waves (small catalogues, and
+the full refit of flagged sources) against the oracle and against the grid of
 larger catalogues: the largest catalogue it takes and the first it does not,
-grids whose point count is not a multiple of a block's 32 points, and refits
-of none, of some (first, last and scattered over several chunks of 256 flags)
-and of all sources.  Both kernels add the same terms in another order, so
+grids whose point count is not a multiple of a block's 64 points, knot numbers
+that do not fill the waves' blocks of five, and refits of none, of some and of
+all sources.  Both kernels add the same terms in another order, so
 their ln L agree to the oracle's tolerance."""
 import numpy as np
 import pytest
@@ -28,14 +28,16 @@ def _facets(n_src, p=None, seed=5):
     return o, cat, resid, ctx, f
 
 
-@pytest.mark.parametrize("n_src,n_e,step", [(1, 81, 0.02), (24, 81, 0.02), (25, 81, 0.02), (3, 21, 0.1), (2, 3, 0.5)])
-def test_small_catalogue_grid(n_src, n_e, step):
-    o, cat, resid, ctx, f = _facets(n_src, rlf.params(n_e=n_e, e_step=step))
+@pytest.mark.parametrize("n_src,n_e,step,num_r", [(1, 81, 0.02, 20), (48, 81, 0.02, 20), (49, 81, 0.02, 20),
+                                                  (3, 21, 0.1, 20), (2, 3, 0.5, 20), (2, 81, 0.02, 7),
+                                                  (2, 81, 0.02, 23), (2, 81, 0.02, 32), (2, 81, 0.02, 2)])
+def test_small_catalogue_grid(n_src, n_e, step, num_r):
+    o, cat, resid, ctx, f = _facets(n_src, rlf.params(n_e=n_e, e_step=step, num_r=num_r))
     out = G.fit_out_tensors(n_src, n_e)
     ctx.fit_sources(f, out, want_surface=True)
     ctx.sync()
     h = G.host(out)
-    p = oracle.Params(n_e=n_e, e_step=step)
+    p = oracle.Params(n_e=n_e, e_step=step, num_r=num_r)
     for s in sorted({0, n_src // 2, n_src - 1}):
         surf, est = oracle.fit_source(G.oracle_facet(o, resid, cat, s), cat.flux_jy[s], p)
         G.check_fit(h, s, surf, [est] if n_e < 81 else G.oracle_estimate_variants(surf), h["surface"][s])
