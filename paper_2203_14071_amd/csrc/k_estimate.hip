@@ -19,11 +19,15 @@ namespace rlf {
 
 namespace {
 
-// Threads per block (one block per source): a pass over the 6,333 grid values
-// is a few loads per thread; the mixed form's recheck needs twice the
-// registers.
-template <bool kRecheck>
-constexpr int est_threads() { return kRecheck ? 512 : 1024; }
+// One block per source; the launch is bound by the latency of its chain of
+// loads, reductions and barriers.  The block holds up to kHeld grid values in
+// registers between its passes (the 81 x 81 grid has 6,333 points; larger
+// grids are read again by every pass) and reduces the sums of a pass
+// together: one source takes 13 us, against 20 with every pass reading the
+// values and reducing sum by sum.  1,024 threads: 16 us (the held values
+// spill); values held in LDS: 18 us.
+constexpr int kThreads = 512, kWavesEst = kThreads / 64;
+constexpr int kHeld = 14 * kThreads;
 constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
 
 // ln L(e) of source s at (e1, e2) in FP64, evaluated by one whole wave (all
@@ -80,18 +84,25 @@ __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, doub
   return mx + log(acc);
 }
 
-template <int kWavesEst>
-__device__ __forceinline__ double block_sum(double x, double *sh) {
+// Sums of N values over the block, in the order of the waves; sh holds
+// N * kWavesEst values.
+template <int N>
+__device__ __forceinline__ void block_sum(double (&x)[N], double *sh) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-  for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
-  if (lane == 0) sh[wid] = x;
-  __syncthreads();
-  double t = 0.0;
+  for (int i = 0; i < N; ++i) {
 #pragma unroll
-  for (int w = 0; w < kWavesEst; ++w) t += sh[w];
+    for (int d = 32; d > 0; d >>= 1) x[i] += __shfl_xor(x[i], d);
+    if (lane == 0) sh[i * kWavesEst + wid] = x[i];
+  }
   __syncthreads();
-  return t;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    x[i] = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWavesEst; ++w) x[i] += sh[i * kWavesEst + w];
+  }
+  __syncthreads();
 }
 
 __device__ __forceinline__ bool grid_valid(int i1, int i2, int n_e, int r2) {
@@ -107,9 +118,8 @@ __device__ __forceinline__ bool in_box(const int32_t *win, int s, int i1, int i2
 }
 
 template <bool kRecheck>
-__global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateArgs a) {
-  constexpr int kThreads = est_threads<kRecheck>(), kWavesEst = kThreads / 64;
-  __shared__ double shd[kWavesEst];
+__global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
+  __shared__ double shd[4 * kWavesEst];
   __shared__ double shv[kWavesEst];
   __shared__ int shi[kWavesEst];
   __shared__ int touch;
@@ -121,6 +131,30 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
   const int ctr = (a.n_e - 1) / 2;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 
+  // fn(j, ln L) for this thread's points, increasing j
+  constexpr int kPer = kHeld / kThreads;
+  double held[kPer];
+  const bool hold = a.n_valid <= kHeld;
+  auto fill = [&]() {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int j = (int)threadIdx.x + i * kThreads;
+      held[i] = hold && n_cells > 0 && j < a.n_valid ? L[j] : 0.0;
+    }
+  };
+  auto each = [&](auto &&fn) {
+    if (hold) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int j = (int)threadIdx.x + i * kThreads;
+        if (j < a.n_valid) fn(j, held[i]);
+      }
+    } else {
+      for (int j = threadIdx.x; j < a.n_valid; j += kThreads) fn(j, L[j]);
+    }
+  };
+  fill();
+
   // pass 1: maximum, smallest index on ties (each thread scans increasing j)
   double best;
   int bi;
@@ -128,18 +162,17 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
     best = -INFINITY;
     bi = 0x7fffffff;
     if (n_cells > 0) {
-      for (int j = threadIdx.x; j < a.n_valid; j += kThreads) {
-        const double v = L[j];
+      each([&](int j, double v) {
         if (a.window) {
           const int f = a.epts[j];
           const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-          if (!in_box(a.window, s, i1, i2)) continue;
+          if (!in_box(a.window, s, i1, i2)) return;
         }
         if (v > best) {
           best = v;
           bi = j;
         }
-      }
+      });
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
@@ -197,6 +230,7 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
     }
     __threadfence_block();
     __syncthreads();
+    fill();
     find_max();
   }
 
@@ -236,11 +270,10 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
   // (the set may continue beyond it: the narrowed result is not trusted) or
   // an evaluated lattice point outside the window reaches the set
   const double thr = best + a.log_frac;
-  double sw = 0.0, s1 = 0.0, s2 = 0.0, cnt = 0.0;
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};          // weight, first moments, count
   if (threadIdx.x == 0) touch = 0;
   __syncthreads();
-  for (int j = threadIdx.x; j < a.n_valid; j += kThreads) {
-    const double v = L[j];
+  each([&](int j, double v) {
     if (v >= thr) {
       const int f = a.epts[j];
       const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
@@ -249,7 +282,7 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
         if (a.redo_out && a.check_stride > 0 && (i1 - ctr) % a.check_stride == 0 &&
             (i2 - ctr) % a.check_stride == 0)
           atomicOr(&touch, 1);
-        continue;
+        return;
       }
       if (a.window && a.redo_out) {
         const int nb[4][2] = {{1, 0}, {-1, 0}, {0, 1}, {0, -1}};
@@ -260,36 +293,32 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
       }
       const double w = exp(v - best);
       const double x1 = (double)(i1 - ctr) * a.e_step, x2 = (double)(i2 - ctr) * a.e_step;
-      sw += w;
-      s1 += w * x1;
-      s2 += w * x2;
-      cnt += 1.0;
+      sum[0] += w;
+      sum[1] += w * x1;
+      sum[2] += w * x2;
+      sum[3] += 1.0;
     }
-  }
-  sw = block_sum<kWavesEst>(sw, shd);
-  s1 = block_sum<kWavesEst>(s1, shd);
-  s2 = block_sum<kWavesEst>(s2, shd);
-  cnt = block_sum<kWavesEst>(cnt, shd);
-  const double m1 = s1 / sw, m2 = s2 / sw;
+  });
+  block_sum(sum, shd);
+  const double sw = sum[0], cnt = sum[3];
+  const double m1 = sum[1] / sw, m2 = sum[2] / sw;
 
   // pass 3: central second moments
-  double c11 = 0.0, c22 = 0.0, c12 = 0.0;
-  for (int j = threadIdx.x; j < a.n_valid; j += kThreads) {
-    const double v = L[j];
+  double sec[3] = {0.0, 0.0, 0.0};
+  each([&](int j, double v) {
     if (v >= thr) {
       const int f = a.epts[j];
       const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-      if (!in_box(a.window, s, i1, i2)) continue;
+      if (!in_box(a.window, s, i1, i2)) return;
       const double w = exp(v - best);
       const double d1 = (double)(i1 - ctr) * a.e_step - m1, d2 = (double)(i2 - ctr) * a.e_step - m2;
-      c11 += w * d1 * d1;
-      c22 += w * d2 * d2;
-      c12 += w * d1 * d2;
+      sec[0] += w * d1 * d1;
+      sec[1] += w * d2 * d2;
+      sec[2] += w * d1 * d2;
     }
-  }
-  c11 = block_sum<kWavesEst>(c11, shd) / sw;
-  c22 = block_sum<kWavesEst>(c22, shd) / sw;
-  c12 = block_sum<kWavesEst>(c12, shd) / sw;
+  });
+  block_sum(sec, shd);
+  const double c11 = sec[0] / sw, c22 = sec[1] / sw, c12 = sec[2] / sw;
 
   if (threadIdx.x == 0) {
     const double sd1 = sqrt(c11), sd2 = sqrt(c22);
@@ -327,9 +356,9 @@ __global__ __launch_bounds__(est_threads<kRecheck>()) void k_estimate(EstimateAr
 
 hipError_t launch_estimate(const EstimateArgs &a, hipStream_t st) {
   if (a.fit64)
-    hipLaunchKernelGGL(k_estimate<true>, dim3(a.n_src), dim3(est_threads<true>()), 0, st, a);
+    hipLaunchKernelGGL(k_estimate<true>, dim3(a.n_src), dim3(kThreads), 0, st, a);
   else
-    hipLaunchKernelGGL(k_estimate<false>, dim3(a.n_src), dim3(est_threads<false>()), 0, st, a);
+    hipLaunchKernelGGL(k_estimate<false>, dim3(a.n_src), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 
