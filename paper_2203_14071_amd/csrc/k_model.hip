@@ -10,7 +10,10 @@
 //               sum (the profile's constant 3/2 is applied once at the end);
 //   mixed form: phase and its fractional part (v_fract_f64, exact, in
 //               [0, 1) turns) in FP64, rounded to FP32 for v_sin/v_cos
-//               (argument in turns), profile and sum in FP32.
+//               (argument in turns), profile and sum in FP32.  The three
+//               transcendental instructions take 24 of the 57 cycles of 64
+//               pairs; with several channels the phase and the quadratic
+//               form are formed once per row and group of channels.
 // Two entry kernels: visibilities in caller order (rlf_model_vis), and the
 // residual in the facet object's uv-sorted order (extraction input).  Their
 // FP64 forms take a 2048-entry table (32 KB of LDS; sin's x^5 term drops,
@@ -80,6 +83,36 @@ __global__ __launch_bounds__(model_threads<kMixed>()) void k_model(ModelArgs a) 
       r = make_float2(fmaf(-sp, acc.x, o.x), fmaf(-sp, acc.y, o.y));
     }
     out[i] = r;
+  }
+}
+
+// Mixed form, several channels: one thread per row and group of NC channels
+// (blockIdx.y); the last group's channels beyond n_chan repeat the last one
+// and are not stored.
+template <int NC>
+__global__ __launch_bounds__(256) void k_model_rows(ModelArgs a) {
+  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= a.n_rows) return;
+  const int c0 = blockIdx.y * NC;
+  double sc[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) sc[k] = a.chan->scale[min(c0 + k, a.n_chan - 1)];
+  float2 acc[NC];
+  sum_mixed_row<NC>(a.u_m[row], a.v_m[row], a.w_m[row], sc, a.src32, a.s_begin, a.s_end, acc);
+  const int64_t i0 = row * a.n_chan + c0;
+  float2 *out = reinterpret_cast<float2 *>(a.out) + i0;
+  const float2 *in = reinterpret_cast<const float2 *>(a.mode == 2 ? a.vis_in : a.out) + i0;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    if (c0 + k >= a.n_chan) break;
+    const float sp = (float)a.chan->spec[c0 + k];
+    if (a.mode == 0) {
+      out[k] = make_float2(sp * acc[k].x, sp * acc[k].y);
+    } else {
+      const float sg = a.mode == 1 ? sp : -sp;
+      const float2 o = in[k];
+      out[k] = make_float2(fmaf(sg, acc[k].x, o.x), fmaf(sg, acc[k].y, o.y));
+    }
   }
 }
 
@@ -172,7 +205,40 @@ hipError_t launch_update_sorted(const UpdateArgs &a, int mixed, hipStream_t st) 
   return hipGetLastError();
 }
 
+namespace {
+
+// Channels per thread of k_model_rows, or 1: one thread per visibility
+// (k_model).  Time per 1000 sources and 64 visibilities, us on the whole
+// card, 579,181 rows: k_model 0.027; groups of two 0.027, of three 0.023, of
+// four 0.021; five and eight fall back to 0.024 and 0.022 (their registers
+// leave the FP32 instructions more operand conflicts), so more channels go in
+// groups of four.  A last group with one idle channel still gains (7
+// channels), five channels do not.  Below three waves per SIMD the larger
+// pieces of work leave the card idle at the end: 60,000 rows of three or four
+// channels 0.91x and 0.85x, 180,000 of four 0.99x; from 196,608 groups on
+// 1.00x to 1.13x (579,181 rows of eight 1,938 -> 1,713 us).
+constexpr int64_t kRowWaves = 3072;
+
+int row_channels(int64_t n_rows, int n_chan) {
+  const int nc = n_chan < 4 ? n_chan : n_chan == 6 || n_chan == 9 ? 3 : 4;
+  const int64_t groups = (n_chan + nc - 1) / nc;
+  return n_chan == 5 || (n_rows + 63) / 64 * groups < kRowWaves ? 1 : nc;
+}
+
+}  // namespace
+
 hipError_t launch_model(const ModelArgs &a, int mixed, hipStream_t st) {
+  const int nc = mixed ? row_channels(a.n_rows, a.n_chan) : 1;
+  if (nc > 1) {
+    const dim3 grid((unsigned)((a.n_rows + 255) / 256), (unsigned)((a.n_chan + nc - 1) / nc)), block(256);
+    if (nc == 2)
+      hipLaunchKernelGGL(k_model_rows<2>, grid, block, 0, st, a);
+    else if (nc == 3)
+      hipLaunchKernelGGL(k_model_rows<3>, grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL(k_model_rows<4>, grid, block, 0, st, a);
+    return hipGetLastError();
+  }
   const int64_t n = a.n_rows * a.n_chan;
   if (mixed) {
     constexpr int t = model_threads<true>();

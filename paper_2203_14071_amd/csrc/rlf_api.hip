@@ -183,6 +183,9 @@ SrcMixed to_mixed(const SrcModel &m) {
   r.q12x2 = (float)m.q12x2;
   r.q22 = (float)m.q22;
   r.theta = m.theta;
+  // S^{-2/3}; for no flux a value whose -3/2 power is zero in FP32
+  const double cr = std::cbrt((double)r.flux);
+  r.c0 = r.flux > 0.0f ? (float)std::fmin(1.0 / (cr * cr), 1e38) : 1e38f;
   return r;
 }
 

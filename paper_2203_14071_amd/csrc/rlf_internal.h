@@ -29,6 +29,7 @@ struct alignas(64) SrcMixed {
   double l, m, n1;
   float flux, q11, q12x2, q22;
   double theta;
+  float c0;                  // flux^{-2/3}: flux x^{-3/2} = (c0 x)^{-3/2}
 };
 static_assert(sizeof(SrcMixed) == 64, "one 64-byte scalar load per source");
 
