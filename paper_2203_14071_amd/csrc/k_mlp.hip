@@ -252,6 +252,162 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmNTArgs g) {
       }
 }
 
+__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+
+__device__ __forceinline__ float gelu_grad(float z) {
+  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+}
+
+// Products too small for 128 x 128 tiles to fill the card (512 x 512 is 16 of
+// them): one wave per 32 x 32 tile, fragments straight from memory (both
+// operands contiguous along k, so a fragment is one 16-byte load per lane),
+// 512 k in flight at once, no LDS and no barrier; the bias and GELU of the
+// forward pass, or GELU's derivative and the bias gradient's partial sums of
+// the backward pass, are applied to the accumulators, and a launch can carry
+// a second product beside the first.  Sums run over k in the order of
+// k_gemm_nt, the epilogues' in that of k_bias_act and k_gelu_back_colsum, so
+// the results are the same bits.  Bound by the latency of the loads.  512
+// rows: forward layer 12.2 + 4.9 us (128 x 128 tiles, then bias and GELU) ->
+// 8.0 us; backward layer, both products, GELU's derivative and the transposes,
+// 34 -> 11.0 us.
+constexpr int kTileSteps = 16;                   // 16-k steps per register buffer
+
+template <bool kWhole>
+__device__ __forceinline__ void tile_load(bf16x8 (&fa)[kTileSteps], bf16x8 (&fb)[kTileSteps], const __bf16 *pa,
+                                          const __bf16 *pb, int k0, int ke, int half) {
+#pragma unroll
+  for (int s = 0; s < kTileSteps; ++s) {
+    const int k = k0 + 16 * s;                   // this lane's eight: k + 8 half ...
+    if (kWhole || k + 8 * half + 8 <= ke) {
+      fa[s] = *reinterpret_cast<const bf16x8 *>(pa + k);
+      fb[s] = *reinterpret_cast<const bf16x8 *>(pb + k);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) fa[s][e] = fb[s][e] = to_bf16(0.0f);
+    }
+  }
+}
+
+// One tile's product over k in [kb, ke), ke - kb a multiple of 8.
+__device__ __forceinline__ f32x16 tile_product(const TileArgs &g, int m0, int n0, int kb, int ke) {
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const __bf16 *pa = g.a + (int64_t)min(m0 + (lane & 31), g.M - 1) * g.lda + 8 * half;
+  const __bf16 *pb = g.b + (int64_t)min(n0 + (lane & 31), g.N - 1) * g.ldb + 8 * half;
+  constexpr int kStep = 16 * kTileSteps;
+  f32x16 acc;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  bf16x8 a0[kTileSteps], b0[kTileSteps], a1[kTileSteps], b1[kTileSteps];
+  auto load = [&](bf16x8 (&fa)[kTileSteps], bf16x8 (&fb)[kTileSteps], int k0) {
+    if (k0 + kStep <= ke)
+      tile_load<true>(fa, fb, pa, pb, k0, ke, half);
+    else
+      tile_load<false>(fa, fb, pa, pb, k0, ke, half);
+  };
+  auto mul = [&](const bf16x8 (&fa)[kTileSteps], const bf16x8 (&fb)[kTileSteps]) {
+#pragma unroll
+    for (int s = 0; s < kTileSteps; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s], fb[s], acc, 0, 0, 0);
+  };
+  load(a0, b0, kb);
+  for (int k0 = kb; k0 < ke; k0 += 2 * kStep) {
+    if (k0 + kStep < ke) load(a1, b1, k0 + kStep);
+    mul(a0, b0);
+    if (k0 + 2 * kStep < ke) load(a0, b0, k0 + 2 * kStep);
+    if (k0 + kStep < ke) mul(a1, b1);
+  }
+  return acc;
+}
+
+// The tile of block L of n (all of one product) in XCD-aware order, as
+// nt_tile: n tiles fastest, then m tiles, then k slices.
+__device__ __forceinline__ void tile_of(const TileArgs &g, int L, int n, int &n0, int &m0, int &z) {
+  const int gx = (g.N + 31) / 32, gy = (g.M + 31) / 32;
+  const int x = L & 7, r = L >> 3, q = n >> 3, rem = n & 7;
+  const int T = x * q + min(x, rem) + r;
+  n0 = (T % gx) * 32;
+  m0 = ((T / gx) % gy) * 32;
+  z = T / (gx * gy);
+}
+
+__host__ __device__ inline int tile_count(const TileArgs &g) {
+  return ((g.N + 31) / 32) * ((g.M + 31) / 32) * g.split;
+}
+
+// Element r of lane l's accumulators is row 8(r/4) + 4(l/32) + r%4, column l%32.
+template <int kMode>
+__global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int n1 = tile_count(g1);
+  int m0, n0, z;
+  if ((int)blockIdx.x >= n1 || kMode == kTilePlain) {
+    const TileArgs &g = kMode == kTilePlain ? g1 : g2;
+    const int first = kMode == kTilePlain ? 0 : n1;
+    tile_of(g, blockIdx.x - first, tile_count(g), n0, m0, z);
+    const int kper = ((g.K + g.split - 1) / g.split + kTK - 1) / kTK * kTK;
+    const f32x16 acc = tile_product(g, m0, n0, z * kper, min(g.K, (z + 1) * kper));
+    float *out = g.split > 1 ? g.ws + (int64_t)z * g.M * g.N : g.c;
+    const int n = n0 + (lane & 31);
+    if (n < g.N)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (m < g.M) out[(int64_t)m * g.N + n] = acc[r];
+      }
+    return;
+  }
+  tile_of(g1, blockIdx.x, n1, n0, m0, z);
+  const int n = n0 + (lane & 31);                // N a multiple of 32 here
+  if (kMode == kTileForward) {
+    const float bias = g1.bias[n];
+    const f32x16 acc = tile_product(g1, m0, n0, 0, g1.K);
+    bf16x4 hq[4];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 8 * (r >> 2) + 4 * half + (r & 3);
+      const float v = acc[r] + bias;
+      const __bf16 h = to_bf16(gelu(v));
+      hq[r >> 2][r & 3] = h;
+      if (m < g1.M) {
+        g1.z[(int64_t)m * g1.N + n] = v;
+        g1.h[(int64_t)m * g1.N + n] = h;
+      }
+    }
+    if (g1.ht)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = m0 + 8 * q + 4 * half;
+        if (m < g1.M) *reinterpret_cast<bf16x4 *>(g1.ht + (int64_t)n * g1.M + m) = hq[q];
+      }
+    return;
+  }
+  float zv[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    zv[r] = g1.z[(int64_t)min(m0 + 8 * (r >> 2) + 4 * half + (r & 3), g1.M - 1) * g1.N + n];
+  const f32x16 acc = tile_product(g1, m0, n0, 0, g1.K);
+  bf16x4 dq[4];
+  float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};       // rows g, g + 4, ... in order, g = 0..3
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + 8 * (r >> 2) + 4 * half + (r & 3);
+    const bool in = m < g1.M;
+    const float x = in ? acc[r] : 0.0f, gg = in ? gelu_grad(zv[r]) : 0.0f;
+    const __bf16 d = to_bf16(x * gg);
+    dq[r >> 2][r & 3] = d;
+    if (in) g1.dz[(int64_t)m * g1.N + n] = d;
+    const float xo = __shfl_xor(x, 32), go = __shfl_xor(gg, 32);   // the other half's row
+    sum[r & 3] = fmaf(half ? xo : x, half ? go : gg, sum[r & 3]);
+    sum[r & 3] = fmaf(half ? x : xo, half ? gg : go, sum[r & 3]);
+  }
+  if (g1.dzt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = m0 + 8 * q + 4 * half;
+      if (m < g1.M) *reinterpret_cast<bf16x4 *>(g1.dzt + (int64_t)n * g1.M + m) = dq[q];
+    }
+  if (half == 0) g1.part[(int64_t)(m0 / 32) * g1.N + n] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+}
+
 // dst[c][r] = src[r][c] for BF16 matrices [rows x cols]: 64 x 64 tiles
 // through LDS, four BF16 (8 bytes) per global access when the tile is whole
 // and the row lengths are multiples of 4, else one element per access.  One
@@ -330,10 +486,19 @@ __global__ __launch_bounds__(256) void k_reduce_split(const float *ws, int split
   }
 }
 
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+// z = sum of the slices in order + b, h = GELU(z): k_reduce_split and
+// k_bias_act in one pass.
+__global__ __launch_bounds__(256) void k_reduce_bias_act(const float *__restrict__ ws, int split,
+                                                         const float *__restrict__ b, int64_t rows, int cols,
+                                                         float *__restrict__ z, __bf16 *__restrict__ h) {
+  const int64_t n = rows * cols;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    float acc = ws[i];
+    for (int s = 1; s < split; ++s) acc += ws[(int64_t)s * n + i];
+    const float v = acc + b[i % cols];
+    z[i] = v;
+    h[i] = to_bf16(gelu(v));
+  }
 }
 
 // z = c + b; h = GELU(z) (BF16) or, for the output layer, y = z (FP32)
@@ -704,9 +869,45 @@ hipError_t launch_gemm_nt(const GemmNTArgs &g, int split_k, hipStream_t st) {
   if (split_k > 1 && (!g.ws || (int64_t)split_k * g.M * g.N > g.ws_floats)) return hipErrorInvalidValue;
   const dim3 grid((g.N + kTN - 1) / kTN, (g.M + kTM - 1) / kTM, split_k > 1 ? split_k : 1);
   hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, g);
-  if (split_k > 1)
+  if (split_k > 1 && g.c)
     hipLaunchKernelGGL(k_reduce_split, dim3(grid_for((int64_t)g.M * g.N)), dim3(256), 0, st, g.ws, split_k, g.M, g.N,
                        g.c, g.ldc);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs *plain, hipStream_t st) {
+  const TileArgs *both[2] = {&first, plain};
+  for (const TileArgs *g : both) {
+    if (!g) continue;
+    const bool epi = g == &first && mode != kTilePlain;
+    if (g->M < 1 || g->N < 1 || g->K < 1 || g->split < 1 || g->K % 8 || g->lda % 8 || g->ldb % 8 ||
+        (epi && (g->split != 1 || g->N % 32 || ((g->ht || g->dzt) && g->M % 8))) || (g->split > 1 && !g->ws))
+      return hipErrorInvalidValue;
+  }
+  if (plain && mode == kTilePlain) return hipErrorInvalidValue;
+  const TileArgs none{};
+  const dim3 grid((unsigned)(tile_count(first) + (plain ? tile_count(*plain) : 0))), block(64);
+  if (mode == kTileForward)
+    hipLaunchKernelGGL(k_gemm_tile<kTileForward>, grid, block, 0, st, first, plain ? *plain : none);
+  else if (mode == kTileBackward)
+    hipLaunchKernelGGL(k_gemm_tile<kTileBackward>, grid, block, 0, st, first, plain ? *plain : none);
+  else
+    hipLaunchKernelGGL(k_gemm_tile<kTilePlain>, grid, block, 0, st, first, none);
+  const TileArgs &p = plain ? *plain : first;
+  if (p.split > 1)
+    hipLaunchKernelGGL(k_reduce_split, dim3(grid_for((int64_t)p.M * p.N)), dim3(256), 0, st, p.ws, p.split, p.M, p.N,
+                       p.c, (int64_t)p.N);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, int64_t rows, int cols, float *z,
+                                  __bf16 *h, hipStream_t st) {
+  hipLaunchKernelGGL(k_reduce_bias_act, dim3(grid_for(rows * cols)), dim3(256), 0, st, ws, split, b, rows, cols, z, h);
+  return hipGetLastError();
+}
+
+hipError_t launch_colsum_join(const float *part, int slices, int cols, float *db, hipStream_t st) {
+  hipLaunchKernelGGL(k_colsum_join, dim3((cols + 3) / 4), dim3(256), 0, st, part, slices, cols, db);
   return hipGetLastError();
 }
 

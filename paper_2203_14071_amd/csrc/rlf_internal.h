@@ -301,11 +301,29 @@ struct GemmNTArgs {
   int64_t lda;
   const __bf16 *b;
   int64_t ldb;
-  float *c;
+  float *c;                  // null with a split: the partials stay in ws
   int64_t ldc;
   int32_t M, N, K;
   float *ws;                 // split-K partials [split x M x N]
   int64_t ws_floats;
+};
+
+// One product of k_gemm_tile, operands as GemmNTArgs, and what its epilogue
+// does with C: forward (z, h set): z = C + bias, h = GELU(z); backward (dz
+// set): dz = C gelu'(z) with the column sums of each 32 rows to part
+// [M / 32 x N]; neither: C as FP32 to c (or the split's partials to ws).
+// ht / dzt: also transposed ([N x M], M a multiple of 8) unless null.
+struct TileArgs {
+  const __bf16 *a, *b;
+  int64_t lda, ldb;
+  int32_t M, N, K, split;
+  float *c;                  // row stride N
+  float *ws;                 // split-K partials [split x M x N]
+  const float *bias;
+  float *z;                  // written forward, read backward
+  __bf16 *h, *ht;
+  __bf16 *dz, *dzt;
+  float *part;
 };
 
 struct FeatureArgs {
@@ -367,6 +385,15 @@ hipError_t launch_out_backward(const __bf16 *h, const __bf16 *dyb, const float *
 hipError_t launch_gelu_back_colsum(const float *dh, const float *z, int64_t rows, int cols, __bf16 *dzb, float *db,
                                    float *ws, int64_t ws_floats, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmNTArgs &g, int split_k, hipStream_t st);
+enum TileMode { kTilePlain, kTileForward, kTileBackward };
+// One launch of the 32 x 32-tile products `first` (whose epilogue is `mode`)
+// and, if given, `plain` (no epilogue; its split's partials are added up).
+hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs *plain, hipStream_t st);
+// z = sum of the split's slices in ws + bias, h = GELU(z)
+hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, int64_t rows, int cols, float *z,
+                                  __bf16 *h, hipStream_t st);
+hipError_t launch_colsum_join(const float *part, int slices, int cols, float *db, hipStream_t st);
+void colsum_slices(int64_t rows, int cols, int64_t ws_floats, int64_t *per, int *nsl);
 // dst[c][r] = src[r][c] for up to kMaxTransposeJobs BF16 matrices
 // [rows x cols] in one launch.
 constexpr int kMaxTransposeJobs = 4;

@@ -37,12 +37,15 @@ struct rlf_mlp {
   __bf16 *h[3] = {nullptr, nullptr, nullptr};
   float *y = nullptr, *cbuf = nullptr, *dy = nullptr, *dh = nullptr;
   float *ws = nullptr;                       // split-K partial products, column-sum slices
-  __bf16 *dyb = nullptr, *dzb = nullptr;
+  __bf16 *dyb = nullptr;
+  __bf16 *dzb[2] = {nullptr, nullptr};       // a layer's dZ, and the one before it while that is formed
+  float *part = nullptr;                     // column-sum slices of 32 rows
   // k-contiguous operands of the NT GEMM: the BF16 weights transposed per
   // layer (W_l^T [out x in] at the offsets of W_l), and per batch the layer
   // input and the gradient dZ transposed ([in x rows], [512 x rows])
   __bf16 *wbt = nullptr;
-  __bf16 *xt = nullptr, *ht = nullptr, *dzt = nullptr;
+  __bf16 *xt = nullptr;
+  __bf16 *ht[2] = {nullptr, nullptr}, *dzt[2] = {nullptr, nullptr};
   __bf16 *xf = nullptr;                      // network inputs of a facet object's sources [max_batch x 8192]
 };
 
@@ -68,12 +71,15 @@ void mlp_release(rlf_mlp *n) {
   dfree(n->dy);
   dfree(n->dh);
   dfree(n->dyb);
-  dfree(n->dzb);
   dfree(n->ws);
   dfree(n->wbt);
   dfree(n->xt);
-  dfree(n->ht);
-  dfree(n->dzt);
+  dfree(n->part);
+  for (int k = 0; k < 2; ++k) {
+    dfree(n->dzb[k]);
+    dfree(n->ht[k]);
+    dfree(n->dzt[k]);
+  }
   dfree(n->xf);
 }
 
@@ -86,6 +92,12 @@ int split_for(int M, int N, int K) {
   while (tiles * s * 2 <= kMaxSplitBlocks && K / (s * 2) >= 64) s *= 2;
   return s;
 }
+
+// Largest batch whose 512 x 512-layer products go through k_gemm_tile.  Time
+// of a step, us, with 128 x 128 tiles and with these: 2,048 rows 255 | 244,
+// 2,560 rows 314 | 318, 3,000 rows 389 | 360, 3,584 rows 356 | 359, 4,096
+// rows 379 | 400 (the large tiles then fill the card and read less).
+constexpr int64_t kTileRows = 3072;
 
 // C[M x N] = A * B with element strides (see GemmArgs).
 int gemm(rlf_mlp *net, const __bf16 *a, int64_t sam, int64_t sak, const __bf16 *b, int64_t sbk, int64_t sbn,
@@ -161,16 +173,38 @@ int update_wbt(rlf_mlp *n) {
 }
 
 // Forward of rows [0, nb) of x into the layer buffers; y_out receives the outputs.
-int forward_chunk(rlf_mlp *n, const __bf16 *x, int nb, float *y_out) {
+// A training step's forward also writes the second layer's transposed
+// activations if its weight gradients use them (ht1).
+int forward_chunk(rlf_mlp *n, const __bf16 *x, int nb, float *y_out, __bf16 *ht1 = nullptr) {
   rlf_ctx *c = n->c;
   const __bf16 *hin = x;
   int kin = kIn;
   const int64_t offW[3] = {kOffW1, kOffW2, kOffW3}, offB[3] = {kOffB1, kOffB2, kOffB3};
   for (int l = 0; l < 3; ++l) {
     // z = h W: rows of h and of W^T are both contiguous along the contraction
-    if (int e = gemm_nt(n, hin, kin, n->wbt + offW[l], kin, n->cbuf, kHid, nb, kHid, kin)) return e;
-    hipError_t e = launch_bias_act(n->cbuf, n->w + offB[l], nb, kHid, n->z[l], n->h[l], 1, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "bias/GELU launch");
+    const int split = split_nt(nb, kHid, kin);
+    hipError_t e;
+    if (l > 0 && nb <= kTileRows) {
+      TileArgs t{};
+      t.a = hin;
+      t.b = n->wbt + offW[l];
+      t.lda = t.ldb = kin;
+      t.M = nb;
+      t.N = kHid;
+      t.K = kin;
+      t.split = 1;
+      t.bias = n->w + offB[l];
+      t.z = n->z[l];
+      t.h = n->h[l];
+      t.ht = l == 1 ? ht1 : nullptr;
+      e = launch_gemm_tile(t, kTileForward, nullptr, c->stream);
+    } else {
+      float *out = split > 1 ? nullptr : n->cbuf;
+      if (int e2 = gemm_nt(n, hin, kin, n->wbt + offW[l], kin, out, kHid, nb, kHid, kin)) return e2;
+      e = split > 1 ? launch_reduce_bias_act(n->ws, split, n->w + offB[l], nb, kHid, n->z[l], n->h[l], c->stream)
+                    : launch_bias_act(n->cbuf, n->w + offB[l], nb, kHid, n->z[l], n->h[l], 1, c->stream);
+    }
+    if (e != hipSuccess) return hip_fail(c, e, "hidden layer launch");
     hin = n->h[l];
     kin = kHid;
   }
@@ -211,12 +245,16 @@ int rlf_mlp_create(rlf_ctx *c, int64_t max_batch, rlf_mlp **out) {
     if ((rc = dalloc(c, &n->dy, B * kOut))) break;
     if ((rc = dalloc(c, &n->dyb, B * kOut))) break;
     if ((rc = dalloc(c, &n->dh, B * kHid))) break;
-    if ((rc = dalloc(c, &n->dzb, B * kHid))) break;
     if ((rc = dalloc(c, &n->ws, kWsFloats))) break;
     if ((rc = dalloc(c, &n->wbt, kParams))) break;
     if ((rc = dalloc(c, &n->xt, B * kIn))) break;
-    if ((rc = dalloc(c, &n->ht, B * kHid))) break;
-    if ((rc = dalloc(c, &n->dzt, B * kHid))) break;
+    if ((rc = dalloc(c, &n->part, (kTileRows / 32) * kHid))) break;
+    for (int k = 0; k < 2 && rc == RLF_OK; ++k) {
+      if ((rc = dalloc(c, &n->dzb[k], B * kHid))) break;
+      if ((rc = dalloc(c, &n->ht[k], B * kHid))) break;
+      rc = dalloc(c, &n->dzt[k], B * kHid);
+    }
+    if (rc) break;
     if ((rc = dalloc(c, &n->xf, B * kIn))) break;
     hipError_t e = hipMemset(n->w, 0, sizeof(float) * kParams);
     if (e == hipSuccess) e = hipMemset(n->m, 0, sizeof(float) * kParams);
@@ -445,7 +483,9 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   HIPCHK(c, hipSetDevice(c->device));
   const int nb = (int)rows;
   const __bf16 *xb = reinterpret_cast<const __bf16 *>(x);
-  if (int e = forward_chunk(n, xb, nb, n->y)) return e;
+  // the NT GEMM needs the batch dimension in multiples of 8 for the weight gradients
+  const bool nt_rows = nb % 8 == 0, tiled = nb <= kTileRows;
+  if (int e = forward_chunk(n, xb, nb, n->y, nt_rows ? n->ht[1] : nullptr)) return e;
   HIPCHK(c, launch_head(n->y, target, nb, n->dy, n->dyb, loss, c->stream));
   // output layer: dW4 = h3^T dY, db4 = sum dY (together, in the parameters'
   // order), dh3 = dY W4^T
@@ -453,25 +493,69 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   HIPCHK(c, launch_out_backward(n->h[2], n->dyb, n->dy, nb, n->wb + kOffW4, n->g + kOffW4, n->dh, n->ws, kWsFloats,
                                 c->stream));
   const int64_t offW[3] = {kOffW1, kOffW2, kOffW3}, offB[3] = {kOffB1, kOffB2, kOffB3};
-  // the NT GEMM needs the batch dimension in multiples of 8 for the weight gradients
-  const bool nt_rows = nb % 8 == 0;
-  for (int l = 2; l >= 0; --l) {
-    HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[l], nb, kHid, n->dzb, n->g + offB[l], n->ws, kWsFloats,
-                                      c->stream));
-    const __bf16 *hin = l == 0 ? xb : n->h[l - 1];
-    const int kin = l == 0 ? kIn : kHid;
-    if (nt_rows) {
-      // dW = h^T dZ with both operands transposed to [features x rows]
-      __bf16 *hin_t = l == 0 ? n->xt : n->ht;
-      const TransposeJob jobs[2] = {{hin, nb, kin, hin_t}, {n->dzb, nb, kHid, n->dzt}};
-      HIPCHK(c, launch_transpose_bf16(jobs, 2, c->stream));
-      if (int e = gemm_nt(n, hin_t, nb, n->dzt, nb, n->g + offW[l], kHid, kin, kHid, nb)) return e;
-    } else {
-      if (int e = gemm(n, hin, 1, kin, n->dzb, kHid, 1, n->g + offW[l], kin, kHid, nb)) return e;
-    }
+  int64_t per;
+  int slices;
+  colsum_slices(nb, kHid, kWsFloats, &per, &slices);
+  const bool fused = tiled && per == 32;         // the tiles' column sums are the slices
+  int cur = 0;
+  HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[2], nb, kHid, n->dzb[0], n->g + offB[2], n->ws, kWsFloats, c->stream));
+  if (nt_rows) {
+    // dW = h^T dZ with both operands transposed to [features x rows]: what the
+    // tile products do not write themselves, in one launch if that is all of it
+    const TransposeJob jx{xb, nb, kIn, n->xt}, jh0{n->h[0], nb, kHid, n->ht[0]}, jh1{n->h[1], nb, kHid, n->ht[1]};
+    const TransposeJob jobs[3] = {{n->dzb[0], nb, kHid, n->dzt[0]}, fused ? jx : jh1, jh0};
+    HIPCHK(c, launch_transpose_bf16(jobs, fused ? 3 : tiled ? 1 : 2, c->stream));
+  }
+  for (int l = 2; l > 0; --l, cur ^= 1) {
     // dh = dZ W^T: rows of dZ and of W both run along the output index
-    if (l > 0)
-      if (int e = gemm_nt(n, n->dzb, kHid, n->wb + offW[l], kHid, n->dh, kHid, nb, kHid, kHid)) return e;
+    TileArgs dh{}, dw{};
+    dh.a = n->dzb[cur];
+    dh.b = n->wb + offW[l];
+    dh.lda = dh.ldb = kHid;
+    dh.M = nb;
+    dh.N = dh.K = kHid;
+    dh.split = 1;
+    dh.c = n->dh;
+    dw.a = n->ht[l - 1];
+    dw.b = n->dzt[cur];
+    dw.lda = dw.ldb = nb;
+    dw.M = dw.N = kHid;
+    dw.K = nb;
+    dw.split = split_nt(kHid, kHid, nb);
+    dw.c = n->g + offW[l];
+    dw.ws = n->ws;
+    __bf16 *dz = n->dzb[cur ^ 1], *dzt = n->dzt[cur ^ 1];
+    if (!nt_rows)
+      if (int e = gemm(n, n->h[l - 1], 1, kHid, n->dzb[cur], kHid, 1, n->g + offW[l], kHid, kHid, nb)) return e;
+    if (fused) {
+      dh.z = n->z[l - 1];
+      dh.dz = dz;
+      dh.dzt = nt_rows ? dzt : nullptr;
+      dh.part = n->part;
+      HIPCHK(c, launch_gemm_tile(dh, kTileBackward, nt_rows ? &dw : nullptr, c->stream));
+      HIPCHK(c, launch_colsum_join(n->part, slices, kHid, n->g + offB[l - 1], c->stream));
+      continue;
+    }
+    if (tiled) {
+      HIPCHK(c, launch_gemm_tile(dh, kTilePlain, nullptr, c->stream));
+      if (nt_rows) HIPCHK(c, launch_gemm_tile(dw, kTilePlain, nullptr, c->stream));
+    } else {
+      if (int e = gemm_nt(n, dh.a, kHid, dh.b, kHid, n->dh, kHid, nb, kHid, kHid)) return e;
+      if (nt_rows)
+        if (int e = gemm_nt(n, dw.a, nb, dw.b, nb, dw.c, kHid, kHid, kHid, nb)) return e;
+    }
+    HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[l - 1], nb, kHid, dz, n->g + offB[l - 1], n->ws, kWsFloats,
+                                      c->stream));
+    if (nt_rows) {
+      const __bf16 *hin = l == 1 ? xb : n->h[0];
+      const TransposeJob jobs[2] = {{dz, nb, kHid, dzt}, {hin, nb, l == 1 ? kIn : kHid, l == 1 ? n->xt : n->ht[0]}};
+      HIPCHK(c, launch_transpose_bf16(jobs, 2, c->stream));
+    }
+  }
+  if (nt_rows) {
+    if (int e = gemm_nt(n, n->xt, nb, n->dzt[cur], nb, n->g + offW[0], kHid, kIn, kHid, nb)) return e;
+  } else {
+    if (int e = gemm(n, xb, 1, kIn, n->dzb[cur], kHid, 1, n->g + offW[0], kIn, kHid, nb)) return e;
   }
   n->step += 1;
   HIPCHK(c, launch_adam(n->w, n->wb, n->g, n->m, n->v, kParams, lr, n->step, c->stream));
