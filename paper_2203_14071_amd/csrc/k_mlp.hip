@@ -614,31 +614,10 @@ __device__ __forceinline__ void head_terms(float mu, float s_raw, float tv, floa
   *gs = s_raw < kLogVarMin ? 0.0f : 0.5f * (1.0f - e * e * ie) / nf;
 }
 
-__global__ __launch_bounds__(1024) void k_head(const float *__restrict__ y, const float *__restrict__ t, int64_t n,
-                                               float *__restrict__ dy, __bf16 *__restrict__ dyb,
-                                               double *__restrict__ loss) {
-  __shared__ double sh[16];
+// The loss by one block of 1024 threads (sh: 16 values).
+__device__ __forceinline__ void head_loss(const float *__restrict__ y, const float *__restrict__ t, int64_t n,
+                                          double *__restrict__ loss, double *sh) {
   const int64_t stride = blockDim.x;
-  if (blockIdx.x > 0) {
-    const int64_t i = (int64_t)(blockIdx.x - 1) * stride + threadIdx.x;
-    if (i >= n) return;
-    float yv[6], tv[3];
-#pragma unroll
-    for (int c = 0; c < 6; ++c) yv[c] = y[i * 6 + c];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) tv[d] = t[i * 3 + d];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      double lt;
-      float gm, gs;
-      head_terms(yv[d], yv[3 + d], tv[d], (float)n, &lt, &gm, &gs);
-      dy[i * 6 + d] = gm;
-      dy[i * 6 + 3 + d] = gs;
-      dyb[i * 6 + d] = to_bf16(gm);
-      dyb[i * 6 + 3 + d] = to_bf16(gs);
-    }
-    return;
-  }
   double acc = 0.0;
   for (int64_t i0 = threadIdx.x; i0 < n; i0 += kHeadRows * stride) {
     float yv[kHeadRows][6], tv[kHeadRows][3];
@@ -674,6 +653,201 @@ __global__ __launch_bounds__(1024) void k_head(const float *__restrict__ y, cons
   }
 }
 
+__global__ __launch_bounds__(1024) void k_head(const float *__restrict__ y, const float *__restrict__ t, int64_t n,
+                                               float *__restrict__ dy, __bf16 *__restrict__ dyb,
+                                               double *__restrict__ loss) {
+  __shared__ double sh[16];
+  const int64_t stride = blockDim.x;
+  if (blockIdx.x > 0) {
+    const int64_t i = (int64_t)(blockIdx.x - 1) * stride + threadIdx.x;
+    if (i >= n) return;
+    float yv[6], tv[3];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) yv[c] = y[i * 6 + c];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) tv[d] = t[i * 3 + d];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      double lt;
+      float gm, gs;
+      head_terms(yv[d], yv[3 + d], tv[d], (float)n, &lt, &gm, &gs);
+      dy[i * 6 + d] = gm;
+      dy[i * 6 + 3 + d] = gs;
+      dyb[i * 6 + d] = to_bf16(gm);
+      dyb[i * 6 + 3 + d] = to_bf16(gs);
+    }
+    return;
+  }
+  head_loss(y, t, n, loss, sh);
+}
+
+// The output layer of a training step in one launch: a block takes a slice of
+// 32 rows through y = h W4 + b4 and the loss gradient, then 128 of the 512
+// columns (blockIdx.y) through the slice's part of dW4 and db4, dh = dY W4^T
+// and dZ = dh gelu'(Z) with its column sums, with the arithmetic and the order
+// of k_out_forward, k_head, k_out_grad_part, k_out_dh and k_gelu_back_colsum
+// (which need 32-row slices of both sums).  Bound by latency, a chain of five
+// short phases: 512 rows 11.3 us, against 28 us of the five kernels (with all
+// 512 columns in one block 20.8 us: sixteen blocks for 256 CUs).
+constexpr int kSlice = 32, kHeadCols = 128, kDzLd = kSlice + 2;
+
+__global__ __launch_bounds__(1024) void k_head_slice(HeadArgs a) {
+  __shared__ __attribute__((aligned(16))) __bf16 sh[kSlice * 512];
+  __shared__ __attribute__((aligned(16))) __bf16 sw[kOutW];
+  __shared__ __bf16 sdz[kHeadCols * kDzLd];
+  __shared__ float sy[kSlice][6], sdy[kSlice][6], sdyb[kSlice][6], scol[4][kHeadCols];
+  const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * kSlice;
+  const int nr = (int)min((int64_t)kSlice, a.rows - r0);
+  // last phase: column c, rows g + 4 i with i = 4 up + 0..3
+  const int c = t & (kHeadCols - 1), g = (t >> 7) & 3, up = t >> 9;
+  const int col = (int)blockIdx.y * kHeadCols + c;
+  float zv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) zv[i] = a.z[(r0 + min(g + 16 * up + 4 * i, nr - 1)) * 512 + col];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e8 = t + 1024 * q;
+    bf16x8 v;
+    if ((e8 >> 6) < nr)
+      v = *reinterpret_cast<const bf16x8 *>(a.h + (r0 + (e8 >> 6)) * 512 + (e8 & 63) * 8);
+    else
+      for (int e = 0; e < 8; ++e) v[e] = to_bf16(0.0f);
+    *reinterpret_cast<bf16x8 *>(sh + e8 * 8) = v;
+  }
+  if (t < kOutW / 8) *reinterpret_cast<bf16x8 *>(sw + t * 8) = *reinterpret_cast<const bf16x8 *>(a.w + t * 8);
+  __syncthreads();
+  // the six weights of input k
+  auto weights = [&](int k, float (&w)[6]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t u = reinterpret_cast<const uint32_t *>(sw)[k * 3 + q];
+      w[2 * q] = __uint_as_float(u << 16);
+      w[2 * q + 1] = __uint_as_float(u & 0xffff0000u);
+    }
+  };
+  {                                                         // forward: a wave per two rows
+    float acc[2][6] = {};
+#pragma unroll
+    for (int k = lane; k < 512; k += 64) {
+      float w[6];
+      weights(k, w);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float hv = (float)sh[(wid + 16 * q) * 512 + k];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) acc[q][j] = fmaf(hv, w[j], acc[q][j]);
+      }
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) acc[q][j] += __shfl_xor(acc[q][j], d);
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+          const int r = wid + 16 * q;
+          const float yv = acc[q][j] + a.b[j];
+          sy[r][j] = yv;
+          if (r < nr && blockIdx.y == 0) a.y[(r0 + r) * 6 + j] = yv;
+        }
+  }
+  __syncthreads();
+  if (t < kSlice * 3) {                                     // loss gradient
+    const int r = t / 3, d = t - 3 * r;
+    double lt;
+    float gm = 0.0f, gs = 0.0f;
+    if (r < nr) head_terms(sy[r][d], sy[r][3 + d], a.target[(r0 + r) * 3 + d], (float)a.rows, &lt, &gm, &gs);
+    sdy[r][d] = gm;
+    sdy[r][3 + d] = gs;
+    sdyb[r][d] = (float)to_bf16(gm);
+    sdyb[r][3 + d] = (float)to_bf16(gs);
+  }
+  __syncthreads();
+  float *part = a.out_part + (int64_t)blockIdx.x * kOutWB;
+  if (t < kHeadCols * 6) {                                  // dW4 of the slice, and db4
+    const int v = (int)blockIdx.y * kHeadCols * 6 + t, k = v / 6, j = v - 6 * k;
+    float acc = 0.0f;
+#pragma unroll
+    for (int r = 0; r < kSlice; ++r) acc = fmaf((float)sh[r * 512 + k], sdyb[r][j], acc);
+    part[v] = acc;
+  } else if (blockIdx.y == 0 && t < kHeadCols * 6 + 6) {
+    float acc = 0.0f;
+    for (int r = 0; r < kSlice; ++r) acc = fmaf(1.0f, sdy[r][t - kHeadCols * 6], acc);
+    part[kOutW + t - kHeadCols * 6] = acc;
+  }
+  float w[6], dh[4], gg[4];
+  weights(col, w);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {                             // dZ
+    const int r = g + 16 * up + 4 * i;
+    dh[i] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) dh[i] = fmaf(sdyb[r][j], w[j], dh[i]);
+    gg[i] = r < nr ? gelu_grad(zv[i]) : 0.0f;
+    const __bf16 d = to_bf16(dh[i] * gg[i]);
+    sdz[c * kDzLd + r] = d;
+    if (r < nr) a.dz[(r0 + r) * 512 + col] = d;
+  }
+  if (up == 0) {                                            // column sums: the upper rows continue the lower ones'
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = fmaf(dh[i], gg[i], acc);
+    scol[g][c] = acc;
+  }
+  __syncthreads();
+  if (up == 1) {
+    float acc = scol[g][c];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = fmaf(dh[i], gg[i], acc);
+    scol[g][c] = acc;
+  }
+  if (a.dzt && t < kHeadCols * 4) {
+    const int k = t >> 2, r = (t & 3) * 8;
+    if (r < nr) {                                           // rows and so nr are multiples of 8
+      bf16x8 v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = sdz[k * kDzLd + r + e];
+      *reinterpret_cast<bf16x8 *>(a.dzt + (int64_t)(blockIdx.y * kHeadCols + k) * a.rows + r0 + r) = v;
+    }
+  }
+  __syncthreads();
+  if (t < kHeadCols)
+    a.part[(int64_t)blockIdx.x * 512 + blockIdx.y * kHeadCols + t] =
+        (scol[0][t] + scol[1][t]) + (scol[2][t] + scol[3][t]);
+}
+
+// One launch for a step's sums over slices (a wave per value, as
+// k_out_grad_join and k_colsum_join) and the loss (block 0).
+__global__ __launch_bounds__(1024) void k_join(JoinArgs a) {
+  __shared__ double sh[16];
+  if (blockIdx.x == 0) {
+    head_loss(a.y, a.target, a.rows, a.loss, sh);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  int v = ((int)blockIdx.x - 1) * 16 + (int)(threadIdx.x >> 6);
+  if (v >= kOutWB + 3 * 512) return;                        // whole waves
+  const float *p = a.out_part + v;
+  float *out = a.gw + v;
+  int cols = kOutWB;
+  if (v >= kOutWB) {
+    v -= kOutWB;
+    p = a.part[v >> 9] + (v & 511);
+    out = a.db[v >> 9] + (v & 511);
+    cols = 512;
+  }
+  float acc = 0.0f;
+  for (int s = lane; s < a.slices; s += 64) acc += p[(int64_t)s * cols];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
+  if (lane == 0) *out = acc;
+}
+
 // The hidden layers' backward epilogue and the first step of their bias
 // gradients in one pass: dZ = dH gelu'(Z) (BF16 copy for the products) over
 // a block of 64 columns and a slice of rows, with the slice's column sums
@@ -700,17 +874,86 @@ __global__ __launch_bounds__(256) void k_gelu_back_colsum(const float *dh, const
     part[(int64_t)blockIdx.y * cols + col] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
 }
 
-__global__ __launch_bounds__(256) void k_adam(float *w, __bf16 *wb, const float *g, float *m, float *v, int64_t n,
-                                              float lr, float b1, float b2, float eps, float c1, float c2) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    w[i] = wi;
-    if (wb) wb[i] = to_bf16(wi);
+struct AdamConst {
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float adam_value(float w, float g, float &m, float &v, const AdamConst &k) {
+  m = fmaf(1.0f - k.b1, g, k.b1 * m);
+  v = fmaf(g, (1.0f - k.b2) * g, k.b2 * v);
+  return w - k.lr * (m / k.c1) / (sqrtf(v / k.c2) + k.eps);
+}
+
+// Adam: the first mt blocks take one 64 x 64 tile of a weight matrix each
+// (16 bytes of four arrays per access) and also write its BF16 copy
+// transposed through LDS, the others the remaining values one by one.  Bound
+// by memory (32 bytes per weight read and written): 25 us for 4.7 million
+// weights, 6 TB/s, against 23.4 us without the transposed copy and 7.4 us for
+// a pass that made it.
+struct AdamTiles {
+  int64_t first[AdamMats::kMax + 1];             // first block of a matrix
+};
+
+__global__ __launch_bounds__(256) void k_adam(float *w, __bf16 *wb, __bf16 *wbt, const float *g, float *m, float *v,
+                                              int64_t n, AdamConst k, AdamMats mats, AdamTiles tiles) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const int64_t b = blockIdx.x, mt = tiles.first[AdamMats::kMax];
+  if (b >= mt) {
+    // what lies between and behind the matrices
+    for (int64_t i = (b - mt) * 256 + threadIdx.x; i < n; i += ((int64_t)gridDim.x - mt) * 256) {
+      int64_t p = i;
+#pragma unroll
+      for (int j = 0; j < AdamMats::kMax; ++j)
+        if (p >= mats.off[j]) p += mats.rows[j] * mats.cols[j];
+      float mi = m[p], vi = v[p];
+      const float wi = adam_value(w[p], g[p], mi, vi, k);
+      m[p] = mi;
+      v[p] = vi;
+      w[p] = wi;
+      wb[p] = to_bf16(wi);
+    }
+    return;
+  }
+  __shared__ __bf16 t[64][66];
+  int j = 0;
+  while (j + 1 < AdamMats::kMax && b >= tiles.first[j + 1]) ++j;
+  const int64_t cols = mats.cols[j], rows = mats.rows[j], off = mats.off[j];
+  const int64_t local = b - tiles.first[j], tx = cols / 64;
+  const int64_t r0 = local / tx * 64, c0 = local % tx * 64;
+  const int c4 = (threadIdx.x & 15) * 4, rb = threadIdx.x >> 4;
+  float4 wv[4], gv[4], mv[4], vv[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t p = off + (r0 + rb + 16 * q) * cols + c0 + c4;
+    wv[q] = *reinterpret_cast<const float4 *>(w + p);
+    gv[q] = *reinterpret_cast<const float4 *>(g + p);
+    mv[q] = *reinterpret_cast<const float4 *>(m + p);
+    vv[q] = *reinterpret_cast<const float4 *>(v + p);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t p = off + (r0 + rb + 16 * q) * cols + c0 + c4;
+    float4 x;
+    x.x = adam_value(wv[q].x, gv[q].x, mv[q].x, vv[q].x, k);
+    x.y = adam_value(wv[q].y, gv[q].y, mv[q].y, vv[q].y, k);
+    x.z = adam_value(wv[q].z, gv[q].z, mv[q].z, vv[q].z, k);
+    x.w = adam_value(wv[q].w, gv[q].w, mv[q].w, vv[q].w, k);
+    const bf16x4 xb = {to_bf16(x.x), to_bf16(x.y), to_bf16(x.z), to_bf16(x.w)};
+    *reinterpret_cast<float4 *>(w + p) = x;
+    *reinterpret_cast<float4 *>(m + p) = mv[q];
+    *reinterpret_cast<float4 *>(v + p) = vv[q];
+    *reinterpret_cast<bf16x4 *>(wb + p) = xb;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[rb + 16 * q][c4 + e] = xb[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int jc = rb + 16 * q, r4 = (threadIdx.x & 15) * 4;           // output row: column c0 + jc
+    bf16x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = t[r4 + e][jc];
+    *reinterpret_cast<bf16x4 *>(wbt + off + (c0 + jc) * rows + r0 + r4) = x;
   }
 }
 
@@ -906,8 +1149,15 @@ hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, in
   return hipGetLastError();
 }
 
-hipError_t launch_colsum_join(const float *part, int slices, int cols, float *db, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsum_join, dim3((cols + 3) / 4), dim3(256), 0, st, part, slices, cols, db);
+hipError_t launch_head_slice(const HeadArgs &a, hipStream_t st) {
+  if (a.rows < 1 || (a.dzt && a.rows % 8)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_head_slice, dim3((unsigned)((a.rows + kSlice - 1) / kSlice), 512 / kHeadCols), dim3(1024), 0, st,
+                     a);
+  return hipGetLastError();
+}
+
+hipError_t launch_join(const JoinArgs &a, hipStream_t st) {
+  hipLaunchKernelGGL(k_join, dim3(1 + (kOutWB + 3 * 512 + 15) / 16), dim3(1024), 0, st, a);
   return hipGetLastError();
 }
 
@@ -927,11 +1177,23 @@ hipError_t launch_transpose_bf16(const TransposeJob *jobs, int n_jobs, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float *w, __bf16 *wb, const float *g, float *m, float *v, int64_t n, float lr, int64_t step,
-                       hipStream_t st) {
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = (float)(1.0 - std::pow(0.9, (double)step)), c2 = (float)(1.0 - std::pow(0.999, (double)step));
-  hipLaunchKernelGGL(k_adam, dim3(grid_for(n)), dim3(256), 0, st, w, wb, g, m, v, n, lr, b1, b2, 1e-8f, c1, c2);
+hipError_t launch_adam(float *w, __bf16 *wb, __bf16 *wbt, const AdamMats &mats, const float *g, float *m, float *v,
+                       int64_t n, float lr, int64_t step, hipStream_t st) {
+  const AdamConst k{lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - std::pow(0.9, (double)step)),
+                    (float)(1.0 - std::pow(0.999, (double)step))};
+  AdamTiles tiles{};
+  int64_t rest = n, end = 0;
+  for (int j = 0; j < AdamMats::kMax; ++j) {
+    // in order, apart, inside the values, whole tiles, 16-byte accesses
+    if (mats.off[j] < end || mats.off[j] % 8 || mats.rows[j] % 64 || mats.cols[j] % 64) return hipErrorInvalidValue;
+    const int64_t size = mats.rows[j] * mats.cols[j];
+    end = mats.off[j] + size;
+    rest -= size;
+    tiles.first[j + 1] = tiles.first[j] + size / 4096;
+  }
+  if (end > n) return hipErrorInvalidValue;
+  const int64_t blocks = tiles.first[AdamMats::kMax] + (rest + 255) / 256;
+  hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, st, w, wb, wbt, g, m, v, rest, k, mats, tiles);
   return hipGetLastError();
 }
 

@@ -326,6 +326,36 @@ struct TileArgs {
   float *part;
 };
 
+// The output layer of a training step (k_head_slice): forward, loss
+// gradient, the layer's gradients and the hidden layer's dZ in one pass over
+// slices of 32 rows.
+struct HeadArgs {
+  const __bf16 *h;           // last hidden layer's activations [rows x 512]
+  const __bf16 *w;           // W4 [512 x 6]
+  const float *b;            // b4
+  const float *target;       // [rows x 3]
+  const float *z;            // last hidden layer's Z [rows x 512]
+  int64_t rows;
+  float *y;                  // [rows x 6]
+  __bf16 *dz;                // [rows x 512]
+  __bf16 *dzt;               // [512 x rows] (rows a multiple of 8), or null
+  float *part;               // column sums of dZ [slices x 512]
+  float *out_part;           // dW4 and db4 [slices x 3078]
+};
+
+// Sums over slices: parts of the output layer's gradients (out_part -> gw)
+// and of the hidden layers' bias gradients (part[l] -> db[l]), and the loss.
+struct JoinArgs {
+  int32_t slices;
+  const float *out_part;
+  float *gw;
+  const float *part[3];
+  float *db[3];
+  const float *y, *target;
+  int64_t rows;
+  double *loss;
+};
+
 struct FeatureArgs {
   int32_t s0;                // first source of the rows written
   int32_t n_src;             // rows written (sources s0 .. s0 + n_src - 1)
@@ -392,7 +422,8 @@ hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs
 // z = sum of the split's slices in ws + bias, h = GELU(z)
 hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, int64_t rows, int cols, float *z,
                                   __bf16 *h, hipStream_t st);
-hipError_t launch_colsum_join(const float *part, int slices, int cols, float *db, hipStream_t st);
+hipError_t launch_head_slice(const HeadArgs &a, hipStream_t st);
+hipError_t launch_join(const JoinArgs &a, hipStream_t st);
 void colsum_slices(int64_t rows, int cols, int64_t ws_floats, int64_t *per, int *nsl);
 // dst[c][r] = src[r][c] for up to kMaxTransposeJobs BF16 matrices
 // [rows x cols] in one launch.
@@ -403,8 +434,15 @@ struct TransposeJob {
   __bf16 *dst;
 };
 hipError_t launch_transpose_bf16(const TransposeJob *jobs, int n_jobs, hipStream_t st);
-hipError_t launch_adam(float *w, __bf16 *wb, const float *g, float *m, float *v, int64_t n, float lr, int64_t step,
-                       hipStream_t st);
+// One Adam step over n values; the first ones form the matrices [rows x cols]
+// of `mats` (both dimensions multiples of 64), whose BF16 copies are also
+// written transposed to wbt at the same offsets.
+struct AdamMats {
+  static constexpr int kMax = 3;
+  int64_t off[kMax], rows[kMax], cols[kMax];
+};
+hipError_t launch_adam(float *w, __bf16 *wb, __bf16 *wbt, const AdamMats &mats, const float *g, float *m, float *v,
+                       int64_t n, float lr, int64_t step, hipStream_t st);
 hipError_t launch_to_bf16(const float *x, __bf16 *y, int64_t n, hipStream_t st);
 hipError_t launch_features(const FeatureArgs &a, hipStream_t st);
 hipError_t launch_posterior_targets(const double *e1, const double *e2, const double *s1, const double *s2,

@@ -39,7 +39,7 @@ struct rlf_mlp {
   float *ws = nullptr;                       // split-K partial products, column-sum slices
   __bf16 *dyb = nullptr;
   __bf16 *dzb[2] = {nullptr, nullptr};       // a layer's dZ, and the one before it while that is formed
-  float *part = nullptr;                     // column-sum slices of 32 rows
+  float *part = nullptr;                     // slices of 32 rows: column sums per layer, output layer's gradients
   // k-contiguous operands of the NT GEMM: the BF16 weights transposed per
   // layer (W_l^T [out x in] at the offsets of W_l), and per batch the layer
   // input and the gradient dZ transposed ([in x rows], [512 x rows])
@@ -98,6 +98,7 @@ int split_for(int M, int N, int K) {
 // 2,560 rows 314 | 318, 3,000 rows 389 | 360, 3,584 rows 356 | 359, 4,096
 // rows 379 | 400 (the large tiles then fill the card and read less).
 constexpr int64_t kTileRows = 3072;
+constexpr int64_t kSlices = kTileRows / 32;
 
 // C[M x N] = A * B with element strides (see GemmArgs).
 int gemm(rlf_mlp *net, const __bf16 *a, int64_t sam, int64_t sak, const __bf16 *b, int64_t sbk, int64_t sbn,
@@ -161,21 +162,20 @@ int gemm_nt(rlf_mlp *net, const __bf16 *a, int64_t lda, const __bf16 *b, int64_t
   return RLF_OK;
 }
 
-// The transposed BF16 weights W_l^T [out x in] from W_l [in x out].
+// The hidden layers' transposed BF16 weights W_l^T [out x in] from W_l [in x out].
 int update_wbt(rlf_mlp *n) {
-  const int64_t offW[4] = {kOffW1, kOffW2, kOffW3, kOffW4};
-  const int64_t din[4] = {kIn, kHid, kHid, kHid}, dout[4] = {kHid, kHid, kHid, kOut};
-  TransposeJob jobs[4];
-  for (int l = 0; l < 4; ++l) jobs[l] = TransposeJob{n->wb + offW[l], din[l], dout[l], n->wbt + offW[l]};
-  hipError_t e = launch_transpose_bf16(jobs, 4, n->c->stream);
+  const int64_t offW[3] = {kOffW1, kOffW2, kOffW3}, din[3] = {kIn, kHid, kHid};
+  TransposeJob jobs[3];
+  for (int l = 0; l < 3; ++l) jobs[l] = TransposeJob{n->wb + offW[l], din[l], kHid, n->wbt + offW[l]};
+  hipError_t e = launch_transpose_bf16(jobs, 3, n->c->stream);
   if (e != hipSuccess) return hip_fail(n->c, e, "weight transpose launch");
   return RLF_OK;
 }
 
-// Forward of rows [0, nb) of x into the layer buffers; y_out receives the outputs.
-// A training step's forward also writes the second layer's transposed
-// activations if its weight gradients use them (ht1).
-int forward_chunk(rlf_mlp *n, const __bf16 *x, int nb, float *y_out, __bf16 *ht1 = nullptr) {
+// Forward of rows [0, nb) of x through the hidden layers' buffers.  A training
+// step's forward also writes the second layer's transposed activations if its
+// weight gradients use them (ht1).
+int forward_hidden(rlf_mlp *n, const __bf16 *x, int nb, __bf16 *ht1) {
   rlf_ctx *c = n->c;
   const __bf16 *hin = x;
   int kin = kIn;
@@ -208,9 +208,19 @@ int forward_chunk(rlf_mlp *n, const __bf16 *x, int nb, float *y_out, __bf16 *ht1
     hin = n->h[l];
     kin = kHid;
   }
-  hipError_t e = launch_out_forward(hin, n->wb + kOffW4, n->w + kOffB4, nb, y_out, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "output layer launch");
   return RLF_OK;
+}
+
+int forward_output(rlf_mlp *n, int nb, float *y_out) {
+  hipError_t e = launch_out_forward(n->h[2], n->wb + kOffW4, n->w + kOffB4, nb, y_out, n->c->stream);
+  if (e != hipSuccess) return hip_fail(n->c, e, "output layer launch");
+  return RLF_OK;
+}
+
+// Forward of rows [0, nb) of x; y_out receives the outputs.
+int forward_chunk(rlf_mlp *n, const __bf16 *x, int nb, float *y_out) {
+  if (int e = forward_hidden(n, x, nb, nullptr)) return e;
+  return forward_output(n, nb, y_out);
 }
 
 }  // namespace
@@ -248,7 +258,7 @@ int rlf_mlp_create(rlf_ctx *c, int64_t max_batch, rlf_mlp **out) {
     if ((rc = dalloc(c, &n->ws, kWsFloats))) break;
     if ((rc = dalloc(c, &n->wbt, kParams))) break;
     if ((rc = dalloc(c, &n->xt, B * kIn))) break;
-    if ((rc = dalloc(c, &n->part, (kTileRows / 32) * kHid))) break;
+    if ((rc = dalloc(c, &n->part, kSlices * (3 * kHid + kHid * kOut + kOut)))) break;
     for (int k = 0; k < 2 && rc == RLF_OK; ++k) {
       if ((rc = dalloc(c, &n->dzb[k], B * kHid))) break;
       if ((rc = dalloc(c, &n->ht[k], B * kHid))) break;
@@ -485,26 +495,47 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   const __bf16 *xb = reinterpret_cast<const __bf16 *>(x);
   // the NT GEMM needs the batch dimension in multiples of 8 for the weight gradients
   const bool nt_rows = nb % 8 == 0, tiled = nb <= kTileRows;
-  if (int e = forward_chunk(n, xb, nb, n->y, nt_rows ? n->ht[1] : nullptr)) return e;
-  HIPCHK(c, launch_head(n->y, target, nb, n->dy, n->dyb, loss, c->stream));
-  // output layer: dW4 = h3^T dY, db4 = sum dY (together, in the parameters'
-  // order), dh3 = dY W4^T
-  static_assert(kOffB4 == kOffW4 + (int64_t)kHid * kOut, "b4 follows W4");
-  HIPCHK(c, launch_out_backward(n->h[2], n->dyb, n->dy, nb, n->wb + kOffW4, n->g + kOffW4, n->dh, n->ws, kWsFloats,
-                                c->stream));
+  if (int e = forward_hidden(n, xb, nb, nt_rows ? n->ht[1] : nullptr)) return e;
   const int64_t offW[3] = {kOffW1, kOffW2, kOffW3}, offB[3] = {kOffB1, kOffB2, kOffB3};
   int64_t per;
   int slices;
   colsum_slices(nb, kHid, kWsFloats, &per, &slices);
   const bool fused = tiled && per == 32;         // the tiles' column sums are the slices
   int cur = 0;
-  HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[2], nb, kHid, n->dzb[0], n->g + offB[2], n->ws, kWsFloats, c->stream));
+  // output layer: dW4 = h3^T dY, db4 = sum dY (together, in the parameters'
+  // order), dh3 = dY W4^T, and the last hidden layer's dZ
+  static_assert(kOffB4 == kOffW4 + (int64_t)kHid * kOut, "b4 follows W4");
+  float *part[3], *out_part = n->part + 3 * kSlices * kHid;
+  for (int l = 0; l < 3; ++l) part[l] = n->part + l * kSlices * kHid;
+  if (fused) {
+    HeadArgs ha{};
+    ha.h = n->h[2];
+    ha.w = n->wb + kOffW4;
+    ha.b = n->w + kOffB4;
+    ha.target = target;
+    ha.z = n->z[2];
+    ha.rows = nb;
+    ha.y = n->y;
+    ha.dz = n->dzb[0];
+    ha.dzt = nt_rows ? n->dzt[0] : nullptr;
+    ha.part = part[2];
+    ha.out_part = out_part;
+    HIPCHK(c, launch_head_slice(ha, c->stream));
+  } else {
+    if (int e = forward_output(n, nb, n->y)) return e;
+    HIPCHK(c, launch_head(n->y, target, nb, n->dy, n->dyb, loss, c->stream));
+    HIPCHK(c, launch_out_backward(n->h[2], n->dyb, n->dy, nb, n->wb + kOffW4, n->g + kOffW4, n->dh, n->ws, kWsFloats,
+                                  c->stream));
+    HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[2], nb, kHid, n->dzb[0], n->g + offB[2], n->ws, kWsFloats,
+                                      c->stream));
+  }
   if (nt_rows) {
     // dW = h^T dZ with both operands transposed to [features x rows]: what the
     // tile products do not write themselves, in one launch if that is all of it
     const TransposeJob jx{xb, nb, kIn, n->xt}, jh0{n->h[0], nb, kHid, n->ht[0]}, jh1{n->h[1], nb, kHid, n->ht[1]};
-    const TransposeJob jobs[3] = {{n->dzb[0], nb, kHid, n->dzt[0]}, fused ? jx : jh1, jh0};
-    HIPCHK(c, launch_transpose_bf16(jobs, fused ? 3 : tiled ? 1 : 2, c->stream));
+    const TransposeJob jdz{n->dzb[0], nb, kHid, n->dzt[0]};
+    const TransposeJob jobs[2] = {fused ? jx : jdz, fused ? jh0 : jh1};
+    HIPCHK(c, launch_transpose_bf16(jobs, fused || !tiled ? 2 : 1, c->stream));
   }
   for (int l = 2; l > 0; --l, cur ^= 1) {
     // dh = dZ W^T: rows of dZ and of W both run along the output index
@@ -531,9 +562,8 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
       dh.z = n->z[l - 1];
       dh.dz = dz;
       dh.dzt = nt_rows ? dzt : nullptr;
-      dh.part = n->part;
+      dh.part = part[l - 1];
       HIPCHK(c, launch_gemm_tile(dh, kTileBackward, nt_rows ? &dw : nullptr, c->stream));
-      HIPCHK(c, launch_colsum_join(n->part, slices, kHid, n->g + offB[l - 1], c->stream));
       continue;
     }
     if (tiled) {
@@ -557,9 +587,24 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   } else {
     if (int e = gemm(n, xb, 1, kIn, n->dzb[cur], kHid, 1, n->g + offW[0], kIn, kHid, nb)) return e;
   }
+  if (fused) {
+    JoinArgs ja{};
+    ja.slices = slices;
+    ja.out_part = out_part;
+    ja.gw = n->g + kOffW4;
+    for (int l = 0; l < 3; ++l) {
+      ja.part[l] = part[l];
+      ja.db[l] = n->g + offB[l];
+    }
+    ja.y = n->y;
+    ja.target = target;
+    ja.rows = nb;
+    ja.loss = loss;
+    HIPCHK(c, launch_join(ja, c->stream));
+  }
   n->step += 1;
-  HIPCHK(c, launch_adam(n->w, n->wb, n->g, n->m, n->v, kParams, lr, n->step, c->stream));
-  if (int e = update_wbt(n)) return e;
+  const AdamMats mats{{kOffW1, kOffW2, kOffW3}, {kIn, kHid, kHid}, {kHid, kHid, kHid}};
+  HIPCHK(c, launch_adam(n->w, n->wb, n->wbt, mats, n->g, n->m, n->v, kParams, lr, n->step, c->stream));
   return RLF_OK;
 }
 
