@@ -251,6 +251,24 @@ void *scratch_ptr(int device) {
 
 namespace rlf {
 
+int pinned_reserve(rlf_ctx *c, size_t bytes, char **p) {
+  if (bytes > kPinnedRing / 4) return fail(c, RLF_EINVAL, "pinned_reserve: size");
+  if (!c->pinned) {
+    void *ring = nullptr;
+    HIPCHK(c, hipHostMalloc(&ring, kPinnedRing, hipHostMallocDefault));
+    c->pinned = static_cast<char *>(ring);
+    c->pinned_off = 0;
+  }
+  size_t off = (c->pinned_off + 255) & ~(size_t)255;
+  if (off + bytes > kPinnedRing) {                    // wrap: every earlier copy must have run
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    off = 0;
+  }
+  *p = c->pinned + off;
+  c->pinned_off = off + bytes;
+  return RLF_OK;
+}
+
 int upload_async(rlf_ctx *c, void *dst, const void *src, size_t bytes) {
   if (bytes == 0) return RLF_OK;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -261,20 +279,46 @@ int upload_async(rlf_ctx *c, void *dst, const void *src, size_t bytes) {
     HIPCHK(c, hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
     return RLF_OK;
   }
-  if (!c->pinned) {
-    void *p = nullptr;
-    HIPCHK(c, hipHostMalloc(&p, kPinnedRing, hipHostMallocDefault));
-    c->pinned = static_cast<char *>(p);
-    c->pinned_off = 0;
-  }
-  size_t off = (c->pinned_off + 255) & ~(size_t)255;
-  if (off + bytes > kPinnedRing) {                    // wrap: every earlier copy must have run
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    off = 0;
-  }
-  std::memcpy(c->pinned + off, src, bytes);
-  HIPCHK(c, hipMemcpyAsync(dst, c->pinned + off, bytes, hipMemcpyHostToDevice, c->stream));
-  c->pinned_off = off + bytes;
+  char *p = nullptr;
+  if (int e = pinned_reserve(c, bytes, &p)) return e;
+  std::memcpy(p, src, bytes);
+  HIPCHK(c, hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, c->stream));
+  return RLF_OK;
+}
+
+int UploadBatch::flush() {
+  if (jobs_.n == 0) return RLF_OK;
+  const hipError_t e = launch_copy_jobs(jobs_, c_->stream);
+  jobs_.n = 0;
+  return e == hipSuccess ? RLF_OK : hip_fail(c_, e, "table upload launch");
+}
+
+int UploadBatch::copy(void *dst, const void *src, size_t bytes) {
+  if (bytes == 0) return RLF_OK;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIPCHK(c_, hipStreamIsCapturing(c_->stream, &cs));
+  if (cs != hipStreamCaptureStatusNone) return fail(c_, RLF_EINVAL, "table upload while the stream is being captured");
+  // staged tables that no launch reads yet must not be there when the ring wraps
+  const bool wraps = ((c_->pinned_off + 255) & ~(size_t)255) + bytes > kPinnedRing;
+  if (jobs_.n == CopyJobs::kMax || bytes > kMaxTable || wraps)
+    if (int e = flush()) return e;
+  if (bytes > kMaxTable || bytes % 4) return upload_async(c_, dst, src, bytes);
+  char *p = nullptr;
+  if (int e = pinned_reserve(c_, bytes, &p)) return e;
+  std::memcpy(p, src, bytes);
+  jobs_.job[jobs_.n].dst = dst;
+  jobs_.job[jobs_.n].src = p;
+  jobs_.job[jobs_.n++].bytes = bytes;
+  return RLF_OK;
+}
+
+int UploadBatch::clear(void *dst, size_t bytes) {
+  if (bytes == 0) return RLF_OK;
+  if (jobs_.n == CopyJobs::kMax)
+    if (int e = flush()) return e;
+  jobs_.job[jobs_.n].dst = dst;
+  jobs_.job[jobs_.n].src = nullptr;
+  jobs_.job[jobs_.n++].bytes = bytes;
   return RLF_OK;
 }
 
@@ -284,19 +328,25 @@ namespace {
 
 // Source tables of a catalogue, uploaded behind the work already queued on
 // the stream (kernels still reading the old tables run first).
-int upload_sources(rlf_ctx *c, const rlf_catalog *k, SrcModel *dst, SrcMixed *dst32) {
+int upload_sources(rlf_ctx *c, const rlf_catalog *k, SrcModel *dst, SrcMixed *dst32, UploadBatch *up = nullptr) {
   std::vector<SrcModel> h((size_t)k->n_src);
   std::vector<SrcMixed> h32((size_t)k->n_src);
   for (int64_t s = 0; s < k->n_src; ++s) {
     h[(size_t)s] = pack_source(c->p, k, s);
     h32[(size_t)s] = to_mixed(h[(size_t)s]);
   }
+  if (up) {
+    if (int e = up->copy(dst, h.data(), sizeof(SrcModel) * h.size())) return e;
+    return up->copy(dst32, h32.data(), sizeof(SrcMixed) * h32.size());
+  }
   if (int e = upload_async(c, dst, h.data(), sizeof(SrcModel) * h.size())) return e;
   return upload_async(c, dst32, h32.data(), sizeof(SrcMixed) * h32.size());
 }
 
 // Device source table for rlf_model_vis, reused while the catalogue content is unchanged.
-int model_table(rlf_ctx *c, const rlf_catalog *k, const SrcModel **out, const SrcMixed **out32) {
+// With `up`, the upload joins that batch.
+int model_table(rlf_ctx *c, const rlf_catalog *k, const SrcModel **out, const SrcMixed **out32,
+                UploadBatch *up = nullptr) {
   std::vector<double> key = cat_key(k);
   ++c->tick;
   for (auto &sl : c->slot)
@@ -308,6 +358,8 @@ int model_table(rlf_ctx *c, const rlf_catalog *k, const SrcModel **out, const Sr
     }
   auto &sl = c->slot[0].used <= c->slot[1].used ? c->slot[0] : c->slot[1];
   if (sl.cap < k->n_src) {
+    if (up)
+      if (int e = up->flush()) return e;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     dfree(sl.d);
     dfree(sl.d32);
@@ -317,7 +369,7 @@ int model_table(rlf_ctx *c, const rlf_catalog *k, const SrcModel **out, const Sr
     sl.cap = k->n_src;
   }
   sl.key.clear();
-  if (int e = upload_sources(c, k, sl.d, sl.d32)) return e;
+  if (int e = upload_sources(c, k, sl.d, sl.d32, up)) return e;
   sl.key.swap(key);
   sl.used = c->tick;
   *out = sl.d;
@@ -886,7 +938,7 @@ int create_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const 
 // (same observation): new geometry, weights, lane order and model table;
 // the dense arrays are reused while they are large enough, the uv-sorted
 // layout (owned or borrowed) is kept, and positions go back to fixed.
-int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_facets *f) {
+int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_facets *f, UploadBatch &up) {
   if (!f || f->ctx != c) return fail(c, RLF_EINVAL, "facets is NULL or from another context");
   if (int e = check_obs(c, obs)) return e;
   if (int e = check_cat(c, cat, true)) return e;
@@ -897,6 +949,7 @@ int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
   int64_t total = 0;
   if (int e = facet_geometry(c, obs, cat, f->mx, theta, geom, total)) return e;
   if (total > f->dense_cap) {
+    if (int e = up.flush()) return e;
     HIPCHK(c, hipStreamSynchronize(c->stream));        // queued kernels may still use the arrays
     dfree(f->acc.cell);
     dfree(f->cells.ix);
@@ -929,15 +982,16 @@ int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
   }
   const std::vector<double> logw = facet_logw(c, cat);
   const std::vector<int32_t> order = lane_order(theta);
-  // everything below is queued behind the work already on the stream
-  if (int e = upload_async(c, f->d_geom, geom.data(), sizeof(SrcGeom) * geom.size())) return e;
-  if (int e = upload_async(c, f->d_order, order.data(), sizeof(int32_t) * order.size())) return e;
-  if (int e = upload_async(c, f->d_logw, logw.data(), sizeof(double) * logw.size())) return e;
-  HIPCHK(c, hipMemsetAsync(f->acc.cell, 0, sizeof(double4) * (size_t)total, c->stream));
-  HIPCHK(c, hipMemsetAsync(f->cells.offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1), c->stream));
-  HIPCHK(c, hipMemsetAsync(f->cells.fold_offsets, 0, sizeof(int64_t) * (size_t)(f->n_src + 1), c->stream));
-  HIPCHK(c, hipMemsetAsync(f->d_redo, 0, sizeof(int32_t) * (size_t)f->n_src, c->stream));
-  if (int e = upload_sources(c, cat, f->d_src, f->d_src32)) return e;
+  // everything below is queued behind the work already on the stream when
+  // the batch is flushed, before the object's next use
+  if (int e = up.copy(f->d_geom, geom.data(), sizeof(SrcGeom) * geom.size())) return e;
+  if (int e = up.copy(f->d_order, order.data(), sizeof(int32_t) * order.size())) return e;
+  if (int e = up.copy(f->d_logw, logw.data(), sizeof(double) * logw.size())) return e;
+  if (int e = up.clear(f->acc.cell, sizeof(double4) * (size_t)total)) return e;
+  if (int e = up.clear(f->cells.offsets, sizeof(int64_t) * (size_t)(f->n_src + 1))) return e;
+  if (int e = up.clear(f->cells.fold_offsets, sizeof(int64_t) * (size_t)(f->n_src + 1))) return e;
+  if (int e = up.clear(f->d_redo, sizeof(int32_t) * (size_t)f->n_src)) return e;
+  if (int e = upload_sources(c, cat, f->d_src, f->d_src32, &up)) return e;
   f->model_key = cat_key(cat);
   f->alpha.assign(cat->alpha_arcsec, cat->alpha_arcsec + cat->n_src);
   f->theta.swap(theta);
@@ -1043,7 +1097,7 @@ int sorted_residual(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *sky, cons
 // kept in the sorted layout of f (and in rs for the FP64 form); the two
 // model tables are uploaded into the context's two model slots.
 int prepare_update(rlf_ctx *c, const rlf_catalog *old_m, const rlf_catalog *new_m, const rlf_facets *f,
-                   double2 *rs, UpdateArgs &u) {
+                   double2 *rs, UpdateArgs &u, UploadBatch &up) {
   if (int e = check_cat(c, old_m, false)) return e;
   if (int e = check_cat(c, new_m, false)) return e;
   if (!f->mixed && !rs) return fail(c, RLF_EINVAL, "FP64 form needs the unweighted residual buffer");
@@ -1051,8 +1105,8 @@ int prepare_update(rlf_ctx *c, const rlf_catalog *old_m, const rlf_catalog *new_
   u = UpdateArgs{};
   // the second lookup replaces the least recently used slot, never the one
   // just returned
-  if (int e = model_table(c, old_m, &u.old64, &u.old32)) return e;
-  if (int e = model_table(c, new_m, &u.new64, &u.new32)) return e;
+  if (int e = model_table(c, old_m, &u.old64, &u.old32, &up)) return e;
+  if (int e = model_table(c, new_m, &u.new64, &u.new32, &up)) return e;
   if (u.old64 == u.new64 && cat_key(old_m) != cat_key(new_m))
     return fail(c, RLF_EINVAL, "model tables of the update share a slot");
   u.sv = f->sv;

@@ -356,6 +356,20 @@ struct JoinArgs {
   double *loss;
 };
 
+// Copies made by one kernel between memory the device can address (pinned
+// host memory included); src null: the destination is cleared.  Bytes are
+// multiples of 4; no job's source is another's destination.
+struct CopyJobs {
+  static constexpr int kMax = 16;
+  int n;
+  struct {
+    void *dst;
+    const void *src;
+    size_t bytes;
+  } job[kMax];
+};
+hipError_t launch_copy_jobs(const CopyJobs &j, hipStream_t st);
+
 struct FeatureArgs {
   int32_t s0;                // first source of the rows written
   int32_t n_src;             // rows written (sources s0 .. s0 + n_src - 1)

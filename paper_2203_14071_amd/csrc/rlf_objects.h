@@ -129,11 +129,34 @@ int fit_args(rlf_ctx *c, const rlf_facets *f, FitArgs &fa);
 // reused only after a synchronisation of the stream (every copy issued from
 // it has then run).  Refused while the stream is being captured.
 int upload_async(rlf_ctx *c, void *dst, const void *src, size_t bytes);
+// Room for `bytes` in the ring (at most a quarter of it), for the host until
+// the ring wraps; waits for the stream when it does.
+int pinned_reserve(rlf_ctx *c, size_t bytes, char **p);
+
+// Small uploads and clears on the context's stream, gathered into one launch
+// by flush() (the destructor's at the latest: tables already noted as
+// uploaded must be).  Tables above kMaxTable go by upload_async at once.
+// Not under capture.
+class UploadBatch {
+ public:
+  explicit UploadBatch(rlf_ctx *c) : c_(c) {}
+  ~UploadBatch() { (void)flush(); }
+  UploadBatch(const UploadBatch &) = delete;
+  UploadBatch &operator=(const UploadBatch &) = delete;
+  int copy(void *dst, const void *src, size_t bytes);
+  int clear(void *dst, size_t bytes);
+  int flush();
+  static constexpr size_t kMaxTable = 64 << 10;
+
+ private:
+  rlf_ctx *c_;
+  CopyJobs jobs_{};
+};
 
 // The same facet object for another catalogue of as many sources (same
 // observation); the uv-sorted layout is kept, the dense arrays reused while
 // large enough.
-int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_facets *f);
+int retarget_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_facets *f, UploadBatch &up);
 
 // Extraction into f: with `vis`, first the gather into f's sorted layout
 // (subtract = 1: minus f's own catalogue models); with vis NULL the sorted
@@ -149,7 +172,7 @@ int extract_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const
 // or, pending, by the next extraction (extract_facets(..., upd)).
 int sorted_residual(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *sky, const rlf_facets *f, double2 *rs);
 int prepare_update(rlf_ctx *c, const rlf_catalog *old_m, const rlf_catalog *new_m, const rlf_facets *f,
-                   double2 *rs, UpdateArgs &u);
+                   double2 *rs, UpdateArgs &u, UploadBatch &up);
 int update_sorted_residual(rlf_ctx *c, const UpdateArgs &u, int mixed);
 
 }  // namespace rlf
