@@ -840,8 +840,7 @@ int create_facets(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, const 
   } else {
     // largest |u|, |v| (metres) bound every cell index
     HIPCHK(c, hipMemsetAsync(c->d_absmax, 0, 2 * sizeof(double), c->stream));
-    HIPCHK(c, launch_absmax(obs->u_m, obs->n_rows, c->d_absmax, 0, c->stream));
-    HIPCHK(c, launch_absmax(obs->v_m, obs->n_rows, c->d_absmax, 1, c->stream));
+    HIPCHK(c, launch_absmax(obs->u_m, obs->v_m, obs->n_rows, c->d_absmax, c->stream));
     HIPCHK(c, hipMemcpyAsync(mx, c->d_absmax, sizeof(mx), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (!is_fin(mx[0]) || !is_fin(mx[1])) return fail(c, RLF_EINVAL, "obs: non-finite u or v");

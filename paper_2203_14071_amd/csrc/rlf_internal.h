@@ -399,7 +399,7 @@ hipError_t launch_fit_mixed(const FitArgs &a, hipStream_t st);
 hipError_t launch_fit_queue(const FitArgs &a, const QueueArgs &q, int mixed, int blocks, hipStream_t st);
 int fit_queue_blocks_per_cu(int mixed, int num_r);
 hipError_t launch_estimate(const EstimateArgs &a, hipStream_t st);
-hipError_t launch_absmax(const double *x, int64_t n, double *out2, int slot, hipStream_t st);
+hipError_t launch_absmax(const double *x, const double *y, int64_t n, double *out2, hipStream_t st);
 hipError_t launch_refine_eval(const FitArgs &a, const RefineArgs &r, int mixed, hipStream_t st);
 hipError_t launch_pos_prep(const PosPrepArgs &a, int mixed, hipStream_t st);
 hipError_t launch_lattice_windows(const FitArgs &a, double log_frac, int32_t *win, hipStream_t st);
