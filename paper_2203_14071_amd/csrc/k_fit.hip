@@ -451,54 +451,95 @@ __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixe
   if (threadIdx.x < 64 && j < a.n_valid) a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
 
-// Windowed launch: blockIdx.y = source, one thread per position of the
-// source's inclusive box (i1lo, i1hi, i2lo, i2hi) in row-major order, then,
-// with a check stride S, per lattice point c + S q (both axes, |q| <= c / S)
-// outside the box; invalid points (|e| >= 1) are skipped.  No other point is
-// evaluated (the estimator reads no other).  Blocks past a source's positions
-// leave at once, so the grid is sized for the largest possible box.  Sources
-// largest facet first, as in k_fit.
+// The positions of a windowed launch of source s: its inclusive box (i1lo,
+// i1hi, i2lo, i2hi) in row-major order, then, with a check stride S, the
+// lattice points c + S q (both axes, |q| <= c / S) outside the box.  No other
+// point is evaluated (the estimator reads no other).
+struct Window {
+  int4 b;                                     // the box's part on the grid: at most n_e^2 positions
+  int w2, span, nl, ctr;
+  bool by_valid;
+  __device__ __forceinline__ Window(const FitArgs &a, int s) {
+    // lattice pass 1: the lattice alone (an empty box); pass 2: the lattice
+    // values are already in the surface, only the box is evaluated
+    b = a.lattice_pass == 1 ? make_int4(1, 0, 1, 0) : reinterpret_cast<const int4 *>(a.window)[s];
+    b.x = max(b.x, 0);
+    b.y = min(b.y, a.n_e - 1);
+    b.z = max(b.z, 0);
+    b.w = min(b.w, a.n_e - 1);
+    w2 = b.w >= b.z ? b.w - b.z + 1 : 1;
+    const int area = (b.y >= b.x && b.w >= b.z) ? (b.y - b.x + 1) * w2 : 0;
+    ctr = (a.n_e - 1) / 2;
+    const int h = a.check_stride > 0 ? ctr / a.check_stride : 0;
+    nl = (a.check_stride > 0 && a.lattice_pass != 2) ? 2 * h + 1 : 0;
+    // a box with at least as many positions as the grid has valid points is
+    // walked over the valid points instead (no idle lanes on |e| >= 1)
+    by_valid = area >= a.n_valid;
+    span = by_valid ? a.n_valid : area;
+  }
+  __device__ __forceinline__ int positions() const { return span + nl * nl; }
+  // The valid point of position t, -1 for none: |e| >= 1, evaluated with the
+  // box, or past the source's positions.
+  __device__ __forceinline__ int point(const FitArgs &a, int t) const {
+    if (t >= positions()) return -1;
+    int i1, i2;
+    if (by_valid && t < span) {
+      const int f = a.epts[t];
+      i1 = f / a.n_e;
+      i2 = f - i1 * a.n_e;
+      return i1 >= b.x && i1 <= b.y && i2 >= b.z && i2 <= b.w ? t : -1;
+    }
+    if (t < span) {
+      i1 = b.x + t / w2;
+      i2 = b.z + t % w2;
+    } else {
+      const int u = t - span, h = (nl - 1) / 2;
+      i1 = ctr + a.check_stride * (u / nl - h);
+      i2 = ctr + a.check_stride * (u % nl - h);
+      if (i1 >= b.x && i1 <= b.y && i2 >= b.z && i2 <= b.w) return -1;
+    }
+    if (i1 < 0 || i2 < 0 || i1 >= a.n_e || i2 >= a.n_e) return -1;
+    return a.valid_index[i1 * a.n_e + i2];
+  }
+};
+
+// Windowed launch: blockIdx.y = source, largest facet first as in k_fit, one
+// thread per position.  Blocks past a source's positions, and those of
+// sources that k_window_knots takes, leave at once: the grid is sized for the
+// largest possible box.
 template <int R, bool kExact, bool kMixed>
 __global__ __launch_bounds__(256) void k_fit_window(FitArgs a, int num_r) {
   const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
-  // lattice pass 1: the lattice alone (an empty box); pass 2: the lattice
-  // values are already in the surface, only the box is evaluated
-  int4 b = a.lattice_pass == 1 ? make_int4(1, 0, 1, 0) : reinterpret_cast<const int4 *>(a.window)[s];
-  b.x = max(b.x, 0);                          // the box's part on the grid: at most n_e^2 positions
-  b.y = min(b.y, a.n_e - 1);
-  b.z = max(b.z, 0);
-  b.w = min(b.w, a.n_e - 1);
-  const int w2 = b.w >= b.z ? b.w - b.z + 1 : 1;
-  const int area = (b.y >= b.x && b.w >= b.z) ? (b.y - b.x + 1) * w2 : 0;
-  const int ctr = (a.n_e - 1) / 2;
-  const int h = a.check_stride > 0 ? ctr / a.check_stride : 0;
-  const int nl = (a.check_stride > 0 && a.lattice_pass != 2) ? 2 * h + 1 : 0;
-  // a box with at least as many positions as the grid has valid points is
-  // walked over the valid points instead (no idle lanes on |e| >= 1)
-  const bool by_valid = area >= a.n_valid;
-  const int span = by_valid ? a.n_valid : area;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= span + nl * nl) return;
-  int i1, i2;
-  if (by_valid && t < span) {
-    const int f = a.epts[t];
-    i1 = f / a.n_e;
-    i2 = f - i1 * a.n_e;
-    if (i1 >= b.x && i1 <= b.y && i2 >= b.z && i2 <= b.w) eval_point<R, kExact, kMixed>(a, num_r, s, t);
-    return;
-  }
-  if (t < span) {
-    i1 = b.x + t / w2;
-    i2 = b.z + t % w2;
-  } else {
-    const int u = t - span;
-    i1 = ctr + a.check_stride * (u / nl - h);
-    i2 = ctr + a.check_stride * (u % nl - h);
-    if (i1 >= b.x && i1 <= b.y && i2 >= b.z && i2 <= b.w) return;   // evaluated with the box
-  }
-  if (i1 < 0 || i2 < 0 || i1 >= a.n_e || i2 >= a.n_e) return;
-  const int j = a.valid_index[i1 * a.n_e + i2];
+  const Window w(a, s);
+  if (w.positions() <= a.knot_positions) return;
+  const int j = w.point(a, blockIdx.x * blockDim.x + threadIdx.x);
   if (j >= 0) eval_point<R, kExact, kMixed>(a, num_r, s, j);
+}
+
+// The same for the sources of at most a.knot_positions positions, 64 per
+// block, the knots shared by the block's four waves.  A narrowed fit is a few
+// waves per source and the walk over the largest facet's records (4.2 us per
+// 10 records with all 20 knots in a lane, 0.35 ms at 786 cells) outlasts all
+// others; shared knots make it four times shorter.  300 sources, us, k_fit_window |
+// k_window_knots: lattice of every fourth point and its boxes 709 | 409, boxes
+// of 9 x 9 points 269 | 122; 1000 sources 1,180 | 1,111 and 363 | 195.
+template <bool kMixed>
+__global__ __launch_bounds__((KnotSplit<kMixed, 0>::kThreads), (KnotSplit<kMixed, 0>::kWavesPerSimd)) void k_window_knots(
+    FitArgs a, int num_r) {
+  __shared__ double sh[block_doubles<kMixed, 0>()];
+  const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
+  const Window w(a, s);
+  if (w.positions() > a.knot_positions) return;
+  const int j = w.point(a, blockIdx.x * 64 + (int)(threadIdx.x & 63));
+  if (!__any(j >= 0)) return;                  // the same in every wave
+  double L = NAN;
+  if (a.offsets[s + 1] != a.offsets[s]) {      // uniform
+    // a lane without a point evaluates the centre and drops it
+    const int f = j >= 0 ? a.epts[j] : w.ctr * a.n_e + w.ctr;
+    const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
+    L = loglike_block<kMixed, 0>(a, num_r, s, (double)(i1 - w.ctr) * a.e_step, (double)(i2 - w.ctr) * a.e_step, sh);
+  }
+  if (threadIdx.x < 64 && j >= 0) a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
 
 // Persistent work queue: a grid sized to the resident capacity; each wave
@@ -601,6 +642,31 @@ hipError_t launch_knots(const FitArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Narrowed fits: k_window_knots takes the sources of at most this many
+// positions.  Where a launch fills the card k_fit_window is the better one
+// (its lanes form the quadratic form once instead of four times): 1000
+// sources of 31 x 31 points 844 us, in k_window_knots 879; 300 of about 60 x
+// 60 1,198 and 1,323, but 300 of 31 x 31 410 and 288, and 70 small facets'
+// whole grids 351 and 325.  The boxes are on the device, so a launch whose
+// boxes could fill the card is split by their size, two kernels each leaving
+// the other's sources at once, up to the number of sources where the idle
+// blocks cost more than that gains (2,000 sources of 3 x 3 points 479 us,
+// split 510).  The lattice and the boxes it leads to are small: one kernel
+// (1,000 sources 1,180 and 1,111 us, 2,000 sources 2,370 and 2,836).
+constexpr int kLatticeSources = 1000, kKnotWindows = 80, kSplitWindows = 1500, kKnotWork = 400000;
+
+int knot_positions(const FitArgs &a, int positions) {
+  if (a.n_src <= (a.lattice_pass ? kLatticeSources : kKnotWindows)) return positions;
+  return !a.lattice_pass && a.n_src <= kSplitWindows ? std::min(positions, kKnotWork / a.n_src) : 0;
+}
+
+// Blocks per source for up to n positions, an odd number: blocks go to the
+// eight XCDs in turn by linear index, and with a multiple of eight the first
+// blocks of all sources, often the only ones with work, sit on one of them
+// (200 sources of 3 x 3 points: 342 us with 32 blocks, 119 with 33; the lattice fit of 2,000 sources
+// with 26 blocks 2,903, with 27 2,370).
+unsigned odd_blocks(int n, int per) { return (unsigned)((n + per - 1) / per) | 1u; }
+
 template <bool kMixed>
 hipError_t launch(const FitArgs &a, hipStream_t st) {
   if (a.n_pos) {
@@ -614,7 +680,12 @@ hipError_t launch(const FitArgs &a, hipStream_t st) {
     const int h = a.check_stride > 0 ? ((a.n_e - 1) / 2) / a.check_stride : 0;
     const int lattice = (a.check_stride > 0 && a.lattice_pass != 2) ? (2 * h + 1) * (2 * h + 1) : 0;
     const int positions = (a.lattice_pass == 1 ? 0 : a.n_e * a.n_e) + lattice;
-    RLF_FIT_DISPATCH(k_fit_window, dim3((positions + 255) / 256, a.n_src), a);
+    FitArgs w = a;
+    w.knot_positions = knot_positions(a, positions);
+    if (w.knot_positions < positions) RLF_FIT_DISPATCH(k_fit_window, dim3(odd_blocks(positions, 256), a.n_src), w);
+    if (w.knot_positions > 0)
+      hipLaunchKernelGGL(k_window_knots<kMixed>, dim3(odd_blocks(std::min(positions, w.knot_positions), 64), a.n_src),
+                         dim3(KnotSplit<kMixed, 0>::kThreads), 0, st, w, a.num_r);
   } else if (a.redo || a.n_src <= kKnotSources) {
     return launch_knots<kMixed, 0>(a, st);
   } else {
@@ -650,7 +721,7 @@ namespace {
 
 template <bool kMixed, int NP>
 hipError_t refine_eval(const FitArgs &a, const RefineArgs &r, hipStream_t st) {
-  hipLaunchKernelGGL((k_refine_eval<kMixed, NP>), dim3((r.max_side * r.max_side + 63) / 64, a.n_src), dim3(KnotSplit<kMixed, NP>::kThreads), 0, st, a, r,
+  hipLaunchKernelGGL((k_refine_eval<kMixed, NP>), dim3(odd_blocks(r.max_side * r.max_side, 64), a.n_src), dim3(KnotSplit<kMixed, NP>::kThreads), 0, st, a, r,
                      a.num_r);
   return hipGetLastError();
 }

@@ -192,6 +192,7 @@ struct FitArgs {
   // lattice-seeded window: 1 = evaluate only the check_stride lattice (window
   // ignored); 2 = the lattice values are already in lsurf (box only)
   int32_t lattice_pass;
+  int32_t knot_positions;    // windowed launches: sources of at most this many positions share their knots (launcher)
   // sources by increasing facet size (null: catalogue order); the full-grid
   // launch takes them from the largest, so the longest blocks start first
   const int32_t *size_order;
