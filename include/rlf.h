@@ -353,9 +353,10 @@ int rlf_fit_sequential(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat,
  * this catalogue's sky model (as rlf_extract_facets with residual = NULL),
  * extraction, compaction, the likelihood grid and the estimate, captured
  * once into a HIP graph and replayed by rlf_pass_launch on the context's
- * stream.  The likelihood runs as one persistent work-queue launch: sources
- * in decreasing order of facet cell count, each work item covering tile*64
- * grid points of one source.  The tile for each facet-size bucket (cells
+ * stream.  The likelihood runs as the grid launch of rlf_fit_sources or as
+ * one persistent work-queue launch, whichever is faster on these facets (the
+ * results are the same): sources in decreasing order of facet cell count,
+ * each work item covering tile*64 grid points of one source.  The tile for each facet-size bucket (cells
  * < 256, < 1024, < 4096, >= 4096) is autotuned at creation by timing the
  * candidates 1, 2, 4, 8 on the pass's own facets, unless `tune_path` (a text
  * file, may be NULL) already holds a choice for this precision and knot
