@@ -52,12 +52,12 @@ MODEL_FLOP_PAIR = 19
 # bracket) at this workload, from rocprofv3 FETCH_SIZE and WRITE_SIZE (each
 # scaled by a plain copy's reading), for the kernels as they are now; None
 # where not measured.  profiles/step_kernels_ska_mid_1k_{fp64,mixed}.md:
-#   extraction (k_extract): fetch 1996.7 / 1189.4 MB, write 1096.5 / 983.3 MB
-#   likelihood (k_fit + k_estimate): fetch 155.4 + 150.2 / 79.4 + 146.6 MB,
-#     write 51.3 + 0.3 / 51.3 + 0.8 MB
-#   sky model (k_model): fetch 372.7 / 298.7 MB, write 148.3 / 74.1 MB
-TRAFFIC_BYTES = {"fp64": {"extract": 3093.2e6, "fit": 357.2e6, "model": 521.0e6},
-                 "mixed": {"extract": 2172.7e6, "fit": 278.1e6, "model": 372.8e6}}
+#   extraction (k_extract): fetch 1863.2 / 1188.9 MB, write 1096.5 / 983.3 MB
+#   likelihood (k_fit + k_estimate): fetch 89.8 + 51.9 / 79.5 + 79.2 MB,
+#     write 51.3 + 0.3 / 51.3 + 0.7 MB
+#   sky model (k_model): fetch 373.1 / 298.7 MB, write 148.3 / 74.1 MB
+TRAFFIC_BYTES = {"fp64": {"extract": 2959.7e6, "fit": 193.3e6, "model": 521.4e6},
+                 "mixed": {"extract": 2172.2e6, "fit": 210.7e6, "model": 372.8e6}}
 # VALU roofline in lane-slots: 256 CUs x 64 lanes x 2.4 GHz = 3.93e13 lane-slots/s.
 # Work per unit = the method's necessary operations in each form (not a
 # compiled count), priced with gfx950's measured rates (the VALU probe,
@@ -80,9 +80,9 @@ SLOT_ITEMS = {
         "extract": {"phase 3 FMA": 3, "reduction to one turn": 2, "sin + cos": 8,
                     "cell index 2 mul + 2 rint + key": 5, "cell test": 1, "shape form 3 FMA": 3,
                     "rsqrt": 4, "cube 2": 2, "rotation + own model + accumulate 5 FMA": 5, "weight sum": 1},
-        # per (cell, e point, knot)
+        # per (record, e point, knot), a record being a cell or a cell and its mirror image
         "fit": {"profile argument": 1, "rsqrt": 4, "cube 2": 2, "D and M 2 FMA": 2,
-                "quadratic form 6 per (cell, e point) over 20 knots": 0.3},
+                "quadratic form 6 per (record, e point) over 20 knots": 0.3},
     },
     "mixed": {
         "model": {"phase 3 FMA (FP64)": 3, "fractional turn": 1, "cvt": 1, "sin + cos": 2,
@@ -103,10 +103,10 @@ SLOTS = {f: {k: round(sum(v.values()), 3) for k, v in d.items()} for f, d in SLO
 # rate: slots = VALU instructions with each v_rsq_f64 counted 4, per CU per
 # cycle at that clock.  The VALU probe (probe/valu_probe.hip, run by the
 # benchmark) measures what instruction streams of each kind reach.
-VALU_WORK = {"fp64": {"extract": (5.821e9, 1.48e8, 2.268e9), "fit": (5.193e9, 5.90e8, 2.322e9),
-                      "model": (4.091e9, 1.45e8, 2.057e9)},
-             "mixed": {"extract": (4.745e9, 0.0, 2.330e9), "fit": (4.267e9, 4.16e6, 2.350e9),
-                       "model": (2.321e9, 0.0, 2.245e9)}}
+VALU_WORK = {"fp64": {"extract": (5.805e9, 1.48e8, 2.293e9), "fit": (3.065e9, 3.37e8, 2.331e9),
+                      "model": (4.062e9, 1.45e8, 2.090e9)},
+             "mixed": {"extract": (4.745e9, 0.0, 2.335e9), "fit": (4.267e9, 4.16e6, 2.348e9),
+                       "model": (2.321e9, 0.0, 2.255e9)}}
 
 
 def log(*a):
@@ -235,13 +235,13 @@ def valu_probe(iters=8192, blocks=2048):
 # Kernel-mix probes (probe/valu_probe.hip): the kernels' own inner loops on
 # cache-resident synthetic data; name, the kernel roofline they bound
 # (form, stage), items per pass (the field's 1000 sources; its mean of 296
-# cells per facet), passes.  The grid is 32 times what the chip holds at
+# cells per facet, 168 of the FP64 form's records), passes.  The grid is 32 times what the chip holds at
 # once: a grid of one round (2048 blocks) measured 4-25 % lower rates (its
 # blocks do not spread evenly over the CUs), grids of 8 and 32 rounds agree
 # within 2 %.
 MIX_PROBES = [("sky-model term, FP64 (sum_f64)", ("fp64", "model"), 1000, 1),
               ("sky-model term, mixed (sum_mixed)", ("mixed", "model"), 1000, 1),
-              ("likelihood cell sums, FP64, 20 knots (cell_sums_f64)", ("fp64", "fit"), 296, 1),
+              ("likelihood cell sums, FP64, 20 knots (cell_sums_f64)", ("fp64", "fit"), 168, 1),
               ("likelihood cell sums, mixed, 2 x 10 knots (cell_sums_f32)", ("mixed", "fit"), 296, 1)]
 
 
@@ -291,6 +291,16 @@ def attach_mix_ceilings(res, rows):
     if pf:
         attach(pf["precision"], pf["kernel_rooflines"])
         pf["roofline"] = dict(pf["kernel_rooflines"][pf["roofline"]["stage"]])
+
+
+def _folded_records(fc):
+    """Likelihood records of the FP64 form: per source, the cells with each
+    one's mirror image (-ix, -iy) counted once."""
+    ix, iy = np.asarray(fc["ix"], dtype=np.int64), np.asarray(fc["iy"], dtype=np.int64)
+    src = np.repeat(np.arange(len(fc["offsets"]) - 1), np.diff(fc["offsets"]))
+    flip = (iy < 0) | ((iy == 0) & (ix < 0))
+    ix, iy = np.where(flip, -ix, ix), np.where(flip, -iy, iy)
+    return int(len(np.unique(src * (1 << 32) + iy * (1 << 16) + (ix + (1 << 15)))))
 
 
 def mlp_flop_per_row(train=True):
@@ -720,7 +730,7 @@ def run_surrogate(steps, n_train, epochs, nsigmas, populations, check_stride, fu
         net.free()
         torch.cuda.empty_cache()
 
-    # the captured batched pass (residual + extraction + queue likelihood + estimate)
+    # the captured batched pass (residual + extraction + likelihood + estimate)
     out_p = outs()
     ps = ctx.pass_create(obs, catc, f, out_p)
     tiles, tuned = ps.tiles()
@@ -915,17 +925,21 @@ def run_form(precision, steps, warmup, seq_chunks=(), pos_sigmas=(), pos_sides=(
     peak = FP32_PEAK_TFLOPS if mixed else FP64_PEAK_TFLOPS
     pairs = float(n_vis) * n
 
-    fit_units = float(np.sum(cells)) * n_valid * p.num_r
+    # what the likelihood has to evaluate: the FP64 form's records, a cell and
+    # its mirror image in one (the profile is even, so both share their rsqrt);
+    # the mixed form's cells
+    records = int(np.sum(cells)) if mixed else _folded_records(fc)
+    fit_units = float(records) * n_valid * p.num_r
     units = {"extract": pairs, "fit": fit_units, "model": pairs}
     stage_idx = {"model": 0, "extract": 1, "fit": 2}
     names = {"extract": "facet extraction (k_extract; the stage also runs the sorted-order gather and the "
                         "compaction, < 2 % of it)",
-             "fit": "likelihood grid (k_fit) + estimator (k_estimate, 0.05 ms)",
+             "fit": "likelihood grid (k_fit) + estimator (k_estimate, 0.04 ms)",
              "model": "sky-model residual DFT (k_model)"}
-    unit_names = {"extract": "(visibility, source) pair", "fit": "(cell, e point, knot)",
+    unit_names = {"extract": "(visibility, source) pair", "fit": "(cell, e point, knot)" if mixed else "(record, e point, knot)",
                   "model": "(visibility, source) pair"}
     flop = {"extract": EXTRACT_FLOP_PAIR * pairs,
-            "fit": float(np.sum(cells)) * n_valid * (FIT_FLOP_CELL_POINT + FIT_FLOP_CELL_POINT_KNOT * p.num_r),
+            "fit": float(records) * n_valid * (FIT_FLOP_CELL_POINT + FIT_FLOP_CELL_POINT_KNOT * p.num_r),
             "model": MODEL_FLOP_PAIR * pairs}
     peak_flop = FP32_PEAK_TFLOPS if mixed else FP64_PEAK_TFLOPS
     kernels = {}
@@ -985,7 +999,7 @@ def run_form(precision, steps, warmup, seq_chunks=(), pos_sigmas=(), pos_sides=(
                      "fit": round(stage_ms[2], 4)},
         "roofline": roofline,
         "kernel_rooflines": kernels,
-        "facet_cells": {"total": int(cells.sum()), "mean": round(float(cells.mean()), 1),
+        "facet_cells": {"total": int(cells.sum()), "likelihood_records": records, "mean": round(float(cells.mean()), 1),
                         "min": int(cells.min()), "max": int(cells.max())},
         "fit_quality": {"rms_e_minus_true": round(rms, 5), "bad_var": int(np.sum(flags & 1)),
                         "edge": int(np.sum((flags & 4) > 0))},

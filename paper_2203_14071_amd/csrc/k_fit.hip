@@ -518,9 +518,9 @@ __global__ __launch_bounds__(256) void k_fit_window(FitArgs a, int num_r) {
 
 // The same for the sources of at most a.knot_positions positions, 64 per
 // block, the knots shared by the block's four waves.  A narrowed fit is a few
-// waves per source and the walk over the largest facet's records (4.2 us per
-// 10 records with all 20 knots in a lane, 0.35 ms at 786 cells) outlasts all
-// others; shared knots make it four times shorter.  300 sources, us, k_fit_window |
+// waves per source and the walk over the largest facet's records (some 900
+// VALU cycles per record with all 20 knots in a lane) outlasts all others;
+// shared knots make it four times shorter.  300 sources, us, k_fit_window |
 // k_window_knots: lattice of every fourth point and its boxes 709 | 409, boxes
 // of 9 x 9 points 269 | 122; 1000 sources 1,180 | 1,111 and 363 | 195.
 template <bool kMixed>

@@ -19,7 +19,8 @@
 // FP64 forms take a 2048-entry table (32 KB of LDS; sin's x^5 term drops,
 // one FMA per pair) in blocks of 512 threads, so that four blocks per CU
 // keep eight waves per SIMD in 128 KB of LDS; both form the sky sum with the
-// same table, so the two orders give the same residual values.
+// same table, so the two orders give the same residual values (mixed form:
+// to FP32 rounding where k_model_rows forms the one in caller order).
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
 #include "rlf_sky.h"
