@@ -1,19 +1,14 @@
 // The grid-narrowing network: features, BF16 MFMA GEMM, epilogues, loss,
 // back-propagation helpers, Adam, and the window boxes.
 //
-// GEMM: C[M x N] (FP32) = A[M x K] * B[K x N], A and B BF16 with arbitrary
-// element strides (so X W, dZ W^T and H^T dZ all use one kernel).  Block tile
-// 128 x 128 x 32, four waves each owning a 64 x 64 quarter as 2 x 2
-// v_mfma_f32_32x32x16_bf16 tiles.  Operand fragments of that instruction:
-// lane l holds A[l%32][8(l/32)+t] and B[8(l/32)+t][l%32] (t = 0..7) and
-// accumulator r of lane l is C[8(r/4) + 4(l/32) + r%4][l%32].  LDS keeps the
-// A tile as [m][k] and the B tile as [n][k] (k contiguous, padded by 8), so
-// each fragment is one 16-byte LDS read.  Global loads take 8 contiguous
-// BF16 when the operand is contiguous along k (or along m / n, transposing
-// into LDS), else single elements; out-of-range elements are zero.
-// grid.z splits K; with more than one split each slice writes its partial
-// product to a workspace and a second kernel adds the slices in a fixed
-// order, so results do not depend on scheduling.
+// GEMM: C[M x N] (FP32) = A * B in BF16, both operands contiguous along the
+// contraction k (weights, layer inputs and gradients are kept or made
+// transposed where a product needs it).  Operand fragments of
+// v_mfma_f32_32x32x16_bf16: lane l holds A[l%32][8(l/32)+t] and
+// B[8(l/32)+t][l%32] (t = 0..7) and accumulator r of lane l is
+// C[8(r/4) + 4(l/32) + r%4][l%32].  grid.z splits K; with more than one split
+// each slice writes its partial product to a workspace and a second kernel
+// adds the slices in a fixed order, so results do not depend on scheduling.
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -28,94 +23,10 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kBM = 128, kBN = 128, kBK = 32, kPad = 8, kLd = kBK + kPad;
 constexpr float kLogVarMin = -6.9077552789821368f;   // ln(1e-3)
 constexpr double kFeatureClip = 4.0;
 
 __device__ __forceinline__ __bf16 to_bf16(float x) { return __float2bfloat16(x); }
-
-// Stage rows [r0, r0+128) x k [k0, k0+32) of an operand whose element (r, k)
-// is at p[r*sr + k*sk] into lds[r][k]; rows >= nr or k >= nk read as zero.
-__device__ __forceinline__ void stage(__bf16 *lds, const __bf16 *__restrict__ p, int64_t sr, int64_t sk, int r0,
-                                      int nr, int k0, int nk) {
-  const int t = threadIdx.x;
-  if (sk == 1 && (sr % 8) == 0) {
-    // 128 rows x 4 chunks of 8 k: 512 chunks, 2 per thread
-    for (int c = t; c < kBM * (kBK / 8); c += 256) {
-      const int r = c / (kBK / 8), kc = (c % (kBK / 8)) * 8;
-      const int gr = r0 + r, gk = k0 + kc;
-      bf16x8 v;
-      if (gr < nr && gk + 8 <= nk) {
-        v = *reinterpret_cast<const bf16x8 *>(p + (int64_t)gr * sr + gk);
-      } else {
-        for (int e = 0; e < 8; ++e)
-          v[e] = (gr < nr && gk + e < nk) ? p[(int64_t)gr * sr + (int64_t)(gk + e)] : to_bf16(0.0f);
-      }
-      *reinterpret_cast<bf16x8 *>(lds + r * kLd + kc) = v;
-    }
-  } else if (sr == 1 && (sk % 8) == 0) {
-    // contiguous along rows: 32 k x 16 chunks of 8 rows
-    for (int c = t; c < kBK * (kBM / 8); c += 256) {
-      const int k = c / (kBM / 8), rc = (c % (kBM / 8)) * 8;
-      const int gk = k0 + k, gr = r0 + rc;
-      bf16x8 v;
-      if (gk < nk && gr + 8 <= nr) {
-        v = *reinterpret_cast<const bf16x8 *>(p + (int64_t)gk * sk + gr);
-      } else {
-        for (int e = 0; e < 8; ++e)
-          v[e] = (gk < nk && gr + e < nr) ? p[(int64_t)gk * sk + (int64_t)(gr + e)] : to_bf16(0.0f);
-      }
-      for (int e = 0; e < 8; ++e) lds[(rc + e) * kLd + k] = v[e];
-    }
-  } else {
-    for (int c = t; c < kBM * kBK; c += 256) {
-      const int r = c / kBK, k = c % kBK;
-      const int gr = r0 + r, gk = k0 + k;
-      lds[r * kLd + k] = (gr < nr && gk < nk) ? p[(int64_t)gr * sr + (int64_t)gk * sk] : to_bf16(0.0f);
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) __bf16 sa[kBM * kLd];
-  __shared__ __attribute__((aligned(16))) __bf16 sb[kBN * kLd];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * kBM, n0 = blockIdx.x * kBN;
-  const int wm = (wid >> 1) * 64, wn = (wid & 1) * 64;
-  // K slices start on kBK boundaries so the 16-byte loads stay aligned
-  const int kper = ((g.K + (int)gridDim.z - 1) / (int)gridDim.z + kBK - 1) / kBK * kBK;
-  const int kb = blockIdx.z * kper, ke = min(g.K, kb + kper);
-  f32x16 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j)
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  for (int k0 = kb; k0 < ke; k0 += kBK) {
-    __syncthreads();
-    // A tile: rows m, elements A(m, k) = a[m*sam + k*sak]; B tile stored [n][k]: B(k, n) = b[k*sbk + n*sbn]
-    stage(sa, g.a, g.sam, g.sak, m0, g.M, k0, ke);
-    stage(sb, g.b, g.sbn, g.sbk, n0, g.N, k0, ke);
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kBK; kk += 16) {
-      bf16x8 fa[2], fb[2];
-      for (int i = 0; i < 2; ++i)
-        fa[i] = *reinterpret_cast<const bf16x8 *>(sa + (wm + i * 32 + (lane & 31)) * kLd + kk + 8 * (lane >> 5));
-      for (int j = 0; j < 2; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8 *>(sb + (wn + j * 32 + (lane & 31)) * kLd + kk + 8 * (lane >> 5));
-      for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-  }
-  float *outp = gridDim.z > 1 ? g.ws + (int64_t)blockIdx.z * g.M * g.N : g.c;
-  const int64_t ld = gridDim.z > 1 ? g.N : g.ldc;
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j)
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int n = n0 + wn + j * 32 + (lane & 31);
-        if (m < g.M && n < g.N) outp[(int64_t)m * ld + n] = acc[i][j][r];
-      }
-}
 
 // GEMM with both operands contiguous along k: C[M x N] (FP32, row stride
 // ldc) = sum_k A[m lda + k] B[n ldb + k].  Block tile 128 x 128, k tile 64,
@@ -127,7 +38,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 // issued two tiles ahead of its MFMAs, and one barrier per tile separates
 // the phases.  Rows beyond M or N and k beyond the slice read as
 // zero (K a multiple of 8, lda and ldb multiples of 8).  grid.z splits K in
-// multiples of 64; with more than one slice each writes its partial product
+// slices of kper; with more than one slice each writes its partial product
 // to the workspace and k_reduce_split adds the slices in order.
 constexpr int kTM = 128, kTN = 128, kTK = 64, kLdT = kTK + 8;
 
@@ -199,8 +110,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(GemmNTArgs g) {
   nt_tile(nt, mt, z);
   const int m0 = mt * kTM, n0 = nt * kTN;
   const int wm = (wid >> 1) * 64, wn = (wid & 1) * 64;
-  const int kper = ((g.K + (int)gridDim.z - 1) / (int)gridDim.z + kTK - 1) / kTK * kTK;
-  const int kb = z * kper, ke = min(g.K, kb + kper);
+  const int kb = z * g.kper, ke = min(g.K, kb + g.kper);
   const int T = kb < ke ? (ke - kb + kTK - 1) / kTK : 0;      // k tiles of this slice
   f32x16 acc[2][2];
   for (int i = 0; i < 2; ++i)
@@ -343,8 +253,7 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
     const TileArgs &g = kMode == kTilePlain ? g1 : g2;
     const int first = kMode == kTilePlain ? 0 : n1;
     tile_of(g, blockIdx.x - first, tile_count(g), n0, m0, z);
-    const int kper = ((g.K + g.split - 1) / g.split + kTK - 1) / kTK * kTK;
-    const f32x16 acc = tile_product(g, m0, n0, z * kper, min(g.K, (z + 1) * kper));
+    const f32x16 acc = tile_product(g, m0, n0, z * g.kper, min(g.K, (z + 1) * g.kper));
     float *out = g.split > 1 ? g.ws + (int64_t)z * g.M * g.N : g.c;
     const int n = n0 + (lane & 31);
     if (n < g.N)
@@ -366,7 +275,7 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
       const int m = m0 + 8 * (r >> 2) + 4 * half + (r & 3);
       const float v = acc[r] + bias;
       const __bf16 h = to_bf16(gelu(v));
-      hq[r >> 2][r & 3] = h;
+      hq[r >> 2][r & 3] = m < g1.M ? h : to_bf16(0.0f);
       if (m < g1.M) {
         g1.z[(int64_t)m * g1.N + n] = v;
         g1.h[(int64_t)m * g1.N + n] = h;
@@ -376,7 +285,7 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int m = m0 + 8 * q + 4 * half;
-        if (m < g1.M) *reinterpret_cast<bf16x4 *>(g1.ht + (int64_t)n * g1.M + m) = hq[q];
+        if (m < g1.ldt) *reinterpret_cast<bf16x4 *>(g1.ht + (int64_t)n * g1.ldt + m) = hq[q];
       }
     return;
   }
@@ -403,13 +312,14 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int m = m0 + 8 * q + 4 * half;
-      if (m < g1.M) *reinterpret_cast<bf16x4 *>(g1.dzt + (int64_t)n * g1.M + m) = dq[q];
+      if (m < g1.ldt) *reinterpret_cast<bf16x4 *>(g1.dzt + (int64_t)n * g1.ldt + m) = dq[q];
     }
   if (half == 0) g1.part[(int64_t)(m0 / 32) * g1.N + n] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
 }
 
-// dst[c][r] = src[r][c] for BF16 matrices [rows x cols]: 64 x 64 tiles
-// through LDS, four BF16 (8 bytes) per global access when the tile is whole
+// dst[c][r] = src[r][c] for BF16 matrices [rows x cols], rows of dst ld long
+// and zero from `rows` on: 64 x 64 tiles through LDS, four BF16 (8 bytes) per
+// global access when the tile is whole
 // and the row lengths are multiples of 4, else one element per access.  One
 // launch serves several matrices: the blocks run over the tiles of job 0,
 // then job 1, ...
@@ -429,10 +339,10 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(TransposeBatch tb) {
   const TransposeJob &J = tb.job[jn];
   const __bf16 *__restrict__ src = J.src;
   __bf16 *__restrict__ dst = J.dst;
-  const int64_t rows = J.rows, cols = J.cols;
+  const int64_t rows = J.rows, cols = J.cols, ld = J.ld;
   const int64_t local = b - tb.first_tile[jn];
   const int64_t r0 = (local / tb.tiles_x[jn]) * 64, c0 = (local % tb.tiles_x[jn]) * 64;
-  const bool whole = r0 + 64 <= rows && c0 + 64 <= cols && (cols % 4) == 0 && (rows % 4) == 0 &&
+  const bool whole = r0 + 64 <= rows && c0 + 64 <= cols && (cols % 4) == 0 && (ld % 4) == 0 &&
                      ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 7) == 0;
   if (whole) {
     // 64 rows x 16 groups of 4 columns: 4 per thread
@@ -446,7 +356,7 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(TransposeBatch tb) {
       const int j = q >> 4, r4 = (q & 15) * 4;           // output row j = source column c0 + j
       bf16x4 v;
       for (int e = 0; e < 4; ++e) v[e] = t[r4 + e][j];
-      *reinterpret_cast<bf16x4 *>(dst + (c0 + j) * rows + r0 + r4) = v;
+      *reinterpret_cast<bf16x4 *>(dst + (c0 + j) * ld + r0 + r4) = v;
     }
     return;
   }
@@ -458,7 +368,7 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(TransposeBatch tb) {
   __syncthreads();
   for (int i = ty; i < 64; i += 4) {
     const int64_t c = c0 + i, r = r0 + tx;
-    if (c < cols && r < rows) dst[c * rows + r] = t[tx][i];
+    if (c < cols && r < ld) dst[c * ld + r] = t[tx][i];    // zero from rows on
   }
 }
 
@@ -806,13 +716,13 @@ __global__ __launch_bounds__(1024) void k_head_slice(HeadArgs a) {
     for (int i = 0; i < 4; ++i) acc = fmaf(dh[i], gg[i], acc);
     scol[g][c] = acc;
   }
-  if (a.dzt && t < kHeadCols * 4) {
+  if (t < kHeadCols * 4) {
     const int k = t >> 2, r = (t & 3) * 8;
-    if (r < nr) {                                           // rows and so nr are multiples of 8
+    if (r0 + r < a.ldt) {                                   // dZ is zero from row nr on
       bf16x8 v;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = sdz[k * kDzLd + r + e];
-      *reinterpret_cast<bf16x8 *>(a.dzt + (int64_t)(blockIdx.y * kHeadCols + k) * a.rows + r0 + r) = v;
+      *reinterpret_cast<bf16x8 *>(a.dzt + (int64_t)(blockIdx.y * kHeadCols + k) * a.ldt + r0 + r) = v;
     }
   }
   __syncthreads();
@@ -1047,16 +957,6 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs &g, int split_k, hipStream_t st) {
-  if (split_k > 1 && (!g.ws || (int64_t)split_k * g.M * g.N > g.ws_floats)) return hipErrorInvalidValue;
-  const dim3 grid((g.N + kBN - 1) / kBN, (g.M + kBM - 1) / kBM, split_k > 1 ? split_k : 1);
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, g);
-  if (split_k > 1)
-    hipLaunchKernelGGL(k_reduce_split, dim3(grid_for((int64_t)g.M * g.N)), dim3(256), 0, st, g.ws, split_k, g.M, g.N,
-                       g.c, g.ldc);
-  return hipGetLastError();
-}
-
 hipError_t launch_bias_act(const float *c, const float *b, int64_t rows, int cols, float *z, __bf16 *h, int act,
                            hipStream_t st) {
   hipLaunchKernelGGL(k_bias_act, dim3(grid_for(rows * cols)), dim3(256), 0, st, c, b, rows, cols, z, h, act);
@@ -1108,7 +1008,8 @@ hipError_t launch_gelu_back_colsum(const float *dh, const float *z, int64_t rows
 }
 
 hipError_t launch_gemm_nt(const GemmNTArgs &g, int split_k, hipStream_t st) {
-  if (g.K % 8 || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
+  if (g.K % 8 || g.lda % 8 || g.ldb % 8 || g.kper < 8 || g.kper % 8 || (int64_t)g.kper * std::max(1, split_k) < g.K)
+    return hipErrorInvalidValue;
   if (split_k > 1 && (!g.ws || (int64_t)split_k * g.M * g.N > g.ws_floats)) return hipErrorInvalidValue;
   const dim3 grid((g.N + kTN - 1) / kTN, (g.M + kTM - 1) / kTM, split_k > 1 ? split_k : 1);
   hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, g);
@@ -1124,7 +1025,10 @@ hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs
     if (!g) continue;
     const bool epi = g == &first && mode != kTilePlain;
     if (g->M < 1 || g->N < 1 || g->K < 1 || g->split < 1 || g->K % 8 || g->lda % 8 || g->ldb % 8 ||
-        (epi && (g->split != 1 || g->N % 32 || ((g->ht || g->dzt) && g->M % 8))) || (g->split > 1 && !g->ws))
+        (!epi && (g->kper < 8 || g->kper % 8 || (int64_t)g->kper * g->split < g->K)) ||
+        (epi && (g->split != 1 || g->N % 32 ||
+                 ((g->ht || g->dzt) && (g->ldt % 8 || g->ldt < g->M || g->ldt >= g->M + 8)))) ||
+        (g->split > 1 && !g->ws))
       return hipErrorInvalidValue;
   }
   if (plain && mode == kTilePlain) return hipErrorInvalidValue;
@@ -1150,7 +1054,7 @@ hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, in
 }
 
 hipError_t launch_head_slice(const HeadArgs &a, hipStream_t st) {
-  if (a.rows < 1 || (a.dzt && a.rows % 8)) return hipErrorInvalidValue;
+  if (a.rows < 1 || !a.dzt || a.ldt % 8 || a.ldt < a.rows || a.ldt >= a.rows + 8) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_head_slice, dim3((unsigned)((a.rows + kSlice - 1) / kSlice), 512 / kHeadCols), dim3(1024), 0, st,
                      a);
   return hipGetLastError();
@@ -1167,7 +1071,9 @@ hipError_t launch_transpose_bf16(const TransposeJob *jobs, int n_jobs, hipStream
   tb.n = n_jobs;
   tb.first_tile[0] = 0;
   for (int j = 0; j < n_jobs; ++j) {
-    if (jobs[j].rows < 1 || jobs[j].cols < 1) return hipErrorInvalidValue;
+    // (the cleared columns lie in the tiles of the last rows)
+    if (jobs[j].rows < 1 || jobs[j].cols < 1 || jobs[j].ld < jobs[j].rows || jobs[j].ld > (jobs[j].rows + 63) / 64 * 64)
+      return hipErrorInvalidValue;
     tb.job[j] = jobs[j];
     tb.tiles_x[j] = (jobs[j].cols + 63) / 64;
     tb.first_tile[j + 1] = tb.first_tile[j] + tb.tiles_x[j] * ((jobs[j].rows + 63) / 64);

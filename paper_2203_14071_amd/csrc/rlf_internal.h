@@ -281,20 +281,6 @@ struct EstimateArgs {
   double recheck_rel, recheck_abs;
 };
 
-// C[M x N] (FP32, row stride ldc) = A * B, A(m, k) = a[m*sam + k*sak],
-// B(k, n) = b[k*sbk + n*sbn], both BF16.
-struct GemmArgs {
-  const __bf16 *a;
-  int64_t sam, sak;
-  const __bf16 *b;
-  int64_t sbk, sbn;
-  float *c;
-  int64_t ldc;
-  int32_t M, N, K;
-  float *ws;                 // split-K partials [split x M x N]
-  int64_t ws_floats;
-};
-
 // C[M x N] (FP32, row stride ldc) = sum_k A[m lda + k] B[n ldb + k], A and B
 // BF16 contiguous along k.
 struct GemmNTArgs {
@@ -305,6 +291,7 @@ struct GemmNTArgs {
   float *c;                  // null with a split: the partials stay in ws
   int64_t ldc;
   int32_t M, N, K;
+  int32_t kper;              // k per slice, a multiple of 8
   float *ws;                 // split-K partials [split x M x N]
   int64_t ws_floats;
 };
@@ -313,11 +300,13 @@ struct GemmNTArgs {
 // does with C: forward (z, h set): z = C + bias, h = GELU(z); backward (dz
 // set): dz = C gelu'(z) with the column sums of each 32 rows to part
 // [M / 32 x N]; neither: C as FP32 to c (or the split's partials to ws).
-// ht / dzt: also transposed ([N x M], M a multiple of 8) unless null.
+// ht / dzt: also transposed ([N x ldt], ldt the multiple of 8 from M on, the
+// columns beyond M zero) unless null.
 struct TileArgs {
   const __bf16 *a, *b;
   int64_t lda, ldb;
-  int32_t M, N, K, split;
+  int32_t M, N, K, split, kper;
+  int32_t ldt;
   float *c;                  // row stride N
   float *ws;                 // split-K partials [split x M x N]
   const float *bias;
@@ -339,7 +328,8 @@ struct HeadArgs {
   int64_t rows;
   float *y;                  // [rows x 6]
   __bf16 *dz;                // [rows x 512]
-  __bf16 *dzt;               // [512 x rows] (rows a multiple of 8), or null
+  __bf16 *dzt;               // [512 x ldt], columns beyond rows zero
+  int32_t ldt;               // the multiple of 8 from rows on
   float *part;               // column sums of dZ [slices x 512]
   float *out_part;           // dW4 and db4 [slices x 3078]
 };
@@ -411,7 +401,6 @@ hipError_t launch_scatter_u32(const uint32_t *src, const int32_t *idx, int64_t n
                               hipStream_t st);
 hipError_t launch_fill_cis(double2 *master, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
-hipError_t launch_gemm(const GemmArgs &g, int split_k, hipStream_t st);
 hipError_t launch_bias_act(const float *c, const float *b, int64_t rows, int cols, float *z, __bf16 *h, int act,
                            hipStream_t st);
 hipError_t launch_head(const float *y, const float *t, int64_t n, float *dy, __bf16 *dyb, double *loss,
@@ -447,6 +436,7 @@ struct TransposeJob {
   const __bf16 *src;
   int64_t rows, cols;
   __bf16 *dst;
+  int64_t ld;                // of dst, >= rows; its columns from rows on are cleared
 };
 hipError_t launch_transpose_bf16(const TransposeJob *jobs, int n_jobs, hipStream_t st);
 // One Adam step over n values; the first ones form the matrices [rows x cols]
