@@ -22,10 +22,16 @@ namespace {
 // One block per source; the launch is bound by the latency of its chain of
 // loads, reductions and barriers.  The block holds up to kHeld grid values in
 // registers between its passes (the 81 x 81 grid has 6,333 points; larger
-// grids are read again by every pass) and reduces the sums of a pass
-// together: one source takes 13 us, against 20 with every pass reading the
-// values and reducing sum by sum.  1,024 threads: 16 us (the held values
-// spill); values held in LDS: 18 us.
+// grids are read again by every pass), lists the points of the set for the
+// passes over them, and reduces the sums of a pass together: one source takes
+// 10.5 us, against 20 with every pass reading the values and reducing sum by
+// sum (1000 sources 28 us, against 45).  1,024 threads: 16 us (the held
+// values spill); values held in LDS: 18 us.
+// The mixed form's recheck is bound by its arithmetic, each candidate point
+// taken by a whole wave: with the knots' logarithms and exponentials a
+// lane each and the candidates dealt out evenly 1000 sources take 0.15 ms,
+// against 0.29 with every lane forming all knots' and each wave its own
+// neighbourhood's candidates.
 constexpr int kThreads = 512, kWavesEst = kThreads / 64;
 constexpr int kHeld = 14 * kThreads;
 constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
@@ -33,8 +39,9 @@ constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
 // ln L(e) of source s at (e1, e2) in FP64, evaluated by one whole wave (all
 // 64 lanes, uniform arguments): the lanes split the source's cells, knots in
 // groups of four; per knot D and M are summed per lane and then across the
-// wave, and ln L(e) = ln sum_k w_k L(e, alpha_k) as in the FP64 fit (the
-// same terms, summed in another order).  Every lane returns the same value.
+// wave, lane k forms the term of knot k, and ln L(e) = ln sum_k w_k
+// L(e, alpha_k) as in the FP64 fit (the same terms, summed in another order).
+// Every lane returns the same value.
 __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, double e2) {
   const int lane = threadIdx.x & 63;
   const double det = 1.0 - e1 * e1 - e2 * e2;
@@ -42,7 +49,7 @@ __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, doub
   const double a11 = 1.0 + e1, a12 = e2, a22 = 1.0 - e1;
   const int64_t c0 = a.fold_offsets[s], c1 = a.fold_offsets[s + 1];
   const double *lw = a.logw + (int64_t)s * a.num_r;
-  double mx = -INFINITY, acc = 0.0;
+  double own_d = 0.0, own_m = 1.0;                 // the sums of knot `lane`
   for (int k0 = 0; k0 < a.num_r; k0 += 4) {
     double D[4], M[4], sk[4];
 #pragma unroll
@@ -71,16 +78,23 @@ __device__ double loglike_f64_wave(const EstimateArgs &a, int s, double e1, doub
       }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (k0 + k < a.num_r) {
-        // D and M carry (2/3) and (4/9) of their values: ln M is off by -2 ln(3/2)
-        const double v = lw[k0 + k] + (D[k] * D[k] / (2.0 * M[k]) - 0.5 * log(M[k]) - kLnPowM32Scale);
-        const double nm = fmax(mx, v);
-        acc = (mx > -INFINITY ? acc * exp(mx - nm) : 0.0) + exp(v - nm);
-        mx = nm;
+    for (int k = 0; k < 4; ++k)
+      if (lane == k0 + k) {
+        own_d = D[k];
+        own_m = M[k];
       }
-    }
   }
+  static_assert(kMaxKnots <= 64, "a lane per knot");
+  const bool knot = lane < a.num_r;
+  // D and M carry (2/3) and (4/9) of their values: ln M is off by -2 ln(3/2)
+  const double v =
+      knot ? lw[lane] + (own_d * own_d / (2.0 * own_m) - 0.5 * log(own_m) - kLnPowM32Scale) : -INFINITY;
+  double mx = v;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d));
+  double acc = knot ? exp(v - mx) : 0.0;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
   return mx + log(acc);
 }
 
@@ -123,6 +137,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
   __shared__ double shv[kWavesEst];
   __shared__ int shi[kWavesEst];
   __shared__ int touch;
+  __shared__ uint16_t list[kHeld];
   const int s = blockIdx.x;
   if (a.redo && !a.redo[s]) return;
   double *L = a.lsurf + (int64_t)s * a.n_valid;
@@ -154,6 +169,24 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
     }
   };
   fill();
+  // where this thread's n entries go in a list over the block, and its length
+  auto wave_base = [&](int n, int &at, int &total) {
+    int x = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(x, d);
+      x += lane >= d ? o : 0;
+    }
+    if (lane == 63) shi[wid] = x;
+    __syncthreads();
+    at = x - n;
+    total = 0;
+    for (int q = 0; q < kWavesEst; ++q) {
+      at += q < wid ? shi[q] : 0;
+      total += shi[q];
+    }
+    __syncthreads();
+  };
 
   // pass 1: maximum, smallest index on ties (each thread scans increasing j)
   double best;
@@ -206,26 +239,38 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
     const double delta = a.recheck_rel * (fabs(best) + a.recheck_abs);
     const double lo = best - 2.0 * delta, thr0 = best + a.log_frac;
     const bool lat_out = a.redo_out && a.check_stride > 0;
-    for (int j0 = wid * 64; j0 < a.n_valid; j0 += kThreads) {
-      const int j = j0 + lane;
-      bool cand = false;
-      if (j < a.n_valid) {
-        const double v = L[j];
-        const int f = a.epts[j];
-        const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-        if (in_box(a.window, s, i1, i2))
-          cand = v >= lo || fabs(v - thr0) <= 2.0 * delta;
-        else if (lat_out && (i1 - ctr) % a.check_stride == 0 && (i2 - ctr) % a.check_stride == 0)
-          cand = fabs(v - thr0) <= 2.0 * delta;
+    auto candidate = [&](int j, double v) {
+      const int f = a.epts[j];
+      const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
+      if (in_box(a.window, s, i1, i2)) return v >= lo || fabs(v - thr0) <= 2.0 * delta;
+      return lat_out && (i1 - ctr) % a.check_stride == 0 && (i2 - ctr) % a.check_stride == 0 &&
+             fabs(v - thr0) <= 2.0 * delta;
+    };
+    auto evaluate = [&](int j) {                   // by the whole wave
+      const int f = a.epts[j];
+      const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
+      const double v = loglike_f64_wave(a, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step);
+      if (lane == 0) L[j] = v;
+    };
+    if (hold) {
+      // the candidates are neighbours on the grid: dealt out to the waves from
+      // a list, so that none has most of them
+      uint32_t mine = 0;                           // bit i: held[i] is one
+#pragma unroll 1
+      for (int i = 0; i < kPer; ++i) {
+        const int j = (int)threadIdx.x + i * kThreads;
+        if (j < a.n_valid && candidate(j, L[j])) mine |= 1u << i;
       }
-      uint64_t m = __ballot(cand);
-      while (m) {
-        const int b = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        const int f = a.epts[j0 + b];
-        const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-        const double v = loglike_f64_wave(a, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step);
-        if (lane == 0) L[j0 + b] = v;
+      int at, n_cand;
+      wave_base(__popc(mine), at, n_cand);
+      for (; mine; mine &= mine - 1) list[at++] = (uint16_t)((int)threadIdx.x + (__ffs(mine) - 1) * kThreads);
+      __syncthreads();
+      for (int t = wid; t < n_cand; t += kWavesEst) evaluate(list[t]);
+    } else {
+      for (int j0 = wid * 64; j0 < a.n_valid; j0 += kThreads) {
+        const int j = j0 + lane;
+        uint64_t m = __ballot(j < a.n_valid && candidate(j, L[j]));
+        for (; m; m &= m - 1) evaluate(j0 + __ffsll((unsigned long long)m) - 1);
       }
     }
     __threadfence_block();
@@ -270,34 +315,52 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
   // (the set may continue beyond it: the narrowed result is not trusted) or
   // an evaluated lattice point outside the window reaches the set
   const double thr = best + a.log_frac;
+  // the points of the set, in a list: the passes over them are short loops
+  // over all threads
+  int n_set = 0;
+  if (hold) {
+    uint32_t mine = 0;                             // bit i: held[i] is in the set
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if ((int)threadIdx.x + i * kThreads < a.n_valid && held[i] >= thr) mine |= 1u << i;
+    int at;
+    wave_base(__popc(mine), at, n_set);
+    for (; mine; mine &= mine - 1) list[at++] = (uint16_t)((int)threadIdx.x + (__ffs(mine) - 1) * kThreads);
+  }
+  auto members = [&](auto &&fn) {
+    if (hold) {
+      for (int t = threadIdx.x; t < n_set; t += kThreads) fn((int)list[t], L[list[t]]);
+    } else {
+      for (int j = threadIdx.x; j < a.n_valid; j += kThreads)
+        if (L[j] >= thr) fn(j, L[j]);
+    }
+  };
   double sum[4] = {0.0, 0.0, 0.0, 0.0};          // weight, first moments, count
   if (threadIdx.x == 0) touch = 0;
   __syncthreads();
-  each([&](int j, double v) {
-    if (v >= thr) {
-      const int f = a.epts[j];
-      const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-      if (!in_box(a.window, s, i1, i2)) {
-        // a lattice point outside the window reaching the set: refit
-        if (a.redo_out && a.check_stride > 0 && (i1 - ctr) % a.check_stride == 0 &&
-            (i2 - ctr) % a.check_stride == 0)
-          atomicOr(&touch, 1);
-        return;
-      }
-      if (a.window && a.redo_out) {
-        const int nb[4][2] = {{1, 0}, {-1, 0}, {0, 1}, {0, -1}};
-        for (int q = 0; q < 4; ++q) {
-          const int j1 = i1 + nb[q][0], j2 = i2 + nb[q][1];
-          if (grid_valid(j1, j2, a.n_e, a.half_r2) && !in_box(a.window, s, j1, j2)) atomicOr(&touch, 1);
-        }
-      }
-      const double w = exp(v - best);
-      const double x1 = (double)(i1 - ctr) * a.e_step, x2 = (double)(i2 - ctr) * a.e_step;
-      sum[0] += w;
-      sum[1] += w * x1;
-      sum[2] += w * x2;
-      sum[3] += 1.0;
+  members([&](int j, double v) {
+    const int f = a.epts[j];
+    const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
+    if (!in_box(a.window, s, i1, i2)) {
+      // a lattice point outside the window reaching the set: refit
+      if (a.redo_out && a.check_stride > 0 && (i1 - ctr) % a.check_stride == 0 &&
+          (i2 - ctr) % a.check_stride == 0)
+        atomicOr(&touch, 1);
+      return;
     }
+    if (a.window && a.redo_out) {
+      const int nb[4][2] = {{1, 0}, {-1, 0}, {0, 1}, {0, -1}};
+      for (int q = 0; q < 4; ++q) {
+        const int j1 = i1 + nb[q][0], j2 = i2 + nb[q][1];
+        if (grid_valid(j1, j2, a.n_e, a.half_r2) && !in_box(a.window, s, j1, j2)) atomicOr(&touch, 1);
+      }
+    }
+    const double w = exp(v - best);
+    const double x1 = (double)(i1 - ctr) * a.e_step, x2 = (double)(i2 - ctr) * a.e_step;
+    sum[0] += w;
+    sum[1] += w * x1;
+    sum[2] += w * x2;
+    sum[3] += 1.0;
   });
   block_sum(sum, shd);
   const double sw = sum[0], cnt = sum[3];
@@ -305,17 +368,15 @@ __global__ __launch_bounds__(kThreads) void k_estimate(EstimateArgs a) {
 
   // pass 3: central second moments
   double sec[3] = {0.0, 0.0, 0.0};
-  each([&](int j, double v) {
-    if (v >= thr) {
-      const int f = a.epts[j];
-      const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-      if (!in_box(a.window, s, i1, i2)) return;
-      const double w = exp(v - best);
-      const double d1 = (double)(i1 - ctr) * a.e_step - m1, d2 = (double)(i2 - ctr) * a.e_step - m2;
-      sec[0] += w * d1 * d1;
-      sec[1] += w * d2 * d2;
-      sec[2] += w * d1 * d2;
-    }
+  members([&](int j, double v) {
+    const int f = a.epts[j];
+    const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
+    if (!in_box(a.window, s, i1, i2)) return;
+    const double w = exp(v - best);
+    const double d1 = (double)(i1 - ctr) * a.e_step - m1, d2 = (double)(i2 - ctr) * a.e_step - m2;
+    sec[0] += w * d1 * d1;
+    sec[1] += w * d2 * d2;
+    sec[2] += w * d1 * d2;
   });
   block_sum(sec, shd);
   const double c11 = sec[0] / sw, c22 = sec[1] / sw, c12 = sec[2] / sw;
