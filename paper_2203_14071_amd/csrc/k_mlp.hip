@@ -249,10 +249,9 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int n1 = tile_count(g1);
   int m0, n0, z;
-  if ((int)blockIdx.x >= n1 || kMode == kTilePlain) {
-    const TileArgs &g = kMode == kTilePlain ? g1 : g2;
-    const int first = kMode == kTilePlain ? 0 : n1;
-    tile_of(g, blockIdx.x - first, tile_count(g), n0, m0, z);
+  if ((int)blockIdx.x >= n1) {
+    const TileArgs &g = g2;
+    tile_of(g, blockIdx.x - n1, tile_count(g), n0, m0, z);
     const f32x16 acc = tile_product(g, m0, n0, z * g.kper, min(g.K, (z + 1) * g.kper));
     float *out = g.split > 1 ? g.ws + (int64_t)z * g.M * g.N : g.c;
     const int n = n0 + (lane & 31);
@@ -304,6 +303,7 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
     const __bf16 d = to_bf16(x * gg);
     dq[r >> 2][r & 3] = d;
     if (in) g1.dz[(int64_t)m * g1.N + n] = d;
+    if (in && g1.c) g1.c[(int64_t)m * g1.N + n] = x;
     const float xo = __shfl_xor(x, 32), go = __shfl_xor(gg, 32);   // the other half's row
     sum[r & 3] = fmaf(half ? xo : x, half ? go : gg, sum[r & 3]);
     sum[r & 3] = fmaf(half ? x : xo, half ? gg : go, sum[r & 3]);
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(64, 1) void k_gemm_tile(TileArgs g1, TileArgs g2) {
       const int m = m0 + 8 * q + 4 * half;
       if (m < g1.ldt) *reinterpret_cast<bf16x4 *>(g1.dzt + (int64_t)n * g1.ldt + m) = dq[q];
     }
-  if (half == 0) g1.part[(int64_t)(m0 / 32) * g1.N + n] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+  if (half == 0 && g1.part) g1.part[(int64_t)(m0 / 32) * g1.N + n] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
 }
 
 // dst[c][r] = src[r][c] for BF16 matrices [rows x cols], rows of dst ld long
@@ -595,8 +595,9 @@ __global__ __launch_bounds__(1024) void k_head(const float *__restrict__ y, cons
 // 32 rows through y = h W4 + b4 and the loss gradient, then 128 of the 512
 // columns (blockIdx.y) through the slice's part of dW4 and db4, dh = dY W4^T
 // and dZ = dh gelu'(Z) with its column sums, with the arithmetic and the order
-// of k_out_forward, k_head, k_out_grad_part, k_out_dh and k_gelu_back_colsum
-// (which need 32-row slices of both sums).  Bound by latency, a chain of five
+// of k_out_forward, k_head, k_out_grad_part, k_out_dh and k_gelu_back_colsum.
+// (Where the latter's slices are not of 32 rows, dh is written instead of
+// their sums, for k_bias_part.)  Bound by latency, a chain of five
 // short phases: 512 rows 11.3 us, against 28 us of the five kernels (with all
 // 512 columns in one block 20.8 us: sixteen blocks for 256 CUs).
 constexpr int kSlice = 32, kHeadCols = 128, kDzLd = kSlice + 2;
@@ -702,6 +703,7 @@ __global__ __launch_bounds__(1024) void k_head_slice(HeadArgs a) {
     const __bf16 d = to_bf16(dh[i] * gg[i]);
     sdz[c * kDzLd + r] = d;
     if (r < nr) a.dz[(r0 + r) * 512 + col] = d;
+    if (r < nr && a.dh) a.dh[(r0 + r) * 512 + col] = dh[i];
   }
   if (up == 0) {                                            // column sums: the upper rows continue the lower ones'
     float acc = 0.0f;
@@ -726,9 +728,27 @@ __global__ __launch_bounds__(1024) void k_head_slice(HeadArgs a) {
     }
   }
   __syncthreads();
-  if (t < kHeadCols)
+  if (t < kHeadCols && a.part)
     a.part[(int64_t)blockIdx.x * 512 + blockIdx.y * kHeadCols + t] =
         (scol[0][t] + scol[1][t]) + (scol[2][t] + scol[3][t]);
+}
+
+// The first step of the bias gradients where their slices are not the tiles'
+// 32 rows, one launch for the three hidden layers (blockIdx.z), with the
+// arithmetic and the order of k_gelu_back_colsum.  A step of 513 rows takes
+// 168 us with it, 209 with the layer's epilogue in kernels of its own for
+// such batches.
+__global__ __launch_bounds__(256) void k_bias_part(BiasArgs a) {
+  __shared__ float sh[4][64];
+  const int c = threadIdx.x & 63, rg = threadIdx.x >> 6, l = blockIdx.z;
+  const int col = blockIdx.x * 64 + c;
+  const float *__restrict__ dh = a.dh[l], *__restrict__ z = a.z[l];
+  const int64_t r0 = (int64_t)blockIdx.y * a.per, r1 = min(a.rows, r0 + a.per);
+  float acc = 0.0f;
+  for (int64_t r = r0 + rg; r < r1; r += 4) acc = fmaf(dh[r * 512 + col], gelu_grad(z[r * 512 + col]), acc);
+  sh[rg][c] = acc;
+  __syncthreads();
+  if (rg == 0) a.part[l][(int64_t)blockIdx.y * 512 + col] = (sh[0][c] + sh[1][c]) + (sh[2][c] + sh[3][c]);
 }
 
 // One launch for a step's sums over slices (a wave per value, as
@@ -752,7 +772,7 @@ __global__ __launch_bounds__(1024) void k_join(JoinArgs a) {
     cols = 512;
   }
   float acc = 0.0f;
-  for (int s = lane; s < a.slices; s += 64) acc += p[(int64_t)s * cols];
+  for (int s = lane; s < (cols == 512 ? a.slices : a.out_slices); s += 64) acc += p[(int64_t)s * cols];
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
   if (lane == 0) *out = acc;
@@ -1023,7 +1043,7 @@ hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs
   const TileArgs *both[2] = {&first, plain};
   for (const TileArgs *g : both) {
     if (!g) continue;
-    const bool epi = g == &first && mode != kTilePlain;
+    const bool epi = g == &first;
     if (g->M < 1 || g->N < 1 || g->K < 1 || g->split < 1 || g->K % 8 || g->lda % 8 || g->ldb % 8 ||
         (!epi && (g->kper < 8 || g->kper % 8 || (int64_t)g->kper * g->split < g->K)) ||
         (epi && (g->split != 1 || g->N % 32 ||
@@ -1031,19 +1051,15 @@ hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs
         (g->split > 1 && !g->ws))
       return hipErrorInvalidValue;
   }
-  if (plain && mode == kTilePlain) return hipErrorInvalidValue;
   const TileArgs none{};
   const dim3 grid((unsigned)(tile_count(first) + (plain ? tile_count(*plain) : 0))), block(64);
   if (mode == kTileForward)
     hipLaunchKernelGGL(k_gemm_tile<kTileForward>, grid, block, 0, st, first, plain ? *plain : none);
-  else if (mode == kTileBackward)
-    hipLaunchKernelGGL(k_gemm_tile<kTileBackward>, grid, block, 0, st, first, plain ? *plain : none);
   else
-    hipLaunchKernelGGL(k_gemm_tile<kTilePlain>, grid, block, 0, st, first, none);
-  const TileArgs &p = plain ? *plain : first;
-  if (p.split > 1)
-    hipLaunchKernelGGL(k_reduce_split, dim3(grid_for((int64_t)p.M * p.N)), dim3(256), 0, st, p.ws, p.split, p.M, p.N,
-                       p.c, (int64_t)p.N);
+    hipLaunchKernelGGL(k_gemm_tile<kTileBackward>, grid, block, 0, st, first, plain ? *plain : none);
+  if (plain && plain->split > 1)
+    hipLaunchKernelGGL(k_reduce_split, dim3(grid_for((int64_t)plain->M * plain->N)), dim3(256), 0, st, plain->ws,
+                       plain->split, plain->M, plain->N, plain->c, (int64_t)plain->N);
   return hipGetLastError();
 }
 
@@ -1057,6 +1073,12 @@ hipError_t launch_head_slice(const HeadArgs &a, hipStream_t st) {
   if (a.rows < 1 || !a.dzt || a.ldt % 8 || a.ldt < a.rows || a.ldt >= a.rows + 8) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_head_slice, dim3((unsigned)((a.rows + kSlice - 1) / kSlice), 512 / kHeadCols), dim3(1024), 0, st,
                      a);
+  return hipGetLastError();
+}
+
+hipError_t launch_bias_part(const BiasArgs &a, hipStream_t st) {
+  if (a.slices < 1 || a.per < 1 || a.per * a.slices < a.rows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_bias_part, dim3(8, (unsigned)a.slices, 3), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

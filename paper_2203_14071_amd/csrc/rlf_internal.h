@@ -299,7 +299,8 @@ struct GemmNTArgs {
 // One product of k_gemm_tile, operands as GemmNTArgs, and what its epilogue
 // does with C: forward (z, h set): z = C + bias, h = GELU(z); backward (dz
 // set): dz = C gelu'(z) with the column sums of each 32 rows to part
-// [M / 32 x N]; neither: C as FP32 to c (or the split's partials to ws).
+// [M / 32 x N], or without part C to c; neither (a launch's second product):
+// C as FP32 to c (or the split's partials to ws).
 // ht / dzt: also transposed ([N x ldt], ldt the multiple of 8 from M on, the
 // columns beyond M zero) unless null.
 struct TileArgs {
@@ -330,14 +331,24 @@ struct HeadArgs {
   __bf16 *dz;                // [rows x 512]
   __bf16 *dzt;               // [512 x ldt], columns beyond rows zero
   int32_t ldt;               // the multiple of 8 from rows on
-  float *part;               // column sums of dZ [slices x 512]
+  float *part;               // column sums of dZ [slices x 512], or null and
+  float *dh;                 // dL/dh [rows x 512] instead
   float *out_part;           // dW4 and db4 [slices x 3078]
+};
+
+// Column sums of dh gelu'(z) over slices of `per` rows, for the three hidden
+// layers: part[l] [slices x 512].
+struct BiasArgs {
+  const float *dh[3], *z[3];
+  float *part[3];
+  int64_t rows, per;
+  int32_t slices;
 };
 
 // Sums over slices: parts of the output layer's gradients (out_part -> gw)
 // and of the hidden layers' bias gradients (part[l] -> db[l]), and the loss.
 struct JoinArgs {
-  int32_t slices;
+  int32_t out_slices, slices;
   const float *out_part;
   float *gw;
   const float *part[3];
@@ -419,7 +430,7 @@ hipError_t launch_out_backward(const __bf16 *h, const __bf16 *dyb, const float *
 hipError_t launch_gelu_back_colsum(const float *dh, const float *z, int64_t rows, int cols, __bf16 *dzb, float *db,
                                    float *ws, int64_t ws_floats, hipStream_t st);
 hipError_t launch_gemm_nt(const GemmNTArgs &g, int split_k, hipStream_t st);
-enum TileMode { kTilePlain, kTileForward, kTileBackward };
+enum TileMode { kTileForward, kTileBackward };
 // One launch of the 32 x 32-tile products `first` (whose epilogue is `mode`)
 // and, if given, `plain` (no epilogue; its split's partials are added up).
 hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs *plain, hipStream_t st);
@@ -427,6 +438,7 @@ hipError_t launch_gemm_tile(const TileArgs &first, TileMode mode, const TileArgs
 hipError_t launch_reduce_bias_act(const float *ws, int split, const float *b, int64_t rows, int cols, float *z,
                                   __bf16 *h, hipStream_t st);
 hipError_t launch_head_slice(const HeadArgs &a, hipStream_t st);
+hipError_t launch_bias_part(const BiasArgs &a, hipStream_t st);
 hipError_t launch_join(const JoinArgs &a, hipStream_t st);
 void colsum_slices(int64_t rows, int cols, int64_t ws_floats, int64_t *per, int *nsl);
 // dst[c][r] = src[r][c] for up to kMaxTransposeJobs BF16 matrices

@@ -39,6 +39,7 @@ struct rlf_mlp {
   float *ws = nullptr;                       // split-K partial products, column-sum slices
   __bf16 *dyb = nullptr;
   __bf16 *dzb[2] = {nullptr, nullptr};       // a layer's dZ, and the one before it while that is formed
+  float *dhl[2] = {nullptr, nullptr};        // dL/dh of the first two hidden layers, for k_bias_part
   float *part = nullptr;                     // slices of 32 rows: column sums per layer, output layer's gradients
   // k-contiguous operands of the NT GEMM: the BF16 weights transposed per
   // layer (W_l^T [out x in] at the offsets of W_l), and per batch the layer
@@ -78,6 +79,7 @@ void mlp_release(rlf_mlp *n) {
   dfree(n->xt);
   dfree(n->part);
   for (int k = 0; k < 2; ++k) {
+    dfree(n->dhl[k]);
     dfree(n->dzb[k]);
     dfree(n->ht[k]);
     dfree(n->dzt[k]);
@@ -258,6 +260,7 @@ int rlf_mlp_create(rlf_ctx *c, int64_t max_batch, rlf_mlp **out) {
     if ((rc = dalloc(c, &n->xt, padded(B) * (int64_t)kIn))) break;
     if ((rc = dalloc(c, &n->part, kSlices * (3 * kHid + kHid * kOut + kOut)))) break;
     for (int k = 0; k < 2 && rc == RLF_OK; ++k) {
+      if ((rc = dalloc(c, &n->dhl[k], std::min(B, kTileRows) * kHid))) break;
       if ((rc = dalloc(c, &n->dzb[k], B * kHid))) break;
       if ((rc = dalloc(c, &n->ht[k], padded(B) * (int64_t)kHid))) break;
       rc = dalloc(c, &n->dzt[k], padded(B) * (int64_t)kHid);
@@ -491,14 +494,14 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   HIPCHK(c, hipSetDevice(c->device));
   const int nb = (int)rows;
   const __bf16 *xb = reinterpret_cast<const __bf16 *>(x);
-  const bool tiled = nb <= kTileRows;
+  const bool fused = nb <= kTileRows;
   const int nbt = padded(nb);
   if (int e = forward_hidden(n, xb, nb, n->ht[1])) return e;
   const int64_t offW[3] = {kOffW1, kOffW2, kOffW3}, offB[3] = {kOffB1, kOffB2, kOffB3};
   int64_t per;
   int slices;
   colsum_slices(nb, kHid, kWsFloats, &per, &slices);
-  const bool fused = tiled && per == 32;         // the tiles' column sums are the slices
+  const bool aligned = per == 32;                // the bias gradients' slices are the tiles' rows
   int cur = 0;
   // output layer: dW4 = h3^T dY, db4 = sum dY (together, in the parameters'
   // order), dh3 = dY W4^T, and the last hidden layer's dZ
@@ -517,7 +520,8 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
     ha.dz = n->dzb[0];
     ha.dzt = n->dzt[0];
     ha.ldt = nbt;
-    ha.part = part[2];
+    ha.part = aligned ? part[2] : nullptr;
+    ha.dh = aligned ? nullptr : n->dh;
     ha.out_part = out_part;
     HIPCHK(c, launch_head_slice(ha, c->stream));
   } else {
@@ -529,12 +533,12 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
                                       c->stream));
   }
   {
-    // dW = h^T dZ with both operands transposed to [features x rows]: what the
-    // tile products do not write themselves, in one launch if that is all of it
+    // dW = h^T dZ with both operands transposed to [features x rows]: here what
+    // the tile products do not write themselves, or the last layer's
     const TransposeJob jx{xb, nb, kIn, n->xt, nbt}, jh0{n->h[0], nb, kHid, n->ht[0], nbt};
     const TransposeJob jh1{n->h[1], nb, kHid, n->ht[1], nbt}, jdz{n->dzb[0], nb, kHid, n->dzt[0], nbt};
     const TransposeJob jobs[2] = {fused ? jx : jdz, fused ? jh0 : jh1};
-    HIPCHK(c, launch_transpose_bf16(jobs, fused || !tiled ? 2 : 1, c->stream));
+    HIPCHK(c, launch_transpose_bf16(jobs, 2, c->stream));
   }
   for (int l = 2; l > 0; --l, cur ^= 1) {
     // dh = dZ W^T: rows of dZ and of W both run along the output index
@@ -545,8 +549,6 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
     dh.M = nb;
     dh.N = dh.K = kHid;
     dh.split = 1;
-    dh.kper = kHid;
-    dh.c = n->dh;
     dw.a = n->ht[l - 1];
     dw.b = n->dzt[cur];
     dw.lda = dw.ldb = nbt;
@@ -563,17 +565,13 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
       dh.dz = dz;
       dh.dzt = dzt;
       dh.ldt = nbt;
-      dh.part = part[l - 1];
+      dh.part = aligned ? part[l - 1] : nullptr;
+      dh.c = aligned ? nullptr : n->dhl[l - 1];
       HIPCHK(c, launch_gemm_tile(dh, kTileBackward, &dw, c->stream));
       continue;
     }
-    if (tiled) {
-      HIPCHK(c, launch_gemm_tile(dh, kTilePlain, nullptr, c->stream));
-      HIPCHK(c, launch_gemm_tile(dw, kTilePlain, nullptr, c->stream));
-    } else {
-      if (int e = gemm_nt(n, dh.a, kHid, dh.b, kHid, n->dh, kHid, nb, kHid, kHid, split_k(nb, kHid, kHid))) return e;
-      if (int e = gemm_nt(n, dw.a, nbt, dw.b, nbt, dw.c, kHid, kHid, kHid, nbt, split)) return e;
-    }
+    if (int e = gemm_nt(n, dh.a, kHid, dh.b, kHid, n->dh, kHid, nb, kHid, kHid, split_k(nb, kHid, kHid))) return e;
+    if (int e = gemm_nt(n, dw.a, nbt, dw.b, nbt, dw.c, kHid, kHid, kHid, nbt, split)) return e;
     HIPCHK(c, launch_gelu_back_colsum(n->dh, n->z[l - 1], nb, kHid, dz, n->g + offB[l - 1], n->ws, kWsFloats,
                                       c->stream));
     const TransposeJob jobs[2] = {{dz, nb, kHid, dzt, nbt},
@@ -583,7 +581,20 @@ int rlf_mlp_train_step(rlf_mlp *n, const void *x, const float *target, int64_t r
   if (int e = gemm_nt(n, n->xt, nbt, n->dzt[cur], nbt, n->g + offW[0], kHid, kIn, kHid, nbt, split_rows(kIn, kHid, nb)))
     return e;
   if (fused) {
+    if (!aligned) {
+      BiasArgs ba{};
+      for (int l = 0; l < 3; ++l) {
+        ba.dh[l] = l == 2 ? n->dh : n->dhl[l];
+        ba.z[l] = n->z[l];
+        ba.part[l] = part[l];
+      }
+      ba.rows = nb;
+      ba.per = per;
+      ba.slices = slices;
+      HIPCHK(c, launch_bias_part(ba, c->stream));
+    }
     JoinArgs ja{};
+    ja.out_slices = (nb + 31) / 32;
     ja.slices = slices;
     ja.out_part = out_part;
     ja.gw = n->g + kOffW4;
