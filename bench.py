@@ -934,7 +934,7 @@ def run_form(precision, steps, warmup, seq_chunks=(), pos_sigmas=(), pos_sides=(
     stage_idx = {"model": 0, "extract": 1, "fit": 2}
     names = {"extract": "facet extraction (k_extract; the stage also runs the sorted-order gather and the "
                         "compaction, < 2 % of it)",
-             "fit": "likelihood grid (k_fit) + estimator (k_estimate, 0.04 ms)",
+             "fit": "likelihood grid (k_fit) + estimator (k_estimate, 0.03 ms)",
              "model": "sky-model residual DFT (k_model)"}
     unit_names = {"extract": "(visibility, source) pair", "fit": "(cell, e point, knot)" if mixed else "(record, e point, knot)",
                   "model": "(visibility, source) pair"}
