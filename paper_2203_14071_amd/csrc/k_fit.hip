@@ -326,35 +326,46 @@ struct KnotSplit {
   static constexpr int kWavesPerSimd = NP == 0 ? 5 : (kMixed ? 2 : 3);
 };
 
-// Doubles of LDS loglike_block needs.
+// Waves per block of the refinement.  Its windows are a few blocks per source,
+// so the largest facet's walk bounds a level; with position offsets a wave
+// holds the sums of 4, 2 or 1 knots only and four waves walk the records two,
+// three or five times.  Ten waves take 20 knots of 25 offsets in one walk (as
+// many as the FP64 sums' registers leave room for; eight in the mixed form):
+// three levels for 100 sources, four waves | these: 9 offsets 491 | 344 us, 25
+// 853 | 514, 49 1,741 | 1,046, 25 in the mixed form 1,146 | 828.
 template <bool kMixed, int NP>
-constexpr int block_doubles() { return NP ? 2 * 64 * KnotSplit<kMixed, NP>::kWaves : kMaxKnots * 64; }
+constexpr int refine_waves() { return NP == 0 ? 4 : (kMixed ? 8 : 10); }
+template <bool kMixed, int NP>
+constexpr int refine_waves_per_simd() { return NP == 0 ? 5 : (kMixed ? 2 : 3); }
+
+// Doubles of LDS loglike_block needs with W waves.
+template <int NP, int W>
+constexpr int block_doubles() { return NP ? 2 * 64 * W : kMaxKnots * 64; }
 
 // ln L(e) of source s (not empty) at one point per lane, the same points in
 // every wave of the block; the result is wave 0's.
-template <bool kMixed, int NP>
+template <bool kMixed, int NP, int W>
 __device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int s, double e1, double e2, double *sh) {
-  using S = KnotSplit<kMixed, NP>;
-  constexpr int KP = S::kKnots;
+  constexpr int KP = KnotSplit<kMixed, NP>::kKnots;
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (NP != 0) {
     Lse t;
-    add_knots_pos<NP, kMixed>(a, num_r, s, e1, e2, wid * KP, S::kWaves * KP, t);
+    add_knots_pos<NP, kMixed>(a, num_r, s, e1, e2, wid * KP, W * KP, t);
     sh[wid * 64 + lane] = t.mx;
-    sh[(S::kWaves + wid) * 64 + lane] = t.acc;
+    sh[(W + wid) * 64 + lane] = t.acc;
     __syncthreads();
     double nm = t.mx, acc = 0.0;
 #pragma unroll
-    for (int w = 0; w < S::kWaves; ++w) nm = fmax(nm, sh[w * 64 + lane]);
+    for (int w = 0; w < W; ++w) nm = fmax(nm, sh[w * 64 + lane]);
 #pragma unroll
-    for (int w = 0; w < S::kWaves; ++w) {
+    for (int w = 0; w < W; ++w) {
       const double m = sh[w * 64 + lane];
-      acc += m > -INFINITY ? sh[(S::kWaves + w) * 64 + lane] * exp(m - nm) : 0.0;   // (a wave without knots)
+      acc += m > -INFINITY ? sh[(W + w) * 64 + lane] * exp(m - nm) : 0.0;   // (a wave without knots)
     }
     return nm + log(acc / (double)NP);
   } else {
 #pragma unroll 1
-    for (int k0 = wid * KP; k0 < num_r; k0 += S::kWaves * KP) {
+    for (int k0 = wid * KP; k0 < num_r; k0 += W * KP) {
       double v[KP];
       if (k0 + KP <= num_r)
         knot_terms<KP, kMixed>(a, s, e1, e2, k0, KP, v);
@@ -375,7 +386,7 @@ __device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int
     mx[1] = fmax(mx[0], mx[1]);
     __syncthreads();
 #pragma unroll 1
-    for (int k0 = wid * KP; k0 < num_r; k0 += S::kWaves * KP)
+    for (int k0 = wid * KP; k0 < num_r; k0 += W * KP)
 #pragma unroll
       for (int k = 0; k < KP; ++k)
         if (k0 + k < num_r) sh[(k0 + k) * 64 + lane] = exp(sh[(k0 + k) * 64 + lane] - (k0 + k < per ? mx[0] : mx[1]));
@@ -399,8 +410,10 @@ __device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int
 // integers; -inf outside the domain.  blockIdx.y = source, the grid sized for
 // the largest window (blocks past a source's window leave at once).
 template <bool kMixed, int NP>
-__global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixed, NP>::kWavesPerSimd)) void k_refine_eval(FitArgs a, RefineArgs r, int num_r) {
-  __shared__ double sh[block_doubles<kMixed, NP>()];
+__global__ __launch_bounds__((64 * refine_waves<kMixed, NP>()), (refine_waves_per_simd<kMixed, NP>())) void k_refine_eval(
+    FitArgs a, RefineArgs r, int num_r) {
+  constexpr int W = refine_waves<kMixed, NP>();
+  __shared__ double sh[block_doubles<NP, W>()];
   const int s = blockIdx.y;
   const int32_t *w = r.win + (int64_t)s * 5;
   if (!w[0]) return;                           // (empty facets are never active)
@@ -412,7 +425,7 @@ __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixe
   const int64_t k1 = w[1] + min(t, np - 1) / n2, k2 = w[2] + min(t, np - 1) % n2;
   const bool in = k1 * k1 + k2 * k2 < lim * lim;
   // a point outside the domain is evaluated at the centre and dropped
-  const double L = loglike_block<kMixed, NP>(a, num_r, s, in ? (double)k1 * res : 0.0, in ? (double)k2 * res : 0.0, sh);
+  const double L = loglike_block<kMixed, NP, W>(a, num_r, s, in ? (double)k1 * res : 0.0, in ? (double)k2 * res : 0.0, sh);
   if (threadIdx.x < 64 && t < np) r.lloc[(int64_t)s * r.max_side * r.max_side + t] = in ? L : -INFINITY;
 }
 
@@ -438,7 +451,7 @@ __global__ __launch_bounds__(256) void k_fit(FitArgs a, int num_r) {
 template <bool kMixed, int NP>
 __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixed, NP>::kWavesPerSimd)) void k_fit_knots(
     FitArgs a, int num_r) {
-  __shared__ double sh[block_doubles<kMixed, NP>()];
+  __shared__ double sh[block_doubles<NP, KnotSplit<kMixed, NP>::kWaves>()];
   const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
   if (a.redo && !a.redo[s]) return;            // uniform
   const int j = blockIdx.x * 64 + (int)(threadIdx.x & 63);
@@ -447,7 +460,7 @@ __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixe
   const int ctr = (a.n_e - 1) / 2;
   double L = NAN;
   if (a.offsets[s + 1] != a.offsets[s])        // uniform
-    L = loglike_block<kMixed, NP>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step, sh);
+    L = loglike_block<kMixed, NP, KnotSplit<kMixed, NP>::kWaves>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step, sh);
   if (threadIdx.x < 64 && j < a.n_valid) a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
 
@@ -526,7 +539,7 @@ __global__ __launch_bounds__(256) void k_fit_window(FitArgs a, int num_r) {
 template <bool kMixed>
 __global__ __launch_bounds__((KnotSplit<kMixed, 0>::kThreads), (KnotSplit<kMixed, 0>::kWavesPerSimd)) void k_window_knots(
     FitArgs a, int num_r) {
-  __shared__ double sh[block_doubles<kMixed, 0>()];
+  __shared__ double sh[block_doubles<0, KnotSplit<kMixed, 0>::kWaves>()];
   const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
   const Window w(a, s);
   if (w.positions() > a.knot_positions) return;
@@ -537,7 +550,7 @@ __global__ __launch_bounds__((KnotSplit<kMixed, 0>::kThreads), (KnotSplit<kMixed
     // a lane without a point evaluates the centre and drops it
     const int f = j >= 0 ? a.epts[j] : w.ctr * a.n_e + w.ctr;
     const int i1 = f / a.n_e, i2 = f - i1 * a.n_e;
-    L = loglike_block<kMixed, 0>(a, num_r, s, (double)(i1 - w.ctr) * a.e_step, (double)(i2 - w.ctr) * a.e_step, sh);
+    L = loglike_block<kMixed, 0, KnotSplit<kMixed, 0>::kWaves>(a, num_r, s, (double)(i1 - w.ctr) * a.e_step, (double)(i2 - w.ctr) * a.e_step, sh);
   }
   if (threadIdx.x < 64 && j >= 0) a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
@@ -721,8 +734,8 @@ namespace {
 
 template <bool kMixed, int NP>
 hipError_t refine_eval(const FitArgs &a, const RefineArgs &r, hipStream_t st) {
-  hipLaunchKernelGGL((k_refine_eval<kMixed, NP>), dim3(odd_blocks(r.max_side * r.max_side, 64), a.n_src), dim3(KnotSplit<kMixed, NP>::kThreads), 0, st, a, r,
-                     a.num_r);
+  hipLaunchKernelGGL((k_refine_eval<kMixed, NP>), dim3(odd_blocks(r.max_side * r.max_side, 64), a.n_src), dim3(64 * refine_waves<kMixed, NP>()), 0,
+                     st, a, r, a.num_r);
   return hipGetLastError();
 }
 
