@@ -193,6 +193,8 @@ int rlf_model_vis_noalloc(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *c
  * along a Morton curve over (u, v) (a layout for the extraction kernels; no
  * result depends on it beyond FP summation order).  Synchronises.  The
  * observation's uvw and sizes must not change while the object is used.
+ * A NaN u or v is passed over here; an extraction leaves its visibility out,
+ * and if the weight is positive the next synchronisation returns RLF_ERANGE.
  * RLF_ERANGE if some N_s > 16383 or there are 2^32 or more visibilities. */
 int rlf_facets_create(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat,
                       rlf_facets **out);

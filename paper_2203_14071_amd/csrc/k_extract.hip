@@ -541,8 +541,9 @@ __global__ __launch_bounds__(kVpThreads) void k_extract_vp(ExtractArgs a, const 
         if (!pend) break;
         // the first lane left opens its cell in place of the less recent one
         const int l = __ffsll((unsigned long long)pend) - 1;
-        if (fabs(from_lane(xf, l)) > half[i] || fabs(from_lane(yf, l)) > half[i]) {
-          // out of the facet: cannot happen unless uvw changed
+        if (!(fabs(from_lane(xf, l)) <= half[i] && fabs(from_lane(yf, l)) <= half[i])) {
+          // out of the facet: a NaN coordinate (which equals no key, its own
+          // included: it must not open a cell), or uvw changed
           if (lane == 0) atomicOr(a.err, 1u);
           pend &= ~(1ull << l);
           if (!pend) break;
