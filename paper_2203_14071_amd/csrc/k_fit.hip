@@ -362,7 +362,7 @@ __device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int
       const double m = sh[w * 64 + lane];
       acc += m > -INFINITY ? sh[(W + w) * 64 + lane] * exp(m - nm) : 0.0;   // (a wave without knots)
     }
-    return nm + log(acc / (double)NP);
+    return nm > -INFINITY ? nm + log(acc / (double)NP) : NAN;   // every term NaN: a cell of the facet is
   } else {
 #pragma unroll 1
     for (int k0 = wid * KP; k0 < num_r; k0 += W * KP) {
