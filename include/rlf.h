@@ -365,8 +365,10 @@ int rlf_fit_sequential(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat,
  * count; new choices are written back to it.  Creation runs the pass once
  * eagerly and synchronises.  Replays read and write the same buffers given
  * here (obs->vis may be refilled between replays); the catalogue, the
- * observation geometry and weights must stay as they were.  opts as for
- * rlf_fit_sources (the windowed mode uses its own windowed launch). */
+ * observation geometry and weights must stay as they were, and the facet
+ * object's position offsets as they are now.  opts as for rlf_fit_sources
+ * (the windowed mode uses its own windowed launch, facets with position
+ * offsets the grid launch: no tiles are chosen for them). */
 int rlf_pass_create(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat, rlf_facets *facets,
                     const rlf_fit_opts *opts, const rlf_fit_out *out, const char *tune_path,
                     rlf_pass **pass);
@@ -374,8 +376,8 @@ int rlf_pass_create(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat, rl
 /* Enqueue one replay of the pass on the context's stream. */
 int rlf_pass_launch(rlf_pass *pass);
 
-/* The chosen tile per bucket, and how it was chosen (0 bucket empty,
- * 1 timed now, 2 read from the table).  Either pointer may be NULL. */
+/* The chosen tile per bucket, and how it was chosen (0 bucket empty or none
+ * needed, 1 timed now, 2 read from the table).  Either pointer may be NULL. */
 int rlf_pass_tiles(const rlf_pass *pass, int32_t *tiles /*[4]*/, int32_t *tuned /*[4]*/);
 
 /* Free a pass (NULL is a no-op); synchronises. */

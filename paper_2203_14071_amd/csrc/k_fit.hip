@@ -763,6 +763,7 @@ hipError_t launch_lattice_windows(const FitArgs &a, double log_frac, int32_t *wi
 }
 
 hipError_t launch_fit_queue(const FitArgs &a, const QueueArgs &q, int mixed, int blocks, hipStream_t st) {
+  if (a.n_pos) return hipErrorInvalidValue;                      // position fixed only
   return mixed ? launch_q<true>(a, q, blocks, st) : launch_q<false>(a, q, blocks, st);
 }
 

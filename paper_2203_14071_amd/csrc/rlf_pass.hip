@@ -182,11 +182,8 @@ int autotune(rlf_pass *ps, const std::vector<int32_t> &ranks, const std::vector<
 // by more than two timings differ.  Passes, us, queue | grid: 20 sources 167
 // | 108, 150 sources 1,242 | 1,172, 1000 sources 3,951 | 3,534.
 int choose_launch(rlf_pass *ps) {
-  if (ps->opts.mode != 0 || ps->f->n_src == 0) return RLF_OK;   // a windowed pass has no queue
-  if (ps->f->pos_side > 1) {                          // the queue's likelihood is that of the fixed position
-    ps->use_queue = true;
-    return RLF_OK;
-  }
+  // a windowed pass has no queue, and the queue's likelihood is that of the fixed position
+  if (ps->opts.mode != 0 || ps->f->n_src == 0 || ps->f->pos_side > 1) return RLF_OK;
   rlf_ctx *c = ps->c;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   float queue = 1e30f, grid = 1e30f;
@@ -259,7 +256,7 @@ int rlf_pass_create(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
     int dev_cus = 0;
     if (hipDeviceGetAttribute(&dev_cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) dev_cus = 256;
     ps->blocks = dev_cus * rlf::fit_queue_blocks_per_cu(f->mixed, c->p.num_r);
-    if ((rc = autotune(ps, ranks, cells, tune_path))) break;
+    if (f->pos_side <= 1 && (rc = autotune(ps, ranks, cells, tune_path))) break;
     if ((rc = upload_schedule(ps, ranks, cells, ps->tiles))) break;
     if ((rc = choose_launch(ps))) break;
     // capture on a stream of our own (a graph cannot be captured on the legacy stream)
