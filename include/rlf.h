@@ -356,14 +356,15 @@ int rlf_fit_sequential(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat,
  * extraction, compaction, the likelihood grid and the estimate, captured
  * once into a HIP graph and replayed by rlf_pass_launch on the context's
  * stream.  The likelihood runs as the grid launch of rlf_fit_sources or as
- * one persistent work-queue launch, whichever is faster on these facets (the
- * results are the same): sources in decreasing order of facet cell count,
- * each work item covering tile*64 grid points of one source.  The tile for each facet-size bucket (cells
- * < 256, < 1024, < 4096, >= 4096) is autotuned at creation by timing the
- * candidates 1, 2, 4, 8 on the pass's own facets, unless `tune_path` (a text
- * file, may be NULL) already holds a choice for this precision and knot
- * count; new choices are written back to it.  Creation runs the pass once
- * eagerly and synchronises.  Replays read and write the same buffers given
+ * one persistent work-queue launch, by precision, knot count and number of
+ * sources (the results are the same): sources in decreasing order of facet
+ * cell count, each work item covering tile*64 grid points of one source.  The
+ * tile for each facet-size bucket (cells < 256, < 1024, < 4096, >= 4096) is
+ * autotuned at creation by timing the candidates 1, 2, 4, 8 on the pass's own
+ * facets, with the output arrays as scratch, unless `tune_path` (a text file,
+ * may be NULL) already holds a choice for this precision and knot count; new
+ * choices are written back to it.  Creation extracts the facets once eagerly
+ * and synchronises.  Replays read and write the same buffers given
  * here (obs->vis may be refilled between replays); the catalogue, the
  * observation geometry and weights must stay as they were, and the facet
  * object's position offsets as they are now.  opts as for rlf_fit_sources

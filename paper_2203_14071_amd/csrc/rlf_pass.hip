@@ -2,11 +2,12 @@
 // source, captured once into a HIP graph and replayed.
 //
 // The likelihood runs as the grid launch of rlf_fit_sources or, where that is
-// faster, as one persistent work-queue launch: ranks are the sources in
-// decreasing order of facet cell count (the longest items are claimed first),
-// an item covers tile*64 consecutive valid grid points of one source.  The tile per facet-size bucket is chosen by an autotuner that
-// times every candidate on the pass's own facets (bucket by bucket) and can
-// store its choice in a small text table for later passes.
+// faster (queue_is_faster), as one persistent work-queue launch: ranks are the
+// sources in decreasing order of facet cell count (the longest items are
+// claimed first), an item covers tile*64 consecutive valid grid points of one
+// source.  The tile per facet-size bucket is chosen by an autotuner that times
+// every candidate on the pass's own facets (bucket by bucket) and can store
+// its choice in a small text table for later passes.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -47,7 +48,6 @@ struct rlf_pass {
   int32_t *d_tile = nullptr;
   uint32_t *d_counter = nullptr;
   QueueArgs q{};
-  bool use_queue = false;                            // or the grid launch, whichever is faster here
   int blocks = 0;
   int tiles[kBuckets] = {1, 1, 1, 1};
   int tuned[kBuckets] = {0, 0, 0, 0};             // 1 = timed in this pass, 2 = read from the table
@@ -118,12 +118,12 @@ void write_table(const char *path, const std::map<std::string, int> &t) {
   for (const auto &kv : t) out << kv.first << " " << kv.second << "\n";
 }
 
-// Best of two runs of the full-grid fit, by the queue or (null) the grid launch.
-int time_fit(rlf_pass *ps, const QueueArgs *q, hipEvent_t e0, hipEvent_t e1, float *ms) {
+// Best of two runs of the full-grid fit by the queue.
+int time_fit(rlf_pass *ps, hipEvent_t e0, hipEvent_t e1, float *ms) {
   rlf_ctx *c = ps->c;
   for (int rep = 0; rep < 2; ++rep) {
     HIPCHK(c, hipEventRecord(e0, c->stream));
-    if (int e = rlf::enqueue_fit(c, ps->f, rlf_fit_opts{}, ps->out, q, q ? ps->blocks : 0)) return e;
+    if (int e = rlf::enqueue_fit(c, ps->f, rlf_fit_opts{}, ps->out, &ps->q, ps->blocks)) return e;
     HIPCHK(c, hipEventRecord(e1, c->stream));
     HIPCHK(c, hipEventSynchronize(e1));
     float t = 0.f;
@@ -159,7 +159,7 @@ int autotune(rlf_pass *ps, const std::vector<int32_t> &ranks, const std::vector<
       std::fill(tl, tl + kBuckets, cand);
       if ((rc = upload_schedule(ps, sub, cells, tl))) break;
       float ms = 1e30f;
-      if ((rc = time_fit(ps, &ps->q, e0, e1, &ms))) break;
+      if ((rc = time_fit(ps, e0, e1, &ms))) break;
       if (ms < best) {
         best = ms;
         ps->tiles[b] = cand;
@@ -175,27 +175,20 @@ int autotune(rlf_pass *ps, const std::vector<int32_t> &ranks, const std::vector<
   return rc;
 }
 
-// The pass captures the likelihood launch that is faster on its facets, both
-// giving the same bits: the work queue, or the grid launch of rlf_fit_sources,
-// whose waves keep their record loads scalar (no stores in a loop) and which
-// shares the knots of small catalogues between waves.  The queue has to win
-// by more than two timings differ.  Passes, us, queue | grid: 20 sources 167
-// | 108, 150 sources 1,242 | 1,172, 1000 sources 3,951 | 3,534.
-int choose_launch(rlf_pass *ps) {
-  // a windowed pass has no queue, and the queue's likelihood is that of the fixed position
-  if (ps->opts.mode != 0 || ps->f->n_src == 0 || ps->f->pos_side > 1) return RLF_OK;
-  rlf_ctx *c = ps->c;
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  float queue = 1e30f, grid = 1e30f;
-  int rc = RLF_OK;
-  if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
-    rc = hip_fail(c, hipGetLastError(), "hipEventCreate");
-  if (rc == RLF_OK) rc = time_fit(ps, nullptr, e0, e1, &grid);
-  if (rc == RLF_OK) rc = time_fit(ps, &ps->q, e0, e1, &queue);
-  if (e0) (void)hipEventDestroy(e0);
-  if (e1) (void)hipEventDestroy(e1);
-  ps->use_queue = queue < 0.97f * grid;
-  return rc;
+// Whether the pass captures the work queue or the grid launch of
+// rlf_fit_sources, both giving the same bits.  The grid launch's kernels hold
+// more waves per SIMD (the queue's loop costs registers, and its stores keep
+// the record loads from being scalar) and share the knots of small
+// catalogues: 20 sources 108 us against the queue's 167, 1000 sources 1,958
+// and 2,033 in the FP64 form, 1,954 and 2,124 in the mixed one.  The mixed
+// form's kernels for knot numbers above 8 other than 20 hold one wave per SIMD
+// (two with 23 knots) in either launch, and there the queue, which hands out
+// waves instead of blocks, keeps them busier from 400 sources on: 1000 sources
+// with 12, 24 and 32 knots 4,840 | 4,994, 5,273 | 5,500 and 5,562 | 5,857 us,
+// with 23 knots 2,445 | 2,494 (200 sources with 24 knots 1,238 | 1,207).
+bool queue_is_faster(const rlf_pass *ps) {
+  const int r = ps->c->p.num_r;
+  return ps->f->mixed && r > 8 && r != 20 && ps->f->n_src >= 400;
 }
 
 void pass_release(rlf_pass *ps) {
@@ -258,7 +251,8 @@ int rlf_pass_create(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
     ps->blocks = dev_cus * rlf::fit_queue_blocks_per_cu(f->mixed, c->p.num_r);
     if (f->pos_side <= 1 && (rc = autotune(ps, ranks, cells, tune_path))) break;
     if ((rc = upload_schedule(ps, ranks, cells, ps->tiles))) break;
-    if ((rc = choose_launch(ps))) break;
+    // a windowed pass has no queue, and the queue's likelihood is that of the fixed position
+    const bool use_queue = o.mode == 0 && f->pos_side <= 1 && queue_is_faster(ps);
     // capture on a stream of our own (a graph cannot be captured on the legacy stream)
     if (hipStreamCreateWithFlags(&ps->cs, hipStreamNonBlocking) != hipSuccess) {
       rc = hip_fail(c, hipGetLastError(), "hipStreamCreate");
@@ -269,7 +263,7 @@ int rlf_pass_create(rlf_ctx *c, const rlf_obs *obs, const rlf_catalog *cat, rlf_
     hipError_t e = hipStreamBeginCapture(ps->cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
       rc = rlf_extract_facets(c, obs, cat, nullptr, f);
-      if (rc == RLF_OK) rc = rlf::enqueue_fit(c, f, o, ps->out, ps->use_queue ? &ps->q : nullptr, ps->blocks);
+      if (rc == RLF_OK) rc = rlf::enqueue_fit(c, f, o, ps->out, use_queue ? &ps->q : nullptr, ps->blocks);
       hipGraph_t g = nullptr;
       e = hipStreamEndCapture(ps->cs, &g);
       ps->graph = g;
