@@ -444,10 +444,11 @@ __global__ __launch_bounds__(256) void k_fit(FitArgs a, int num_r) {
 
 // The grid with the knots shared by waves, for launches of few sources: the
 // full grid of a small catalogue, the full refit of the sources a narrowed
-// fit was not trusted for (blocks of the others leave at once), and every
-// position-marginalised grid.  blockIdx.y = source, largest facets first; one
-// group of 64 points per block (in a loop over groups the stores of one would
-// keep the next one's record loads from being scalar).
+// fit was not trusted for (blocks of the others leave at once), and the
+// position-marginalised grids (mixed form: of few sources).  blockIdx.y =
+// source, largest facets first; one group of 64 points per block (in a loop
+// over groups the stores of one would keep the next one's record loads from
+// being scalar).
 template <bool kMixed, int NP>
 __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixed, NP>::kWavesPerSimd)) void k_fit_knots(
     FitArgs a, int num_r) {
@@ -462,6 +463,30 @@ __global__ __launch_bounds__((KnotSplit<kMixed, NP>::kThreads), (KnotSplit<kMixe
   if (a.offsets[s + 1] != a.offsets[s])        // uniform
     L = loglike_block<kMixed, NP, KnotSplit<kMixed, NP>::kWaves>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step, sh);
   if (threadIdx.x < 64 && j < a.n_valid) a.lsurf[(int64_t)s * a.n_valid + j] = L;
+}
+
+// The position-marginalised grid with all knots in a thread, for launches of
+// many sources in the mixed form: its sums (FP32 partial ones and FP64 totals)
+// leave two waves per SIMD either way, so that sharing the knots adds waves
+// only where there are few.  300 and 1000 sources, us, k_fit_knots | this: 3 x
+// 3 offsets 4,186 | 3,148 and 14,252 | 10,635, 5 x 5 8,379 | 7,179 and 28,548
+// | 24,210, 7 x 7 21,981 | 15,457 and 75,007 | 52,326.
+template <int NP>
+__global__ __launch_bounds__(256) void k_fit_pos(FitArgs a, int num_r) {
+  const int s = a.size_order ? a.size_order[a.n_src - 1 - (int)blockIdx.y] : (int)blockIdx.y;
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= a.n_valid) return;
+  const int idx = a.epts[j];
+  const int i1 = idx / a.n_e, i2 = idx - (idx / a.n_e) * a.n_e;
+  const int ctr = (a.n_e - 1) / 2;
+  double L = NAN;
+  if (a.offsets[s + 1] != a.offsets[s]) {      // uniform
+    Lse t;
+    add_knots_pos<NP, true>(a, num_r, s, (double)(i1 - ctr) * a.e_step, (double)(i2 - ctr) * a.e_step, 0,
+                            pos_knot_block(NP), t);
+    L = t.mx + log(t.acc / (double)NP);
+  }
+  a.lsurf[(int64_t)s * a.n_valid + j] = L;
 }
 
 // The positions of a windowed launch of source s: its inclusive box (i1lo,
@@ -648,9 +673,21 @@ __global__ void k_reset_counter(uint32_t *c) {
                          a.num_r);                                                                  \
   } while (0)
 
+// Mixed form: launches of more than kPosGroups groups of 64 points (15 sources
+// on the 81 x 81 grid) take k_fit_pos.  16 sources, k_fit_knots | k_fit_pos: 3
+// x 3 offsets 284 | 337 us, 5 x 5 546 | 732, 7 x 7 1,321 | 1,730; 32 sources
+// 494 | 414, 939 | 911, 2,362 | 2,003; with facets of very different sizes the
+// lines cross at 15 sources (3 x 3, 16 sources: 302 | 275).
+constexpr int64_t kPosGroups = 1500;
+
 template <bool kMixed, int NP>
 hipError_t launch_knots(const FitArgs &a, hipStream_t st) {
   constexpr int threads = KnotSplit<kMixed, NP>::kThreads;
+  if constexpr (kMixed && NP != 0)
+    if ((a.n_valid + 63) / 64 * (int64_t)a.n_src > kPosGroups) {
+      hipLaunchKernelGGL(k_fit_pos<NP>, dim3((a.n_valid + 255) / 256, a.n_src), dim3(256), 0, st, a, a.num_r);
+      return hipGetLastError();
+    }
   hipLaunchKernelGGL((k_fit_knots<kMixed, NP>), dim3((a.n_valid + 63) / 64, a.n_src), dim3(threads), 0, st, a, a.num_r);
   return hipGetLastError();
 }
