@@ -88,8 +88,7 @@ __global__ __launch_bounds__(model_threads<kMixed>()) void k_model(ModelArgs a) 
 }
 
 // Mixed form, several channels: one thread per row and group of NC channels
-// (blockIdx.y); the last group's channels beyond n_chan repeat the last one
-// and are not stored.
+// (blockIdx.y), n_chan a multiple of NC.
 template <int NC>
 __global__ __launch_bounds__(256) void k_model_rows(ModelArgs a) {
   const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -97,7 +96,7 @@ __global__ __launch_bounds__(256) void k_model_rows(ModelArgs a) {
   const int c0 = blockIdx.y * NC;
   double sc[NC];
 #pragma unroll
-  for (int k = 0; k < NC; ++k) sc[k] = a.chan->scale[min(c0 + k, a.n_chan - 1)];
+  for (int k = 0; k < NC; ++k) sc[k] = a.chan->scale[c0 + k];
   float2 acc[NC];
   sum_mixed_row<NC>(a.u_m[row], a.v_m[row], a.w_m[row], sc, a.src32, a.s_begin, a.s_end, acc);
   const int64_t i0 = row * a.n_chan + c0;
@@ -105,7 +104,6 @@ __global__ __launch_bounds__(256) void k_model_rows(ModelArgs a) {
   const float2 *in = reinterpret_cast<const float2 *>(a.mode == 2 ? a.vis_in : a.out) + i0;
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
-    if (c0 + k >= a.n_chan) break;
     const float sp = (float)a.chan->spec[c0 + k];
     if (a.mode == 0) {
       out[k] = make_float2(sp * acc[k].x, sp * acc[k].y);
@@ -209,32 +207,33 @@ hipError_t launch_update_sorted(const UpdateArgs &a, int mixed, hipStream_t st) 
 namespace {
 
 // Channels per thread of k_model_rows, or 1: one thread per visibility
-// (k_model).  Time per 1000 sources and 64 visibilities, us on the whole
-// card, 579,181 rows: k_model 0.027; groups of two 0.027, of three 0.023, of
-// four 0.021; five and eight fall back to 0.024 and 0.022 (their registers
-// leave the FP32 instructions more operand conflicts), so more channels go in
-// groups of four.  A last group with one idle channel still gains (7
-// channels), five channels do not.  Below three waves per SIMD the larger
-// pieces of work leave the card idle at the end: 60,000 rows of three or four
-// channels 0.91x and 0.85x, 180,000 of four 0.99x; from 196,608 groups on
-// 1.00x to 1.13x (579,181 rows of eight 1,938 -> 1,713 us).
-constexpr int64_t kRowWaves = 3072;
+// (k_model).  Groups of three or four channels without an idle one: 579,181
+// rows and 1000 sources of three, four, six and eight channels take 692, 890,
+// 1,324 and 1,713 us against 770, 1,006, 1,478 and 1,937; of two they gain
+// nothing, five or eight in a group leave the FP32 instructions more operand
+// conflicts, and with an idle channel ten take 176 against 165, thirteen 229
+// against 205 (60 sources).  From kRowWaves waves on: with 3,126 the larger
+// pieces of work leave the card idle at the end (100,000 rows of eight
+// channels 433 | 402), with 4,688 they do not (150,000 rows 524 | 559).  A
+// thread's channels lie side by side, so a wave's accesses are whole lines
+// only where the group is the row; the others need some sources to hide that:
+// 579,181 rows of eight channels, 10, 20, 30 and 60 sources 88 | 33, 49 | 42,
+// 65 | 75 and 113 | 128, of sixteen 272 | 61 (10) and 154 | 170 (80).
+constexpr int64_t kRowWaves = 4600;
 
-int row_channels(int64_t n_rows, int n_chan) {
-  const int nc = n_chan < 4 ? n_chan : n_chan == 6 || n_chan == 9 ? 3 : 4;
-  const int64_t groups = (n_chan + nc - 1) / nc;
-  return n_chan == 5 || (n_rows + 63) / 64 * groups < kRowWaves ? 1 : nc;
+int row_channels(int64_t n_rows, int n_chan, int n_src) {
+  const int nc = n_chan % 4 == 0 ? 4 : n_chan % 3 == 0 ? 3 : 1;
+  const int least = n_chan <= 4 ? 1 : n_chan <= 8 ? 30 : 5 * n_chan;
+  return n_src < least || (n_rows + 63) / 64 * (n_chan / nc) < kRowWaves ? 1 : nc;
 }
 
 }  // namespace
 
 hipError_t launch_model(const ModelArgs &a, int mixed, hipStream_t st) {
-  const int nc = mixed ? row_channels(a.n_rows, a.n_chan) : 1;
+  const int nc = mixed ? row_channels(a.n_rows, a.n_chan, a.s_end - a.s_begin) : 1;
   if (nc > 1) {
-    const dim3 grid((unsigned)((a.n_rows + 255) / 256), (unsigned)((a.n_chan + nc - 1) / nc)), block(256);
-    if (nc == 2)
-      hipLaunchKernelGGL(k_model_rows<2>, grid, block, 0, st, a);
-    else if (nc == 3)
+    const dim3 grid((unsigned)((a.n_rows + 255) / 256), (unsigned)(a.n_chan / nc)), block(256);
+    if (nc == 3)
       hipLaunchKernelGGL(k_model_rows<3>, grid, block, 0, st, a);
     else
       hipLaunchKernelGGL(k_model_rows<4>, grid, block, 0, st, a);
