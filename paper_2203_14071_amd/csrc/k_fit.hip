@@ -44,11 +44,14 @@ namespace {
 
 constexpr int kBlock = kCellBlock;
 constexpr double kLnPowM32Scale = 0.40546510810816438198;   // ln(3/2)
-// Full grids of at most this many sources share their knots between waves
-// (k_fit_knots); grid and estimate in FP64, k_fit / k_fit_knots: 1 source 62 /
-// 38 us, 10 sources 126 / 92, 32 sources 246 / 212, 48 sources 288 / 283, 64
-// sources 347 / 359; in the mixed form 160 / 98 us and 230 / 183 us for 1 and 10.
-constexpr int kKnotSources = 48;
+// Full grids of at most this many groups of 64 points (48 sources on the 81 x
+// 81 grid) share their knots between waves (k_fit_knots).  Grid and estimate,
+// us, k_fit | k_fit_knots: 81 x 81 points, 1, 10, 48 and 100 sources FP64 66 |
+// 35, 99 | 70, 239 | 231 and 433 | 467, mixed 97 | 54, 131 | 81, 221 | 224 and
+// 399 | 422; 21 x 21 points, 100, 500 and 1000 sources 132 | 66, 236 | 174 and
+// 359 | 338, mixed 157 | 68, 213 | 168 and 330 | 317; 11 x 11, 100 and 1000
+// sources 129 | 61 and 196 | 124.
+constexpr int64_t kKnotGroups = 48 * 99;
 
 // Knots per pass over the cells: the mixed form with 20 knots takes them in
 // two passes of 10 (the quadratic form is formed twice per cell, but half
@@ -378,7 +381,8 @@ __device__ __forceinline__ double loglike_block(const FitArgs &a, int num_r, int
     __syncthreads();
     // loglike_e adds its terms pass by pass (the mixed form takes 20 knots in
     // two): the maximum of the passes so far, then the pass's exponentials,
-    // here each by the wave that has the knot
+    // here each by the wave that has the knot (bits as in loglike_e, those two
+    // passes apart: there a few points differ by a unit in the last place)
     const int per = kMixed && num_r == 20 ? 10 : num_r;
     double mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll 4
@@ -736,7 +740,7 @@ hipError_t launch(const FitArgs &a, hipStream_t st) {
     if (w.knot_positions > 0)
       hipLaunchKernelGGL(k_window_knots<kMixed>, dim3(odd_blocks(std::min(positions, w.knot_positions), 64), a.n_src),
                          dim3(KnotSplit<kMixed, 0>::kThreads), 0, st, w, a.num_r);
-  } else if (a.redo || a.n_src <= kKnotSources) {
+  } else if (a.redo || (a.n_valid + 63) / 64 * (int64_t)a.n_src <= kKnotGroups) {
     return launch_knots<kMixed, 0>(a, st);
   } else {
     RLF_FIT_DISPATCH(k_fit, dim3((a.n_valid + 255) / 256, a.n_src), a);
