@@ -58,8 +58,22 @@ constexpr int32_t kNoKey = INT32_MIN;          // the same for the previous run'
 constexpr int kVpSources = 128;
 // ... and so do launches that would leave the chip idle through k_extract:
 // fewer than kTileWaves waves of kMinChunk visibilities (11,400 visibilities,
-// 100 sources: 129 us against 34).
+// 100 sources: 156 us against 37).  Its waves take two sources at a time, each
+// at least a step of 64 visibilities, two reductions and eight atomics, so
+// large catalogues go the other way.  k_extract | k_extract_vp, us: 11,400
+// visibilities, 1,000, 1,200 and 4,000 sources FP64 179 | 137, 173 | 178 and
+// 351 | 692, mixed 106 | 144, 123 | 152 and 314 | 622; 20,000, 800 and 2,000
+// FP64 122 | 112 and 184 | 216, mixed 92 | 77 and 149 | 180; 2,000, 2,000 and
+// 10,000 FP64 178 | 92 and 250 | 991, mixed 89 | 80 and 239 | 893.
 constexpr int64_t kMinChunk = 256, kTileWaves = 4096;
+constexpr int64_t kVpCatalogueF64 = 1024, kVpCatalogueMixed = 800, kVpCatalogueTiny = 2048, kTinyPairs = 4000000;
+
+bool visibilities_on_lanes(int64_t n_vis, int64_t n_src, int mixed) {
+  if (n_src <= kVpSources) return true;
+  if ((n_vis + kMinChunk - 1) / kMinChunk * ((n_src + 63) / 64) >= kTileWaves) return false;
+  return n_src <= (mixed ? kVpCatalogueMixed : kVpCatalogueF64) ||
+         (n_src <= kVpCatalogueTiny && n_vis * n_src <= kTinyPairs);
+}
 
 // Work item of a wave: blocks go to the eight XCDs round-robin by index; item
 // (chunk, part) with the parts of a chunk (source tiles or groups, which read
@@ -649,8 +663,7 @@ hipError_t launch_extract(const ExtractArgs &a, int mixed, hipStream_t st, const
     hipError_t e = launch_update_sorted(*upd, mixed, st);
     if (e != hipSuccess) return e;
   }
-  const int64_t tile_waves = (a.sv.n_vis + kMinChunk - 1) / kMinChunk * ((a.n_src + 63) / 64);
-  if (a.n_src <= kVpSources || tile_waves < kTileWaves) {
+  if (visibilities_on_lanes(a.sv.n_vis, a.n_src, mixed)) {
     const UpdateArgs none{};
     if (a.n_src == 1) return mixed ? run_vp<true, 1, false>(a, none, st) : run_vp<false, 1, false>(a, none, st);
     return mixed ? run_vp<true, 2, false>(a, none, st) : run_vp<false, 2, false>(a, none, st);

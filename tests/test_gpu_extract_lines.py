@@ -1,0 +1,16 @@
+"""The extraction on both sides of the lines between its two kernels, against
+the oracle: small observations by the size of the catalogue and by the number
+of pairs."""
+import pytest
+
+from tests import test_gpu_extract_vp as vp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,n_src,mixed", [(5200, 800, True), (5200, 801, True), (4000, 1024, False),
+                                              (4000, 1025, False), (2000, 2000, True), (2001, 2000, True),
+                                              (2000, 2000, False), (2001, 2000, False), (600, 2048, True),
+                                              (600, 2049, True), (65, 2048, False), (65, 2049, False)])
+def test_catalogue_of_a_small_observation(rows, n_src, mixed):
+    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "cells")
