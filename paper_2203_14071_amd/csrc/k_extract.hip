@@ -613,10 +613,19 @@ int64_t chunk_size(int64_t n_vis, int64_t n_tiles, int64_t capacity) {
 
 // Steps of 64 visibilities per wave of k_extract_vp: enough waves to fill the
 // chip once, between 2 and 64 steps (a wave ends with two reductions and
-// eight atomics per source).
+// eight atomics per source).  Chunks go to the XCDs in turn: between eight
+// and kFewChunks of them are rounded up to a multiple of eight, since otherwise
+// some XCDs have a chunk more than the others (800 sources, FP64, 11,400 and
+// 20,000 visibilities 148 | 107 and 112 | 84 us, mixed form 108 | 101 and 77 | 76).
+constexpr int64_t kFewChunks = 64;
 int64_t vp_steps(int64_t n_vis, int64_t groups, int64_t capacity) {
-  const int64_t total = (n_vis + 63) / 64 * groups;
-  return std::min<int64_t>(64, std::max<int64_t>(2, (total + capacity - 1) / std::max<int64_t>(1, capacity)));
+  const int64_t total = (n_vis + 63) / 64;
+  const int64_t fill = (total * groups + capacity - 1) / std::max<int64_t>(1, capacity);
+  const int64_t steps = std::min<int64_t>(64, std::max<int64_t>(2, fill));
+  const int64_t chunks = (total + steps - 1) / steps;
+  if (chunks <= kXcd || chunks >= kFewChunks) return steps;
+  const int64_t even = (chunks + kXcd - 1) / kXcd * kXcd;
+  return std::max<int64_t>(2, (total + even - 1) / even);
 }
 
 // Blocks whose waves cover every (chunk, part): per XCD, the parts of every

@@ -1,6 +1,7 @@
 """The extraction on both sides of the lines between its two kernels, against
 the oracle: small observations by the size of the catalogue and by the number
-of pairs."""
+of pairs; and chunks of visibilities, whose number is rounded up to a multiple
+of eight between 9 and 63, cut by the shortest step and by the fill."""
 import pytest
 
 from tests import test_gpu_extract_vp as vp
@@ -13,4 +14,11 @@ pytestmark = pytest.mark.gpu
                                               (2000, 2000, False), (2001, 2000, False), (600, 2048, True),
                                               (600, 2049, True), (65, 2048, False), (65, 2049, False)])
 def test_catalogue_of_a_small_observation(rows, n_src, mixed):
+    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "cells")
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("rows,n_src", [(1024, 2), (1025, 2), (1153, 3), (2049, 5), (8064, 2), (8193, 2), (4097, 501),
+                                        (11400, 799)])
+def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "cells")
