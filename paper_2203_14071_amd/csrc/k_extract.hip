@@ -593,39 +593,44 @@ __global__ __launch_bounds__(kVpThreads) void k_extract_vp(ExtractArgs a, const 
   }
 }
 
-// Visibilities per wave of k_extract, sized so that the waves are a whole
-// number of rounds of the resident ones (a last round nearly empty would leave
-// the chip idle for a whole wave's duration): near 2048 where that makes at
-// least four rounds, near 450 otherwise.  A chunk of the dense core of the
-// plane takes longer than one of its outskirts, and fewer rounds leave that
-// unevened: 2,316,728 visibilities, 600 sources, mixed form: one round of
-// 2829 1.94 ms, six of 471 1.57 ms; 1,158,361 and 1000, FP64: one of 2263
-// 1.95 ms, four of 565 1.68 ms.
+// Chunks of a launch that has few of them: they go to the XCDs in turn, so that
+// a number that is no multiple of eight leaves some XCDs a chunk more than the
+// others.
+constexpr int64_t kFewChunks = 64;
+int64_t even_chunks(int64_t chunks) {
+  return chunks > kXcd && chunks < kFewChunks ? (chunks + kXcd - 1) / kXcd * kXcd : chunks;
+}
+
+// Visibilities per wave of k_extract.  A wave's start and end cost its lanes two
+// open runs each (eight atomics), so that few visibilities per wave are slow,
+// and a chunk of the dense core of the plane takes longer than one of its
+// outskirts, which only many waves even out: 640 in the mixed form, 448 in FP64
+// (5,000,000 visibilities, 1000 sources, 520, 640, 1000 and 2048 each: mixed 4,843,
+// 4,800, 4,819 and 4,950 us, FP64 448, 1000 and 2048 6,800, 6,781 and 7,106), fewer
+// where those would fill less than kFill % of the resident waves (60,000 and 1,500
+// sources, filling 35, 50 and 70 %: mixed 231 | 255 | 248 us, FP64 311 | 327 | 286),
+// and a multiple of eight: each wave's first loads then start on a line of 128
+// bytes of every stream (5,000,000 and 256 sources, FP64, 489 each 2,600 us, 448 and
+// 512 2,157 and 2,184; 1000 sources 7,421 and 6,800).
+template <bool kMixed>
 int64_t chunk_size(int64_t n_vis, int64_t n_tiles, int64_t capacity) {
-  constexpr int64_t kLarge = 2048, kSmall = 450;
-  if (capacity <= 0 || n_vis <= 0) return kLarge;
-  const int64_t nominal = n_vis * n_tiles >= 4 * kLarge * capacity ? kLarge : kSmall;
-  const int64_t w0 = (n_vis + nominal - 1) / nominal * n_tiles;
-  const int64_t rounds = std::max<int64_t>(1, (w0 + capacity / 2) / capacity);
-  const int64_t max_chunks = std::max<int64_t>(1, rounds * capacity / n_tiles);
-  return std::max(kMinChunk, (n_vis + max_chunks - 1) / max_chunks);
+  constexpr int64_t kFull = kMixed ? 640 : 448, kFill = kMixed ? 35 : 70, kAlign = 8;
+  const int64_t waves = std::max<int64_t>(1, capacity * kFill / 100);
+  const int64_t len = std::max(kMinChunk, std::min(kFull, (n_vis * n_tiles + waves - 1) / waves));
+  const int64_t chunks = std::max<int64_t>(1, even_chunks((n_vis + len - 1) / len));
+  return std::max(kAlign, ((n_vis + chunks - 1) / chunks + kAlign - 1) / kAlign * kAlign);
 }
 
 // Steps of 64 visibilities per wave of k_extract_vp: enough waves to fill the
 // chip once, between 2 and 64 steps (a wave ends with two reductions and
-// eight atomics per source).  Chunks go to the XCDs in turn: between eight
-// and kFewChunks of them are rounded up to a multiple of eight, since otherwise
-// some XCDs have a chunk more than the others (800 sources, FP64, 11,400 and
+// eight atomics per source).  Few chunks rounded up (800 sources, FP64, 11,400 and
 // 20,000 visibilities 148 | 107 and 112 | 84 us, mixed form 108 | 101 and 77 | 76).
-constexpr int64_t kFewChunks = 64;
 int64_t vp_steps(int64_t n_vis, int64_t groups, int64_t capacity) {
   const int64_t total = (n_vis + 63) / 64;
   const int64_t fill = (total * groups + capacity - 1) / std::max<int64_t>(1, capacity);
   const int64_t steps = std::min<int64_t>(64, std::max<int64_t>(2, fill));
-  const int64_t chunks = (total + steps - 1) / steps;
-  if (chunks <= kXcd || chunks >= kFewChunks) return steps;
-  const int64_t even = (chunks + kXcd - 1) / kXcd * kXcd;
-  return std::max<int64_t>(2, (total + even - 1) / even);
+  const int64_t chunks = std::max<int64_t>(1, even_chunks((total + steps - 1) / steps));
+  return std::min<int64_t>(64, std::max<int64_t>(2, (total + chunks - 1) / chunks));
 }
 
 // Blocks whose waves cover every (chunk, part): per XCD, the parts of every
@@ -654,7 +659,7 @@ hipError_t run_tiles(ExtractArgs a, hipStream_t st) {
   auto kern = k_extract<kMixed, NS, G>;
   constexpr int kW = waves_per_block<kMixed>();
   a.n_tiles = (a.n_src + 64 * NS - 1) / (64 * NS);
-  a.chunk = (int32_t)chunk_size(v.n_vis, a.n_tiles, resident_blocks(kern, 64 * kW) * kW);
+  a.chunk = (int32_t)chunk_size<kMixed>(v.n_vis, a.n_tiles, resident_blocks(kern, 64 * kW) * kW);
   a.n_chunks = (v.n_vis + a.chunk - 1) / a.chunk;
   hipLaunchKernelGGL(kern, dim3(grid_blocks(a.n_chunks, a.n_tiles, kW)), dim3(64 * kW), 0, st, a, v.geo, v.quad, v.res,
                      reinterpret_cast<const uint64_t *>(v.wt), a.acc.cell);

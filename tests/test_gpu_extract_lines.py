@@ -22,3 +22,10 @@ def test_catalogue_of_a_small_observation(rows, n_src, mixed):
                                         (11400, 799)])
 def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "cells")
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("rows,n_src", [(7, 2100), (2048, 2100), (2049, 2100), (5003, 2049), (16129, 2100), (16385, 2049),
+                                        (700001, 200)])
+def test_chunks_of_source_tiles(rows, n_src, mixed):
+    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 100000 else "cells")
