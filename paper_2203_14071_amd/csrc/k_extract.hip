@@ -38,11 +38,11 @@ namespace rlf {
 namespace {
 
 constexpr int kXcd = 8;
-// Waves per block of k_extract: the FP64 form's 2048-entry table takes 32 KB
-// of LDS, so that four blocks of 8 waves per CU keep eight waves per SIMD.
-template <bool kMixed>
-constexpr int waves_per_block() { return kMixed ? 4 : 8; }
-constexpr int kTileTable = 2048;
+// Waves per block of k_extract by the entries T of the FP64 form's table (the
+// mixed form has none): 2048 take 32 KB of LDS, so that four blocks of 8 waves per
+// CU keep eight waves per SIMD; 1024 take 16 KB, eight blocks of 4 (run_tiles).
+template <bool kMixed, int T>
+constexpr int waves_per_block() { return kMixed || T == 1024 ? 4 : 8; }
 constexpr int kNsF64 = 1, kNsMixed = 1;        // sources per lane
 constexpr int kGroupF64 = 2, kGroupMixed = 4;  // visibilities whose scalar loads are issued together
 constexpr double kNoRun = 1099511627776.0;    // 2^40: "no open run" (run keys are below 2^31 in magnitude)
@@ -183,14 +183,14 @@ __device__ __forceinline__ void enter_cell(LaneSrc &L, double4 *__restrict__ acc
 // steers the scalar registers: a minimum of 7 waves gives 94 SGPRs with two
 // spilled to VGPR lanes and measured 4.5 % faster than 6 (97 SGPRs, none
 // spilled), while 8 spills 17 and is 15 % slower.
-template <bool kMixed, int NS, int G>
-__global__ __launch_bounds__((64 * waves_per_block<kMixed>()), kMixed ? 7 : 8) void k_extract(
+template <bool kMixed, int NS, int G, int T>
+__global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8) void k_extract(
     ExtractArgs a, const double4 *__restrict__ sgeo, const void *__restrict__ squad, const void *__restrict__ sres,
     const uint64_t *__restrict__ swt, double4 *__restrict__ acc) {
-  constexpr int kW = waves_per_block<kMixed>();
-  __shared__ double2 tab[kMixed ? 1 : kTileTable];
+  constexpr int kW = waves_per_block<kMixed, T>();
+  __shared__ double2 tab[kMixed ? 1 : T];
   if (!kMixed) {
-    cis_table_load<kTileTable>(tab, a.cis);
+    cis_table_load<T>(tab, a.cis);
     __syncthreads();
   }
   const int lane = threadIdx.x & 63;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed>()), kMixed ? 7 : 8) v
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
           const double ph = fma(u, p[i].l, fma(v, p[i].m, gg[t].z * p[i].n1));
-          const double2 cs = cis2pi_f64<kTileTable>(ph, tab);
+          const double2 cs = cis2pi_f64<T>(ph, tab);
           const double x = fma(p[i].q11, qg[t].x, fma(p[i].q12x2, qg[t].y, fma(p[i].q22, qg[t].z, c0[i])));
           const double own = pow_m32_f64(x);                        // own model / spec, real after the shift
           enter_cell(L[i], acc, a.err, nproc, rint(__dmul_rn(u, p[i].theta)), rint(__dmul_rn(v, p[i].theta)));
@@ -653,14 +653,23 @@ hipError_t run_vp(ExtractArgs a, const UpdateArgs &u, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <bool kMixed, int NS, int G>
+// FP64: the 1024-entry table, whose blocks are half the size, for 8 to 127 tiles
+// where the launch is less than 1.6 rounds of the resident waves.  2048 | 1024
+// entries, us: 5,700, 60,000, 200,000 and 240,000 visibilities of 2,000, 3,000,
+// 1,000 and 1,000 sources 195 | 156, 472 | 430, 547 | 485 and 557 | 495; at 18,102
+// waves (1,158,361 of 448) 840 | 866; 7 tiles (500,000 of 448) 460 | 519, 157 of
+// them (2,000 of 10,000) 244 | 270.
+template <bool kMixed, int NS, int G, int T>
 hipError_t run_tiles(ExtractArgs a, hipStream_t st) {
   const Sorted &v = a.sv;
-  auto kern = k_extract<kMixed, NS, G>;
-  constexpr int kW = waves_per_block<kMixed>();
+  auto kern = k_extract<kMixed, NS, G, T>;
+  constexpr int kW = waves_per_block<kMixed, T>();
   a.n_tiles = (a.n_src + 64 * NS - 1) / (64 * NS);
-  a.chunk = (int32_t)chunk_size<kMixed>(v.n_vis, a.n_tiles, resident_blocks(kern, 64 * kW) * kW);
+  const int64_t capacity = resident_blocks(kern, 64 * kW) * kW;
+  a.chunk = (int32_t)chunk_size<kMixed>(v.n_vis, a.n_tiles, capacity);
   a.n_chunks = (v.n_vis + a.chunk - 1) / a.chunk;
+  if constexpr (!kMixed && T == 2048)
+    if (a.n_tiles >= 8 && a.n_tiles < 128 && a.n_chunks * a.n_tiles * 5 < 8 * capacity) return run_tiles<kMixed, NS, G, 1024>(a, st);
   hipLaunchKernelGGL(kern, dim3(grid_blocks(a.n_chunks, a.n_tiles, kW)), dim3(64 * kW), 0, st, a, v.geo, v.quad, v.res,
                      reinterpret_cast<const uint64_t *>(v.wt), a.acc.cell);
   return hipGetLastError();
@@ -682,7 +691,7 @@ hipError_t launch_extract(const ExtractArgs &a, int mixed, hipStream_t st, const
     if (a.n_src == 1) return mixed ? run_vp<true, 1, false>(a, none, st) : run_vp<false, 1, false>(a, none, st);
     return mixed ? run_vp<true, 2, false>(a, none, st) : run_vp<false, 2, false>(a, none, st);
   }
-  return mixed ? run_tiles<true, kNsMixed, kGroupMixed>(a, st) : run_tiles<false, kNsF64, kGroupF64>(a, st);
+  return mixed ? run_tiles<true, kNsMixed, kGroupMixed, 1024>(a, st) : run_tiles<false, kNsF64, kGroupF64, 2048>(a, st);
 }
 
 }  // namespace rlf

@@ -1,7 +1,8 @@
 """The extraction on both sides of the lines between its two kernels, against
 the oracle: small observations by the size of the catalogue and by the number
 of pairs; and chunks of visibilities, whose number is rounded up to a multiple
-of eight between 9 and 63, cut by the shortest step and by the fill."""
+of eight between 9 and 63, cut by the shortest step and by the fill, and in FP64
+on both sides of the smaller table's range of tiles and of waves."""
 import pytest
 
 from tests import test_gpu_extract_vp as vp
@@ -25,7 +26,7 @@ def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
 
 
 @pytest.mark.parametrize("mixed", [False, True])
-@pytest.mark.parametrize("rows,n_src", [(7, 2100), (2048, 2100), (2049, 2100), (5003, 2049), (16129, 2100), (16385, 2049),
-                                        (700001, 200)])
+@pytest.mark.parametrize("rows,n_src", [(7, 2100), (2048, 2100), (2049, 2100), (2049, 8129), (5003, 2049),
+                                        (16129, 2100), (16385, 2049), (90001, 2100), (120001, 4000), (700001, 200)])
 def test_chunks_of_source_tiles(rows, n_src, mixed):
-    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 100000 else "cells")
+    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 20000 else "cells")
