@@ -50,26 +50,28 @@ constexpr int32_t kNoKey = INT32_MIN;          // the same for the previous run'
 
 // Catalogues of at most kVpSources sources go through k_extract_vp, larger
 // ones through k_extract: its lanes are sources, and with few tiles a chunk's
-// scalar loads are shared by few waves (one tile alone takes 1.75 times what
-// it takes among 16).  Measured, FP64, 9,266,880 visibilities, k_extract /
-// k_extract_vp with the gather: 64 sources 1.72 / 1.48 ms, 128 sources 3.21 /
-// 2.6 ms; 1,158,361 visibilities: 64 sources 0.36 / 0.26 ms, 128 0.48 / 0.46,
-// 150 0.47 / 0.54; the mixed form crosses at the same place.
-constexpr int kVpSources = 128;
+// scalar loads are shared by few waves.  k_extract | k_extract_vp, us: 1,158,361
+// visibilities, 130, 160 and 192 sources FP64 443 | 394, 475 | 448 and 510 | 510,
+// 160, 192 and 256 mixed 405 | 354, 407 | 397 and 467 | 480; 5,000,000, 160, 192
+// and 256 FP64 1,717 | 1,513, 1,771 | 1,769 and 2,137 | 2,317, 192 and 256 mixed
+// 1,227 | 1,195 and 1,505 | 1,556.
+constexpr int kVpSourcesF64 = 160, kVpSourcesMixed = 192;
 // ... and so do launches that would leave the chip idle through k_extract:
 // fewer than kTileWaves waves of kMinChunk visibilities (11,400 visibilities,
-// 100 sources: 156 us against 37).  Its waves take two sources at a time, each
+// 100 sources: 156 us against 37; 240,000 and 640, 9,380 waves, FP64 402 | 354,
+// mixed 297 | 282; 800,000 and 256, 12,500, 486 | 453 and 357 | 347; 500,000 and
+// 448, 13,678, FP64 460 | 513).  Its waves take two sources at a time, each
 // at least a step of 64 visibilities, two reductions and eight atomics, so
 // large catalogues go the other way.  k_extract | k_extract_vp, us: 11,400
 // visibilities, 1,000, 1,200 and 4,000 sources FP64 179 | 137, 173 | 178 and
-// 351 | 692, mixed 106 | 144, 123 | 152 and 314 | 622; 20,000, 800 and 2,000
-// FP64 122 | 112 and 184 | 216, mixed 92 | 77 and 149 | 180; 2,000, 2,000 and
+// 351 | 692, mixed 106 | 113, 123 | 130 and 314 | 622; 20,000, 800 and 2,000
+// FP64 122 | 84 and 184 | 216, mixed 92 | 76 and 149 | 180; 2,000, 2,000 and
 // 10,000 FP64 178 | 92 and 250 | 991, mixed 89 | 80 and 239 | 893.
-constexpr int64_t kMinChunk = 256, kTileWaves = 4096;
+constexpr int64_t kMinChunk = 256, kTileWaves = 12600;
 constexpr int64_t kVpCatalogueF64 = 1024, kVpCatalogueMixed = 800, kVpCatalogueTiny = 2048, kTinyPairs = 4000000;
 
 bool visibilities_on_lanes(int64_t n_vis, int64_t n_src, int mixed) {
-  if (n_src <= kVpSources) return true;
+  if (n_src <= (mixed ? kVpSourcesMixed : kVpSourcesF64)) return true;
   if ((n_vis + kMinChunk - 1) / kMinChunk * ((n_src + 63) / 64) >= kTileWaves) return false;
   return n_src <= (mixed ? kVpCatalogueMixed : kVpCatalogueF64) ||
          (n_src <= kVpCatalogueTiny && n_vis * n_src <= kTinyPairs);
@@ -338,7 +340,7 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8
 }
 
 // Visibility-parallel extraction: small catalogues, small observations, the
-// chunks of a sequential refinement (kVpSources, kTileWaves).  A wave takes a.chunk steps of 64
+// chunks of a sequential refinement (visibilities_on_lanes).  A wave takes a.chunk steps of 64
 // consecutive sorted visibilities, one per lane (coalesced loads, the next
 // step's issued before this one's arithmetic), for NS sources at a time
 // (their records wave-uniform, so the loads serve both), and evaluates each

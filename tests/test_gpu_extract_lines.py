@@ -1,6 +1,6 @@
 """The extraction on both sides of the lines between its two kernels, against
 the oracle: small observations by the size of the catalogue and by the number
-of pairs; and chunks of visibilities, whose number is rounded up to a multiple
+of pairs, large ones by the size of the catalogue; and chunks of visibilities, whose number is rounded up to a multiple
 of eight between 9 and 63, cut by the shortest step and by the fill, and in FP64
 on both sides of the smaller table's range of tiles and of waves."""
 import pytest
@@ -30,3 +30,10 @@ def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
                                         (16129, 2100), (16385, 2049), (90001, 2100), (120001, 4000), (700001, 200)])
 def test_chunks_of_source_tiles(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 20000 else "cells")
+
+
+@pytest.mark.parametrize("rows,n_src,mixed", [(1612801, 160, False), (1612801, 161, False), (1075201, 192, True),
+                                              (1075201, 193, True), (806400, 200, True), (806144, 200, True),
+                                              (806400, 200, False), (806144, 200, False)])
+def test_catalogue_of_a_large_observation(rows, n_src, mixed):
+    vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one")
