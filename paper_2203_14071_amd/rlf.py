@@ -197,9 +197,12 @@ class Context:
             raise RlfError(rc, "rlf_create failed")
         self.h = h
         self.device = device
+        self._owned = {}
 
     def close(self):
         if getattr(self, "h", None):
+            while self._owned:                                # the newest first: a pass before its facets
+                _release(*self._owned.popitem()[1])
             lib().rlf_destroy(self.h)
             self.h = None
 
@@ -306,10 +309,46 @@ def _fit_structs(out, mode, window, want_surface, fallback, check_stride=0):
     return o, r
 
 
-class Pass:
+class _Owned:
+    """An object of a context (facets, a pass, the network).  The handle is in a
+    cell that the context holds too, and closing the context frees what is still
+    there: the library's objects use their context when they are freed, and of a
+    reference cycle (a traceback's frames) Python may finalise the context first."""
+
+    _free: str
+
     def __init__(self, ctx: Context, h):
         self.ctx = ctx
-        self.h = h
+        self._cell = [h]
+        ctx._owned[id(self._cell)] = (self._free, self._cell)
+
+    @property
+    def h(self):
+        return self._cell[0]
+
+    def free(self):
+        self.ctx._owned.pop(id(self._cell), None)
+        _release(self._free, self._cell)
+
+    def __del__(self):
+        # at interpreter exit the HIP runtime may already be gone: leave the
+        # device memory to the process teardown
+        if sys is None or sys.is_finalizing():
+            return
+        try:
+            self.free()
+        except Exception:
+            pass
+
+
+def _release(free, cell):
+    h, cell[0] = cell[0], None
+    if h:
+        getattr(lib(), free)(h)
+
+
+class Pass(_Owned):
+    _free = "rlf_pass_free"
 
     def launch(self):
         return self.ctx._check(lib().rlf_pass_launch(self.h))
@@ -320,41 +359,9 @@ class Pass:
         self.ctx._check(lib().rlf_pass_tiles(self.h, t, u))
         return list(t), list(u)
 
-    def free(self):
-        if self.h:
-            lib().rlf_pass_free(self.h)
-            self.h = None
 
-    def __del__(self):
-        # at interpreter exit the HIP runtime may already be gone: leave the
-        # device memory to the process teardown
-        if sys is None or sys.is_finalizing():
-            return
-        try:
-            self.free()
-        except Exception:
-            pass
-
-
-class Facets:
-    def __init__(self, ctx: Context, h):
-        self.ctx = ctx
-        self.h = h
-
-    def free(self):
-        if self.h:
-            lib().rlf_facets_free(self.h)
-            self.h = None
-
-    def __del__(self):
-        # at interpreter exit the HIP runtime may already be gone: leave the
-        # device memory to the process teardown
-        if sys is None or sys.is_finalizing():
-            return
-        try:
-            self.free()
-        except Exception:
-            pass
+class Facets(_Owned):
+    _free = "rlf_facets_free"
 
     def info(self):
         n_src, n_cells, n_dense = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
@@ -382,30 +389,16 @@ def _np_ptr(a):
     return None if a is None else ctypes.c_void_p(a.ctypes.data)
 
 
-class Mlp:
+class Mlp(_Owned):
     """The grid-narrowing network (rlf_mlp_*); tensors are torch device tensors."""
 
+    _free = "rlf_mlp_free"
+
     def __init__(self, ctx: Context, max_batch=512):
-        self.ctx = ctx
         h = _c_vp()
         ctx._check(lib().rlf_mlp_create(ctx.h, int(max_batch), ctypes.byref(h)))
-        self.h = h
+        super().__init__(ctx, h)
         self.n_params = int(lib().rlf_mlp_num_params())
-
-    def free(self):
-        if self.h:
-            lib().rlf_mlp_free(self.h)
-            self.h = None
-
-    def __del__(self):
-        # at interpreter exit the HIP runtime may already be gone: leave the
-        # device memory to the process teardown
-        if sys is None or sys.is_finalizing():
-            return
-        try:
-            self.free()
-        except Exception:
-            pass
 
     def set_state(self, params, m=None, v=None, step=0):
         p = np.ascontiguousarray(params, dtype=np.float32)
