@@ -8,9 +8,10 @@ One step is one pass of the whole data-parallel path over the SKA-MID-like
   2. extraction of every source into its facet (+ compaction)
   3. full-grid fit of every source: 6,333 ellipticities x 20 scale knots,
      flux and scale marginalised, thresholded-moment estimate
-with the observation already resident in HBM.  Prints one JSON line.
+with the observation already resident in HBM.  Prints one JSON line; what it
+leaves out for its length (LINE_LEAVES_OUT) goes to --detail FILE.
 
-    python bench.py [--gpus 1] [--steps 10] [--warmup 2] [--precision fp64|mixed]
+    python bench.py [--gpus 1] [--steps 10] [--warmup 2] [--precision fp64|mixed] [--detail FILE]
 """
 from __future__ import annotations
 
@@ -367,6 +368,37 @@ def mlp_bench(batches=(512, 4096), steps=20, infer_rows=10_000):
     return res
 
 
+# Left out of the printed line, wherever they stand below its top level: whoever
+# keeps the last 16,000 characters of the output lost the head of a longer line,
+# and with it the value.
+LINE_LEAVES_OUT = frozenset((
+    "kernel", "stage", "bound", "peak", "unit", "basis", "slots_per_unit", "issue", "flop_basis", "units_per_s",
+    "own_mix_ceiling", "probes", "kernel_mix", "loss_per_epoch", "noiseless_what", "what", "note", "workload",
+    "queue_tiles_per_bucket", "tiles_from_tuning", "gvis_per_s", "mean_window_points",
+    "full_grid_windows", "network_rms_e_vs_true", "network_rms_e_vs_full_grid_estimate", "fit_sources_per_s",
+    "of_which_features_and_network_ms", "m1_err", "m2_err", "c1", "c2", "bad_before_refinement", "refined",
+    "posterior_sd_quantiles"))
+LINE_LIMIT = 12000
+
+
+def printed_line(res):
+    """The JSON line of a result: the headline and the roofline whole, the rest
+    without its details, as one line of at most LINE_LIMIT characters."""
+    def short(v):
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items() if k not in LINE_LEAVES_OUT}
+        if isinstance(v, list):
+            return [short(x) for x in v]
+        return float(f"{v:.6g}") if isinstance(v, float) else v
+    out = {k: v if k in ("config", "roofline") or not isinstance(v, (dict, list)) else short(v) for k, v in res.items()}
+    extra = [k for k in reversed(list(out)) if isinstance(out[k], (dict, list)) and k not in ("config", "roofline", "stage_ms")]
+    line = json.dumps(out)
+    while len(line) > LINE_LIMIT and extra:                   # never at the sizes above: the headline goes out whole
+        out[extra.pop(0)] = "left out for length"
+        line = json.dumps(out)
+    return line
+
+
 def _values(text, typ):
     """Comma-separated list of values; '' or 'none' is the empty list."""
     return [] if text in ("", "none") else [typ(v) for v in text.split(",")]
@@ -408,6 +440,7 @@ def main():
                     help="only run the VALU issue-rate probe (roofline ceilings) and print its JSON")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain 1 GiB device-to-device copy (reference for HBM byte counters)")
+    ap.add_argument("--detail", metavar="FILE", help="write the whole result there, as JSON")
     args = ap.parse_args()
     if args.mlp_bench:
         print(json.dumps(mlp_bench()), flush=True)
@@ -452,7 +485,7 @@ def main():
                          lattice_strides)
     res = main_form["json"]
     if args.only:
-        print(json.dumps(res), flush=True)
+        finish(res, args.detail)
         return
     other = "mixed" if args.precision == "fp64" else "fp64"
     other_form = run_form(other, args.steps, args.warmup, lattice_strides=lattice_strides)
@@ -499,7 +532,14 @@ def main():
         log(f"[bench] VALU probe not run: {e}")
     if cpu is not None:
         res["cpu_baseline"] = cpu
-    print(json.dumps(res), flush=True)
+    finish(res, args.detail)
+
+
+def finish(res, detail):
+    if detail:
+        with open(detail, "w") as f:
+            json.dump(res, f)
+    print(printed_line(res), flush=True)
 
 
 def _sources_de_above(de, tol=1e-3):
