@@ -163,7 +163,12 @@ int rlf_alpha_from_flux(const double *flux_jy_host, int64_t n, double add, doubl
  *     / (1 + 4 pi^2 alpha^2 |A^{-T} (u,v)|^2)^{3/2},
  * with A from Eq. 2 and the catalogue's (e1, e2).  `out` is device
  * [n_rows*n_chan] in the context's complex type; see the mode enum.
- * obs->vis is read only in RLF_MODEL_RESIDUAL and may then alias out. */
+ * obs->vis is read only in RLF_MODEL_RESIDUAL and may then alias out.
+ * A visibility's value does not depend on the other rows of the call, in the
+ * mixed form with three or more channels to FP32 rounding: there the kernel
+ * is chosen by the call's rows, channels and sources, and the residual that
+ * rlf_pass_create and the serial refinement form in their own order agrees
+ * with this one to the same rounding. */
 int rlf_model_vis(rlf_ctx *ctx, const rlf_obs *obs, const rlf_catalog *cat,
                   int64_t src_begin, int64_t src_end, void *out, int mode);
 

@@ -46,8 +46,8 @@ __global__ __launch_bounds__(256) void k_count(CompactArgs a) {
 }
 
 // Up to this many sources each block of k_write adds up the counts of the
-// sources before its own, four loads per thread at most: a launch of 4.5 us
-// less, and k_write takes as long as before (5 us for 10 sources, 37 for 1,000).
+// sources before its own, of both kinds, eight loads per thread at most: k_write takes
+// 5 us for 10 sources and 37 for 1,000 either way, and k_scan's 4.5 us are saved.
 constexpr int kOwnScan = 1024;
 
 // Exclusive scans over sources (block 0: cells, block 1: folded cells).
@@ -108,12 +108,11 @@ __device__ __forceinline__ double4 fit_record(int ix, int iy, double theta, doub
 // mirror image, W Re(Vbar) f and W f^2, add before f is known.  An aperture-
 // synthesis track covers both halves of the plane, so this nearly halves the
 // likelihood's work: on the 197-antenna array 270 cells become 153 records
-// per source, and extraction plus grid of 1000 sources went from 29.2 to
-// 22.7 ms (300 sources, lattice-seeded: 2.01 to 1.26 ms; 100 sources over
-// 5 x 5 offsets with the refinement: 11.7 to 7.3 ms).  The mixed form's grid
-// keeps one FP32 record per cell (its results stay those of the cells one by
-// one); its FP64 recheck reads
-// the folded ones.
+// per source, and extraction plus grid of 1000 sources take 22.7 ms (with
+// the cells one by one 29.2; 300 sources, lattice-seeded, 1.26 and 2.01; 100
+// sources over 5 x 5 offsets with the refinement 7.3 and 11.7).  The mixed
+// form's grid keeps one FP32 record per cell (its results are those of the
+// cells one by one); its FP64 recheck reads the folded ones.
 template <bool kMixed>
 __global__ __launch_bounds__(256) void k_write(CompactArgs a, int own_scan) {
   __shared__ int wsum[4];

@@ -340,9 +340,9 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8
 }
 
 // Visibility-parallel extraction: small catalogues, small observations, the
-// chunks of a sequential refinement (visibilities_on_lanes).  A wave takes a.chunk steps of 64
-// consecutive sorted visibilities, one per lane (coalesced loads, the next
-// step's issued before this one's arithmetic), for NS sources at a time
+// chunks of a sequential refinement (visibilities_on_lanes).  A wave takes
+// a.chunk steps of 64 consecutive sorted visibilities, one per lane (coalesced
+// loads, the next step's issued before this one's arithmetic), for NS sources at a time
 // (their records wave-uniform, so the loads serve both), and evaluates each
 // pair exactly as k_extract does.  Along the sorted order a source stays in
 // one facet cell for runs of ~200 visibilities and alternates between two
@@ -351,8 +351,8 @@ __global__ __launch_bounds__((64 * waves_per_block<kMixed, T>()), kMixed ? 7 : 8
 // falls into one open cell (about three in four) costs three additions, a
 // step split between them a masked set of each, and only a third cell makes
 // the wave reduce the less recent one over its lanes and add it to memory
-// (four FP64 atomics); a segmented scan over the lanes at every step would
-// this replaces, cost about four times the pair arithmetic.
+// (four FP64 atomics).  A segmented scan over the lanes at every step would cost
+// about four times the pair arithmetic.
 __device__ __forceinline__ double from_lane(double x, int l) {   // l wave-uniform
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
                           __builtin_amdgcn_readlane(__double2loint(x), l));

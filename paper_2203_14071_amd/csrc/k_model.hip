@@ -11,16 +11,18 @@
 //   mixed form: phase and its fractional part (v_fract_f64, exact, in
 //               [0, 1) turns) in FP64, rounded to FP32 for v_sin/v_cos
 //               (argument in turns), profile and sum in FP32.  The three
-//               transcendental instructions take 24 of the 57 cycles of 64
+//               transcendental instructions take 24 of the 62 cycles of 64
 //               pairs; with several channels the phase and the quadratic
-//               form are formed once per row and group of channels.
+//               form are formed once per row and group of channels (54).
 // Two entry kernels: visibilities in caller order (rlf_model_vis), and the
 // residual in the facet object's uv-sorted order (extraction input).  Their
 // FP64 forms take a 2048-entry table (32 KB of LDS; sin's x^5 term drops,
 // one FMA per pair) in blocks of 512 threads, so that four blocks per CU
 // keep eight waves per SIMD in 128 KB of LDS; both form the sky sum with the
-// same table, so the two orders give the same residual values (mixed form:
-// to FP32 rounding where k_model_rows forms the one in caller order).
+// same table, so the two orders give the same residual values.  In the mixed form
+// with several channels they agree to FP32 rounding: k_model_rows scales a row's
+// phase and quadratic form per channel, and whether it forms a visibility's sum
+// depends on the rows, channels and sources of the call (row_channels).
 #include "rlf_devmath.h"
 #include "rlf_internal.h"
 #include "rlf_sky.h"

@@ -75,32 +75,20 @@ __device__ __forceinline__ double fma_vvs(double a, double b, double c) {
 // as described above.  T = 2048: |x| <= pi/2048 < 1.54e-3, and sin's x^5
 // term (< 7.2e-17) is dropped: sin to x^3 (truncation < x^5/5! < 7.2e-17,
 // below half an ulp of 1), cos to x^4 as before; fourteen VALU operations.
-// In two parts: the reduction with the table read, and the rest.
-struct CisPart {
-  double d;                                      // turns, |d| <= 1/(2T)
-  double2 tv;
-};
-template <int T>
-__device__ __forceinline__ CisPart cis_read(double phi, const double2 *tab) {
+template <int T = kCisTable>
+__device__ __forceinline__ double2 cis2pi_f64(double phi, const double2 *tab) {
   static_assert(T == 1024 || T == 2048, "table sizes with a derived truncation bound");
   constexpr double magic = turn_magic<T>();
   const double m = phi + magic;
-  return CisPart{phi - (m - magic), tab[(uint32_t)__double2loint(m) & (uint32_t)(T - 1)]};
-}
-template <int T>
-__device__ __forceinline__ double2 cis_finish(const CisPart &c) {
-  const double d = c.d, d2 = d * d;
+  const double2 tv = tab[(uint32_t)__double2loint(m) & (uint32_t)(T - 1)];
+  const double d = phi - (m - magic), d2 = d * d;   // turns, |d| <= 1/(2T)
   const double cx = fma(d2, fma_vvs(d2, kCos4, kCos2), 1.0);
   double sx;
   if constexpr (T == 1024)
     sx = d * fma_vvs(d2, fma_vvs(d2, kSin5, kSin3), kSin1);
   else
     sx = d * fma_vvs(d2, kSin3, kSin1);
-  return make_double2(fma(c.tv.x, cx, -(c.tv.y * sx)), fma(c.tv.x, sx, c.tv.y * cx));
-}
-template <int T = kCisTable>
-__device__ __forceinline__ double2 cis2pi_f64(double phi, const double2 *tab) {
-  return cis_finish<T>(cis_read<T>(phi, tab));
+  return make_double2(fma(tv.x, cx, -(tv.y * sx)), fma(tv.x, sx, tv.y * cx));
 }
 
 // (2/3) x^(-3/2), x >= 1 and finite.

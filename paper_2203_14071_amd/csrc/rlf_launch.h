@@ -10,7 +10,7 @@
 namespace rlf {
 
 // Resident blocks of a kernel on the current device (kept per kernel and
-// device; the value is a property of both, so a race writes it twice).
+// device; the value is a property of both, and found once).
 template <class K>
 int64_t resident_blocks(K kernel, int threads) {
   static std::mutex mu;
