@@ -698,15 +698,17 @@ hipError_t launch_knots(const FitArgs &a, hipStream_t st) {
 
 // Narrowed fits: k_window_knots takes the sources of at most this many
 // positions.  Where a launch fills the card k_fit_window is the better one
-// (its lanes form the quadratic form once instead of four times): 1000
-// sources of 31 x 31 points 844 us, in k_window_knots 879; 300 of about 60 x
-// 60 1,198 and 1,323, but 300 of 31 x 31 410 and 288, and 70 small facets'
-// whole grids 351 and 325.  The boxes are on the device, so a launch whose
-// boxes could fill the card is split by their size, two kernels each leaving
-// the other's sources at once, up to the number of sources where the idle
-// blocks cost more than that gains (2,000 sources of 3 x 3 points 479 us,
-// split 510).  The lattice and the boxes it leads to are small: one kernel
-// (1,000 sources 1,180 and 1,111 us, 2,000 sources 2,370 and 2,836).
+// (its lanes form the quadratic form once instead of four times).  k_fit_window
+// | k_window_knots, us, FP64 and mixed: 100 sources of 31 x 31 points 373 | 204
+// and 392 | 233, 300 469 | 425 and 497 | 420, 600 671 | 721 and 730 | 751; 300 of 17
+// x 17 373 | 187 and 412 | 234; whole grids of 40 405 | 362 and 413 | 346, of 80
+// 672 | 706 and 656 | 645, of 150 1,170 | 1,237 and 1,113 | 1,120.  The boxes are on
+// the device, so a launch whose boxes could fill the card is split by their
+// size, two kernels each leaving the other's sources at once, up to the
+// number of sources where the idle blocks cost more than that gains (2,000 of 3 x
+// 3 points 390 and 470, split about 510 in FP64).  The lattice and the boxes it
+// leads to are small: one kernel (every fourth point, 1,000 sources 1,139 |
+// 1,081 and 1,278 | 1,188, 2,000 2,489 | 2,568 and 2,619 | 2,594).
 constexpr int kLatticeSources = 1000, kKnotWindows = 80, kSplitWindows = 1500, kKnotWork = 400000;
 
 int knot_positions(const FitArgs &a, int positions) {
