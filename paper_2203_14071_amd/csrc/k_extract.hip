@@ -606,9 +606,12 @@ int64_t even_chunks(int64_t chunks) {
 // Visibilities per wave of k_extract.  A wave's start and end cost its lanes two
 // open runs each (eight atomics), so that few visibilities per wave are slow,
 // and a chunk of the dense core of the plane takes longer than one of its
-// outskirts, which only many waves even out: 640 in the mixed form, 448 in FP64
-// (5,000,000 visibilities, 1000 sources, 520, 640, 1000 and 2048 each: mixed 4,843,
-// 4,800, 4,819 and 4,950 us, FP64 448, 1000 and 2048 6,800, 6,781 and 7,106), fewer
+// outskirts, which only many waves even out.  448, 768 and 2048 each, us: FP64
+// 500,000 visibilities and 448 sources 463 | 632 | 923, 2,316,722 and 1000 3,209 |
+// 3,253 | 3,538, 3000 9,399 | 9,306 | 9,322, 9,266,880 and 1000 13,116 | 12,850 |
+// 13,230; 448, 640, 768 and 2048 mixed 1,158,361 and 320 577 | 530 | 554 | 716,
+// 9,266,880 and 1000 9,117 | 8,900 | 8,863 | 8,958.  So 448 in FP64, 768 where that
+// makes ten rounds of the resident waves, and 640 in the mixed form; fewer
 // where those would fill less than kFill % of the resident waves (60,000 and 1,500
 // sources, filling 35, 50 and 70 %: mixed 231 | 255 | 248 us, FP64 311 | 327 | 286),
 // and a multiple of eight: each wave's first loads then start on a line of 128
@@ -616,9 +619,10 @@ int64_t even_chunks(int64_t chunks) {
 // 512 2,157 and 2,184; 1000 sources 7,421 and 6,800).
 template <bool kMixed>
 int64_t chunk_size(int64_t n_vis, int64_t n_tiles, int64_t capacity) {
-  constexpr int64_t kFull = kMixed ? 640 : 448, kFill = kMixed ? 35 : 70, kAlign = 8;
+  constexpr int64_t kFill = kMixed ? 35 : 70, kAlign = 8;
+  const int64_t full = kMixed ? 640 : n_vis * n_tiles >= 10 * 768 * capacity ? 768 : 448;
   const int64_t waves = std::max<int64_t>(1, capacity * kFill / 100);
-  const int64_t len = std::max(kMinChunk, std::min(kFull, (n_vis * n_tiles + waves - 1) / waves));
+  const int64_t len = std::max(kMinChunk, std::min(full, (n_vis * n_tiles + waves - 1) / waves));
   const int64_t chunks = std::max<int64_t>(1, even_chunks((n_vis + len - 1) / len));
   return std::max(kAlign, ((n_vis + chunks - 1) / chunks + kAlign - 1) / kAlign * kAlign);
 }

@@ -27,7 +27,8 @@ def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
 
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("rows,n_src", [(7, 2100), (2048, 2100), (2049, 2100), (2049, 8129), (5003, 2049),
-                                        (16129, 2100), (16385, 2049), (90001, 2100), (120001, 4000), (700001, 200)])
+                                        (16129, 2100), (16385, 2049), (90001, 2100), (120001, 4000), (700001, 200),
+                                        (400730, 10000), (400731, 10000)])
 def test_chunks_of_source_tiles(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 20000 else "cells")
 
