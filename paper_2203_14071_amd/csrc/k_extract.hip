@@ -68,13 +68,22 @@ constexpr int kVpSourcesF64 = 160, kVpSourcesMixed = 192;
 // FP64 122 | 84 and 184 | 216, mixed 92 | 76 and 149 | 180; 2,000, 2,000 and
 // 10,000 FP64 178 | 92 and 250 | 991, mixed 89 | 80 and 239 | 893.
 constexpr int64_t kMinChunk = 256, kTileWaves = 12600;
-constexpr int64_t kVpCatalogueF64 = 1024, kVpCatalogueMixed = 800, kVpCatalogueTiny = 2048, kTinyPairs = 4000000;
+constexpr int64_t kVpCatalogueF64 = 1024, kVpCatalogueMixed = 800;
+// ... the larger of them only where there are enough visibilities for the steps
+// and few enough waves for the tiles (30,000 and 1,500 FP64 185 | 168, mixed 159 |
+// 148; 20,000 and 1,500 145 | 158 and 114 | 120; 150,000 and 1,000 mixed 351 | 309,
+// 200,000 and 1,000, 12,512 waves, 390 | 430), or where all is small (600 and 3,000
+// FP64 116 | 85, mixed 86 | 73; 2,000 and 3,000 mixed 96 | 135).
+constexpr int64_t kVpCatalogueLarge = 1536, kVpLargeVis = 25000, kVpLargeWaves = 10400;
+constexpr int64_t kVpCatalogueTiny = 3072, kTinyPairs = 4000000;
 
 bool visibilities_on_lanes(int64_t n_vis, int64_t n_src, int mixed) {
   if (n_src <= (mixed ? kVpSourcesMixed : kVpSourcesF64)) return true;
-  if ((n_vis + kMinChunk - 1) / kMinChunk * ((n_src + 63) / 64) >= kTileWaves) return false;
-  return n_src <= (mixed ? kVpCatalogueMixed : kVpCatalogueF64) ||
-         (n_src <= kVpCatalogueTiny && n_vis * n_src <= kTinyPairs);
+  const int64_t waves = (n_vis + kMinChunk - 1) / kMinChunk * ((n_src + 63) / 64);
+  if (waves >= kTileWaves) return false;
+  if (n_src <= (mixed ? kVpCatalogueMixed : kVpCatalogueF64)) return true;
+  if (n_src <= kVpCatalogueLarge && n_vis >= kVpLargeVis && waves < kVpLargeWaves) return true;
+  return n_src <= kVpCatalogueTiny && n_vis * n_src <= kTinyPairs;
 }
 
 // Work item of a wave: blocks go to the eight XCDs round-robin by index; item
@@ -606,23 +615,25 @@ int64_t even_chunks(int64_t chunks) {
 // Visibilities per wave of k_extract.  A wave's start and end cost its lanes two
 // open runs each (eight atomics), so that few visibilities per wave are slow,
 // and a chunk of the dense core of the plane takes longer than one of its
-// outskirts, which only many waves even out.  448, 768 and 2048 each, us: FP64
-// 500,000 visibilities and 448 sources 463 | 632 | 923, 2,316,722 and 1000 3,209 |
-// 3,253 | 3,538, 3000 9,399 | 9,306 | 9,322, 9,266,880 and 1000 13,116 | 12,850 |
-// 13,230; 448, 640, 768 and 2048 mixed 1,158,361 and 320 577 | 530 | 554 | 716,
-// 9,266,880 and 1000 9,117 | 8,900 | 8,863 | 8,958.  So 448 in FP64, 768 where that
-// makes ten rounds of the resident waves, and 640 in the mixed form; fewer
-// where those would fill less than kFill % of the resident waves (60,000 and 1,500
-// sources, filling 35, 50 and 70 %: mixed 231 | 255 | 248 us, FP64 311 | 327 | 286),
-// and a multiple of eight: each wave's first loads then start on a line of 128
-// bytes of every stream (5,000,000 and 256 sources, FP64, 489 each 2,600 us, 448 and
-// 512 2,157 and 2,184; 1000 sources 7,421 and 6,800).
+// outskirts, which only many waves even out: 1/18 of what a resident wave gets of
+// the launch, between kBase and 2048.  FP64, 448, 768, 1024 and 2048 each, us:
+// 500,000 visibilities and 448 sources 463, 632, 567 and 923, 2,316,722 and 1000
+// 3,209, 3,253, 3,311 and 3,538, 9,266,880 and 1000 13,116, 12,850, 12,818 and
+// 13,230, of eight channels and 5000 (640 for 448) 468, 464, 459 and 450 ms.  Mixed,
+// 448, 640, 1024 and 2048: 1,158,361 and 320 577, 530, 562 and 716, 9,266,880 and
+// 1000 9,117, 8,900, 8,831 and 8,958, of eight channels and 5000 (640 on) 315, 311 and
+// 309 ms.  Fewer than kBase where those would fill less than kFill % of the
+// resident waves (60,000 and 1,500 sources, filling 35, 50 and 70 %: mixed 231 | 255
+// | 248 us, FP64 311 | 327 | 286).  A multiple of eight: each wave's first loads then
+// start on a line of 128 bytes of every stream (5,000,000 and 256 sources, FP64, 489
+// each 2,600 us, 448 and 512 2,157 and 2,184; 1000 sources 7,421 and 6,800).
 template <bool kMixed>
 int64_t chunk_size(int64_t n_vis, int64_t n_tiles, int64_t capacity) {
-  constexpr int64_t kFill = kMixed ? 35 : 70, kAlign = 8;
-  const int64_t full = kMixed ? 640 : n_vis * n_tiles >= 10 * 768 * capacity ? 768 : 448;
-  const int64_t waves = std::max<int64_t>(1, capacity * kFill / 100);
-  const int64_t len = std::max(kMinChunk, std::min(full, (n_vis * n_tiles + waves - 1) / waves));
+  constexpr int64_t kBase = kMixed ? 640 : 448, kFill = kMixed ? 35 : 70, kAlign = 8;
+  capacity = std::max<int64_t>(1, capacity);
+  const int64_t share = (n_vis * n_tiles + capacity - 1) / capacity;
+  const int64_t full = std::min<int64_t>(2048, std::max(kBase, share / 18));
+  const int64_t len = std::max(kMinChunk, std::min(full, share * 100 / kFill));
   const int64_t chunks = std::max<int64_t>(1, even_chunks((n_vis + len - 1) / len));
   return std::max(kAlign, ((n_vis + chunks - 1) / chunks + kAlign - 1) / kAlign * kAlign);
 }

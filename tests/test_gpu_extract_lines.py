@@ -12,8 +12,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("rows,n_src,mixed", [(5200, 800, True), (5200, 801, True), (4000, 1024, False),
                                               (4000, 1025, False), (2000, 2000, True), (2001, 2000, True),
-                                              (2000, 2000, False), (2001, 2000, False), (600, 2048, True),
-                                              (600, 2049, True), (65, 2048, False), (65, 2049, False)])
+                                              (2000, 2000, False), (2001, 2000, False), (600, 3072, True),
+                                              (600, 3073, True), (65, 3072, False), (65, 3073, False),
+                                              (24999, 1100, False), (25000, 1100, False), (25000, 1536, True),
+                                              (25000, 1537, True), (147968, 1100, True), (147969, 1100, True)])
 def test_catalogue_of_a_small_observation(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "cells")
 
@@ -28,7 +30,7 @@ def test_chunks_in_multiples_of_eight(rows, n_src, mixed):
 @pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("rows,n_src", [(7, 2100), (2048, 2100), (2049, 2100), (2049, 8129), (5003, 2049),
                                         (16129, 2100), (16385, 2049), (90001, 2100), (120001, 4000), (700001, 200),
-                                        (400730, 10000), (400731, 10000)])
+                                        (400730, 10000), (900001, 10000)])
 def test_chunks_of_source_tiles(rows, n_src, mixed):
     vp.test_small_extraction_against_oracle(rows, n_src, mixed, "one" if rows > 20000 else "cells")
 
