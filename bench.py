@@ -53,12 +53,12 @@ MODEL_FLOP_PAIR = 19
 # bracket) at this workload, from rocprofv3 FETCH_SIZE and WRITE_SIZE (each
 # scaled by a plain copy's reading), for the kernels as they are now; None
 # where not measured.  profiles/step_kernels_ska_mid_1k_{fp64,mixed}.md:
-#   extraction (k_extract): fetch 1863.2 / 1188.9 MB, write 1096.5 / 983.3 MB
-#   likelihood (k_fit + k_estimate): fetch 89.8 + 51.9 / 79.5 + 79.2 MB,
+#   extraction (k_extract): fetch 1719.3 / 1186.9 MB, write 1879.2 / 1653.3 MB
+#   likelihood (k_fit + k_estimate): fetch 89.8 + 51.5 / 79.4 + 74.8 MB,
 #     write 51.3 + 0.3 / 51.3 + 0.7 MB
 #   sky model (k_model): fetch 373.1 / 298.7 MB, write 148.3 / 74.1 MB
-TRAFFIC_BYTES = {"fp64": {"extract": 2959.7e6, "fit": 193.3e6, "model": 521.4e6},
-                 "mixed": {"extract": 2172.2e6, "fit": 210.7e6, "model": 372.8e6}}
+TRAFFIC_BYTES = {"fp64": {"extract": 3598.5e6, "fit": 192.9e6, "model": 521.4e6},
+                 "mixed": {"extract": 2840.2e6, "fit": 206.2e6, "model": 372.8e6}}
 # VALU roofline in lane-slots: 256 CUs x 64 lanes x 2.4 GHz = 3.93e13 lane-slots/s.
 # Work per unit = the method's necessary operations in each form (not a
 # compiled count), priced with gfx950's measured rates (the VALU probe,
@@ -104,10 +104,10 @@ SLOTS = {f: {k: round(sum(v.values()), 3) for k, v in d.items()} for f, d in SLO
 # rate: slots = VALU instructions with each v_rsq_f64 counted 4, per CU per
 # cycle at that clock.  The VALU probe (probe/valu_probe.hip, run by the
 # benchmark) measures what instruction streams of each kind reach.
-VALU_WORK = {"fp64": {"extract": (5.805e9, 1.48e8, 2.293e9), "fit": (3.065e9, 3.37e8, 2.331e9),
-                      "model": (4.062e9, 1.45e8, 2.090e9)},
-             "mixed": {"extract": (4.745e9, 0.0, 2.335e9), "fit": (4.267e9, 4.16e6, 2.348e9),
-                       "model": (2.321e9, 0.0, 2.255e9)}}
+VALU_WORK = {"fp64": {"extract": (5.831e9, 1.48e8, 2.252e9), "fit": (3.065e9, 3.37e8, 2.316e9),
+                      "model": (4.062e9, 1.45e8, 2.048e9)},
+             "mixed": {"extract": (4.753e9, 0.0, 2.332e9), "fit": (4.267e9, 4.16e6, 2.351e9),
+                       "model": (2.321e9, 0.0, 2.263e9)}}
 
 
 def log(*a):
